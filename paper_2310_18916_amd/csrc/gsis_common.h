@@ -39,7 +39,7 @@ struct Geo {
     int osize[8];
     int obase[8];
     int species;
-    double delta, omega, dr, Zr, A[4];
+    double delta, idelta, omega, dr, Zr, A[4];   // idelta = 1 / delta
     double inv_dt;
     // explicit interface values of the kinetic update: order 1 (upwind) or 2
     // (limited least-squares reconstruction); (K h)^3 of the Venkatakrishnan
@@ -80,6 +80,9 @@ struct BcInfo {
 // DSLOT), so the atomics of different blocks do not queue on one address;
 // readers take the max of the DSLOT partials.
 constexpr int DSLOT = 64, DSTRIDE = 16;
+// sets of partials: launch k of the solve fills set k mod 3, reads the one
+// before and clears the next
+constexpr int DSETS = 3;
 
 struct Dev {
     void *f0, *f1;     // [ncell + 1][nv]: row ncell is the sink of the sweep's stores for dead cells
@@ -152,14 +155,16 @@ struct Dev {
     double *ubsq, *ubhot;   // Grad-13 wall flux: per boundary face [12][unbf] the stress of the iterate, HoT_c
     double *corr;      // [ncell][NCORR]
     double *snap;      // [ncell][NSNAP]
-    // macroscopic solve, all structures of arrays [field][ncell] ([field][nface]
-    // for fbfix, Fb): W (double buffered), prims P, velocity gradient,
-    // high-order terms of the three + faces (six flux components each),
-    // residual R
-    double *W, *W2, *P, *grad, *hot, *R, *Dc, *Src, *fbfix, *Fb, *Gb;
+    // macroscopic solve.  Box: W with its residual, one record per cell (at
+    // most 14 words), double buffered (W, W2); high-order terms of the + faces,
+    // [axis][ncell][6], and what they and the fixed boundary parts add to the
+    // residual of every cell, Rc [ncell][6]; prims P and velocity gradient of W^{n+1/2} as
+    // [field][ncell]; boundary-face terms fbfix, Fb as [field][nface].
+    // Unstructured mesh: W, P, grad, residual R, Src as [field][ncell].
+    double *W, *W2, *P, *grad, *hot, *R, *Rc, *Src, *fbfix, *Fb, *Gb;
     double *ghot;      // [12][nface] Grad-13 wall flux: the face cell's HoT_c (sigma 6, q 3, qr 3)
     double *red;       // reduction scratch
-    unsigned long long *dmax;   // [2][DSLOT] partial maxima, one per 128-byte line (DSTRIDE words apart),
+    unsigned long long *dmax;   // [DSETS][DSLOT] partial maxima, one per 128-byte line (DSTRIDE words apart),
                                 // bit patterns of positive doubles
     int *errflag;
     // residual history of a batch (nullptr for a context on its own):
@@ -270,6 +275,73 @@ __device__ __forceinline__ double pow_pos(double x, double y)
     const double de = (double)e;
     const double lx = fma(de, 6.93147180369123816490e-01, fma(de, 1.90821492927058770002e-10, 2.0 * s * p));
     return exp_core(y * lx);
+}
+
+// a b + K with the literal K read from scalar registers.  As plain code the
+// compiler takes the two-operand form, whose addend is a vector register pair
+// written anew (two moves) at every use: half of the instructions of a
+// polynomial that is evaluated once, outside a loop that could keep them.
+__device__ __forceinline__ double fma_lit(double a, double b, double K)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(K));
+    return r;
+}
+
+// 1 / b by the hardware estimate and two Newton steps (within 1 ulp), b normal
+__device__ __forceinline__ double recip(double b)
+{
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    return fma(r, fma(-b, r, 1.0), r);
+}
+
+// exp_core and pow_pos for straight-line code (same series, same accuracy)
+__device__ __forceinline__ double exp_line(double x)
+{
+    const double n = rint(x * 1.4426950408889634074);
+    double r = fma(n, -6.93147180369123816490e-01, x);
+    r = fma(n, -1.90821492927058770002e-10, r);
+    double p = 1.0 / 479001600.0;
+    p = fma_lit(p, r, 1.0 / 39916800.0);
+    p = fma_lit(p, r, 1.0 / 3628800.0);
+    p = fma_lit(p, r, 1.0 / 362880.0);
+    p = fma_lit(p, r, 1.0 / 40320.0);
+    p = fma_lit(p, r, 1.0 / 5040.0);
+    p = fma_lit(p, r, 1.0 / 720.0);
+    p = fma_lit(p, r, 1.0 / 120.0);
+    p = fma_lit(p, r, 1.0 / 24.0);
+    p = fma_lit(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)n);
+}
+
+__device__ __forceinline__ double pow_line(double x, double y)
+{
+    int e;
+    double m = frexp(x, &e);
+    if (m < 0.70710678118654752440) {
+        m *= 2.0;
+        e -= 1;
+    }
+    const double s = (m - 1.0) * recip(m + 1.0), s2 = s * s;
+    double p = 1.0 / 23.0;
+    p = fma_lit(p, s2, 1.0 / 21.0);
+    p = fma_lit(p, s2, 1.0 / 19.0);
+    p = fma_lit(p, s2, 1.0 / 17.0);
+    p = fma_lit(p, s2, 1.0 / 15.0);
+    p = fma_lit(p, s2, 1.0 / 13.0);
+    p = fma_lit(p, s2, 1.0 / 11.0);
+    p = fma_lit(p, s2, 1.0 / 9.0);
+    p = fma_lit(p, s2, 1.0 / 7.0);
+    p = fma_lit(p, s2, 1.0 / 5.0);
+    p = fma_lit(p, s2, 1.0 / 3.0);
+    p = fma(p, s2, 1.0);
+    const double de = (double)e;
+    const double lx = fma(de, 6.93147180369123816490e-01, fma(de, 1.90821492927058770002e-10, 2.0 * s * p));
+    return exp_line(y * lx);
 }
 
 __device__ __forceinline__ double wave_sum(double v)

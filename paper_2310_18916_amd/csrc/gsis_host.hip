@@ -368,20 +368,20 @@ size_t layout(gsis_ctx *c, char *base)
     }
     carve(off, d.corr, n * NCORR, base);
     carve(off, d.snap, n * NSNAP, base);
-    carve(off, d.W, n * 6, base);
-    carve(off, d.W2, n * 6, base);
+    carve(off, d.W, n * 14, base);
+    carve(off, d.W2, n * 14, base);
     carve(off, d.P, n * 12, base);
     carve(off, d.grad, n * 9, base);
     carve(off, d.hot, n * 18, base);
     carve(off, d.R, n * 6, base);
-    carve(off, d.Dc, n, base);
+    carve(off, d.Rc, n * 6, base);
     carve(off, d.Src, n, base);
     carve(off, d.fbfix, nf * 6, base);
     carve(off, d.Fb, nf * 6, base);
     carve(off, d.Gb, nf, base);
     carve(off, d.ghot, nf * 12, base);
     carve(off, d.red, (size_t)(resid_blocks(g) + 1) * 6, base);
-    carve(off, d.dmax, (size_t)2 * DSLOT * DSTRIDE, base);
+    carve(off, d.dmax, (size_t)DSETS * DSLOT * DSTRIDE, base);
     carve(off, d.errflag, 4, base);
     return align256(off);
 }
@@ -637,6 +637,7 @@ gsis_status gsis_create(gsis_ctx **out, const gsis_config *cfg)
     octant_layout(x);
     g.species = c.species;
     g.delta = std::sqrt(PI) / (2.0 * c.Kn);
+    g.idelta = 1.0 / g.delta;
     g.omega = c.omega;
     g.dr = c.species == GSIS_DIATOMIC ? c.dr : 0.0;
     g.Zr = c.species == GSIS_DIATOMIC ? c.Zr : 1.0;
@@ -1191,7 +1192,7 @@ gsis_status gsis_bind_workspace(gsis_ctx *ctx, void *device_ptr, size_t bytes)
     }
     HIPCHK(ctx, upload_tiles(ctx));
     HIPCHK(ctx, hipMemset(d.errflag, 0, 4 * sizeof(int)));
-    HIPCHK(ctx, hipMemset(d.dmax, 0, (size_t)2 * DSLOT * DSTRIDE * sizeof(unsigned long long)));
+    HIPCHK(ctx, hipMemset(d.dmax, 0, (size_t)DSETS * DSLOT * DSTRIDE * sizeof(unsigned long long)));
     HIPCHK(ctx, launch_setup_tables(g, ctx->bc, d, nullptr));
     HIPCHK(ctx, hipDeviceSynchronize());
     ctx->bound = true;

@@ -6,7 +6,7 @@ namespace gsis {
 
 // Grid shapes of the kernels of a GSIS iteration; a launch over several cases
 // concatenates the blocks each case needs (kind_blocks) through a block map.
-enum Kind { K_CELL64, K_CELL128, K_CELL256, K_CELL1, K_FACE256, K_FACE8, K_GRAD, K_RES, K_CASE, NKIND };
+enum Kind { K_CELL64, K_CELL128, K_CELL256, K_CELL1, K_FACE256, K_FACE8, K_GRAD, K_MTILE, K_CASE, NKIND };
 int kind_blocks(const Geo &g, Kind k);
 
 // What a launch covers: one case (maps null) or a batch of cases that share

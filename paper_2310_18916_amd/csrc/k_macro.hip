@@ -1,5 +1,6 @@
-// GSIS-II macroscopic synthetic solve (Sec. 3.3), plain point-Jacobi
-// iteration on the GPU.  Not an optimisation target: per-cell kernels.
+// GSIS-II macroscopic synthetic solve (Sec. 3.3), point-Jacobi iteration on
+// the GPU: on the box one launch per inner iteration (k_mac_iter), on an
+// unstructured mesh per-cell and per-face kernels.
 //
 // Unknowns per fluid cell W = (rho, rho u, E, Er) with E = rho |u|^2 + 1.5 rho Tt + Er,
 // Er = (dr/2) rho Tr (monatomic: Er = 0) -- the moments 1, xi, |xi|^2 (+ 1 on
@@ -129,31 +130,50 @@ __device__ __forceinline__ void face_flux(const Geo &g, const PV &L, const PV &R
 
 // Outgoing half-range psi-moments of M(rho, u, Tt) through face dir (sum over
 // nodes with xi.n > 0 of w (xi.n) psi M), separable on the tensor grid and
-// summed node by node on a node list, and
-// the face flux of the equilibrium state with the face's boundary rule.  A
-// group of FG adjacent lanes evaluates one face: the lanes share the nodes of
-// each axis and a butterfly inside the group combines them, so every lane of
-// the group ends with the result.
-constexpr int FG = 8;
+// summed node by node on a node list, and the face flux of the equilibrium
+// state with the face's boundary rule.  A group of GW adjacent lanes evaluates
+// one face: the lanes share the nodes (of each axis) and a butterfly inside
+// the group combines them, so every lane of the group ends with the result.
+constexpr int FG = 8;    // lanes per face of the set-up kernel (k_mac_fbfix)
 
-// gradient blocks of k_mac_grad and k_mac_advance: one (cell, axis) per
-// thread, 256 threads, axis-major (a block holds one axis of 256 cells), so a
-// wave's neighbour reads are coalesced and its work is uniform
+// gradient blocks of k_mac_grad: one (cell, axis) per thread, 256 threads,
+// axis-major (a block holds one axis of 256 cells), so a wave's neighbour
+// reads are coalesced and its work is uniform
 __host__ __device__ inline int grad_axis_blocks(const Geo &g) { return (g.ncell + 255) / 256; }
 __host__ __device__ inline int grad_blocks(const Geo &g) { return 3 * grad_axis_blocks(g); }
-// boundary-face blocks (FG lanes per face); they come first in a launch that
-// also has gradient blocks, so the longer face work starts first
 __host__ __device__ inline int face_blocks(const Geo &g) { return (g.nface * FG + 255) / 256; }
 
+// v of the lane that the row permutation CTRL names (data-parallel primitive:
+// no trip through LDS as a general shuffle takes)
+template <int CTRL> __device__ __forceinline__ double row_perm(double v)
+{
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    lo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+    hi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// Sum over a group of GW (8, 16 or 64) lanes, the same bits in every lane:
+// quad swaps, then the mirrored half row and row (whose other half holds equal
+// values in all its lanes).
+template <int GW>
 __device__ __forceinline__ double group_sum(double v)
 {
-#pragma unroll
-    for (int m = 1; m < FG; m <<= 1) v += __shfl_xor(v, m, 64);
+    static_assert(GW == 8 || GW == 16 || GW == 64, "8, 16 or 64 lanes");
+    v += row_perm<0xB1>(v);    // lane ^ 1
+    v += row_perm<0x4E>(v);    // lane ^ 2
+    v += row_perm<0x141>(v);   // half-row mirror
+    if (GW > 8) v += row_perm<0x140>(v);   // row mirror
+    if (GW > 16) {
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+    }
     return v;
 }
 
-template <class PV>
-__device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev &d, const PV &P, int dir, int b,
+// LIST: the velocity set is a node list.
+template <int GW, bool LIST, class PV>
+__device__ __forceinline__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev &d, const PV &P, int dir, int b,
                                        int sub, double F[6])
 {
     const int a = dir / 2;
@@ -164,11 +184,11 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
     const double h1 = g.species == 1 ? 0.5 * g.dr * P[5] : 0.0;
     const gptr<const double> in = G((const double *)d.inpsi) + (b * 6 + dir) * 6;
     double out[6];
-    if (g.vlist) {
-        // node list: the half-range sums over the outgoing nodes directly
+    if constexpr (LIST) {
+        // the half-range sums over the outgoing nodes directly
         double s0 = 0.0, s1[3] = {0.0, 0.0, 0.0}, s4 = 0.0;
         const gptr<const double> nt = G((const double *)d.nt64);
-        for (int k = sub; k < g.nv; k += FG) {
+        for (int k = sub; k < g.nv; k += GW) {
             const double x = nt[4 * (size_t)k + a];
             if (!(sg * x > 0.0)) continue;
             const double v0 = nt[4 * (size_t)k], v1 = nt[4 * (size_t)k + 1], v2 = nt[4 * (size_t)k + 2];
@@ -180,10 +200,10 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
             s1[2] += ex * v2;
             s4 += ex * (v0 * v0 + v1 * v1 + v2 * v2);
         }
-        s0 = group_sum(s0);
+        s0 = group_sum<GW>(s0);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) s1[q] = group_sum(s1[q]);
-        s4 = group_sum(s4);
+        for (int q = 0; q < 3; ++q) s1[q] = group_sum<GW>(s1[q]);
+        s4 = group_sum<GW>(s4);
         out[0] = K * s0;
 #pragma unroll
         for (int q = 0; q < 3; ++q) out[1 + q] = K * s1[q];
@@ -196,7 +216,7 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
     }
     const int b1 = (a + 1) % 3, b2 = (a + 2) % 3;
     double H1 = 0, H2 = 0, H3 = 0;
-    for (int k = sub; k < g.n1[a]; k += FG) {
+    for (int k = sub; k < g.n1[a]; k += GW) {
         const double x = G(d.xi64[a])[k];
         if (!(sg * x > 0.0)) continue;
         const double c = x - P[1 + a];
@@ -210,7 +230,7 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int ax = ax2[q];
-        for (int k = sub; k < g.n1[ax]; k += FG) {
+        for (int k = sub; k < g.n1[ax]; k += GW) {
             const double x = G(d.xi64[ax])[k], c = x - P[1 + ax];
             const double e = G(d.w64[ax])[k] * exp_core(fmax(-c * c * iT, -745.0));
             S[q][0] += e;
@@ -218,13 +238,13 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
             S[q][2] += e * x * x;
         }
     }
-    H1 = group_sum(H1);
-    H2 = group_sum(H2);
-    H3 = group_sum(H3);
+    H1 = group_sum<GW>(H1);
+    H2 = group_sum<GW>(H2);
+    H3 = group_sum<GW>(H3);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int p = 0; p < 3; ++p) S[q][p] = group_sum(S[q][p]);
+        for (int p = 0; p < 3; ++p) S[q][p] = group_sum<GW>(S[q][p]);
     out[0] = K * H1 * S[0][0] * S[1][0];
     out[1 + a] = K * H2 * S[0][0] * S[1][0];
     out[1 + b1] = K * H1 * S[0][1] * S[1][0];
@@ -236,29 +256,24 @@ __device__ void group_equilibrium_flux(const Geo &g, const BcInfo &bc, const Dev
     for (int k = 0; k < 6; ++k) F[k] = out[k] + sc * in[k];
 }
 
-// Stress and heat fluxes of Eq. (NSF_constitutive) at the face group's cell
-// from its central gradients (one-sided next to a non-fluid neighbour, zero
-// with none): lane sub of the group holds v = (ux, uy, uz, Tt, Tr) of the
-// cell's neighbour across direction sub (0..5; the cell's own state, with
-// has = false, where that is not a fluid cell), lanes 6 and 7 the cell's own;
-// mu = Tt^omega / delta of the cell.  sq = (sigma xx yy zz xy xz yz, q, qr),
-// the same in every lane of the group.
-__device__ __forceinline__ void group_cell_nsf(const Geo &g, const double v[5], bool has, double mu, double sq[12])
+// Stress and heat fluxes of Eq. (NSF_constitutive) at a cell from its central
+// gradients (one-sided next to a non-fluid neighbour, zero with none):
+// dv[a] = (v(+a) - v(-a)) of v = (ux, uy, uz, Tt, Tr) along axis a, the cell's
+// own value standing in for a side that is not a fluid cell, hm / hp whether
+// the sides are; mu = Tt^omega / delta of the cell.  sq = (sigma xx yy zz xy
+// xz yz, q, qr).
+__device__ __forceinline__ void cell_nsf(const Geo &g, const double dv[3][5], const bool hm[3], const bool hp[3],
+                                         double mu, double sq[12])
 {
-    const int base = (int)(threadIdx.x & 63) & ~(FG - 1);
     double Gu[9], gt[3], gr[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int hm = __shfl((int)has, base + 2 * a, 64), hp = __shfl((int)has, base + 2 * a + 1, 64);
-        const double iden = (hm && hp) ? 0.5 * g.invh[a] : g.invh[a];
-        const bool none = !hm && !hp;
-        double dv[5];
+        const double iden = (hm[a] && hp[a]) ? 0.5 * g.invh[a] : g.invh[a];
+        const bool none = !hm[a] && !hp[a];
 #pragma unroll
-        for (int k = 0; k < 5; ++k) dv[k] = __shfl(v[k], base + 2 * a + 1, 64) - __shfl(v[k], base + 2 * a, 64);
-#pragma unroll
-        for (int b = 0; b < 3; ++b) Gu[b * 3 + a] = none ? 0.0 : dv[b] * iden;
-        gt[a] = none ? 0.0 : dv[3] * iden;
-        gr[a] = none ? 0.0 : dv[4] * iden;
+        for (int b = 0; b < 3; ++b) Gu[b * 3 + a] = none ? 0.0 : dv[a][b] * iden;
+        gt[a] = none ? 0.0 : dv[a][3] * iden;
+        gr[a] = none ? 0.0 : dv[a][4] * iden;
     }
     const double div = Gu[0] + Gu[4] + Gu[8];
     sq[0] = -mu * (2.0 * Gu[0] - (2.0 / 3.0) * div);
@@ -274,19 +289,40 @@ __device__ __forceinline__ void group_cell_nsf(const Geo &g, const double v[5], 
     }
 }
 
+// The same for a group of at least 8 lanes on one cell: lane sub of the group
+// holds v of the cell's neighbour across direction sub (0..5; the cell's own
+// state, with has = false, where that is not a fluid cell), the other lanes
+// the cell's own; the result is the same in every lane of the group.
+template <int GW>
+__device__ __forceinline__ void group_cell_nsf(const Geo &g, const double v[5], bool has, double mu, double sq[12])
+{
+    const int base = (int)(threadIdx.x & 63) & ~(GW - 1);
+    double dv[3][5];
+    bool hm[3], hp[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        hm[a] = __shfl((int)has, base + 2 * a, 64) != 0;
+        hp[a] = __shfl((int)has, base + 2 * a + 1, 64) != 0;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) dv[a][k] = __shfl(v[k], base + 2 * a + 1, 64) - __shfl(v[k], base + 2 * a, 64);
+    }
+    cell_nsf(g, dv, hm, hp, mu, sq);
+}
+
 // sum over the outgoing half of w xi_n c^e B(c) M(c) / (rho (pi T)^{-3/2}) on
 // the tensor grid, c in the face's axes (normal, t1, t2), B the Grad-13
 // bracket 1 + cs sigma:cc + cq (q.c)(c5 |c|^2 - 1): products of the 1-D sums
 // N[i] = sum_{out} w e xi_n c_n^i and S1[j], S2[k] = sum w e c_t^j over the
-// tangential axes (e the 1-D Gaussian factor).
-template <int EN, int E1, int E2>
-__device__ __forceinline__ double g13_bsum(const double N[6], const double S1[6], const double S2[6],
-                                           const double sl[3][3], const double ql[3], double cs, double cq, double c5)
+// tangential axes (e the 1-D Gaussian factor), each given from its power in
+// c^e on.  sl = sigma nn, 11, 22, n1, n2, 12.
+template <class SV>
+__device__ __forceinline__ double g13_bsum(const SV &N, const SV &S1, const SV &S2, const double sl[6],
+                                           const double ql[3], double cs, double cq, double c5)
 {
-#define GSIS_A3(i, j, k) (N[(i) + EN] * S1[(j) + E1] * S2[(k) + E2])
+#define GSIS_A3(i, j, k) (N[i] * S1[j] * S2[k])
     double r = GSIS_A3(0, 0, 0);
-    r += cs * (sl[0][0] * GSIS_A3(2, 0, 0) + sl[1][1] * GSIS_A3(0, 2, 0) + sl[2][2] * GSIS_A3(0, 0, 2)
-               + 2.0 * (sl[0][1] * GSIS_A3(1, 1, 0) + sl[0][2] * GSIS_A3(1, 0, 1) + sl[1][2] * GSIS_A3(0, 1, 1)));
+    r += cs * (sl[0] * GSIS_A3(2, 0, 0) + sl[1] * GSIS_A3(0, 2, 0) + sl[2] * GSIS_A3(0, 0, 2)
+               + 2.0 * (sl[3] * GSIS_A3(1, 1, 0) + sl[4] * GSIS_A3(1, 0, 1) + sl[5] * GSIS_A3(0, 1, 1)));
     const double t = ql[0] * (c5 * (GSIS_A3(3, 0, 0) + GSIS_A3(1, 2, 0) + GSIS_A3(1, 0, 2)) - GSIS_A3(1, 0, 0))
                    + ql[1] * (c5 * (GSIS_A3(2, 1, 0) + GSIS_A3(0, 3, 0) + GSIS_A3(0, 1, 2)) - GSIS_A3(0, 1, 0))
                    + ql[2] * (c5 * (GSIS_A3(2, 0, 1) + GSIS_A3(0, 2, 1) + GSIS_A3(0, 0, 3)) - GSIS_A3(0, 0, 1));
@@ -297,17 +333,17 @@ __device__ __forceinline__ double g13_bsum(const double N[6], const double S1[6]
 // The Grad-13 half-range sums of group_g13_flux on the tensor grid for a face
 // normal to axis A (a compile-time constant, so that every stress and heat-flux
 // component is picked by a constant index): out[6] before the boundary rule.
-template <int A>
+template <int GW, int A>
 __device__ __forceinline__ void g13_tensor_flux(const Geo &g, const Dev &d, const double u[3], const double sq[12],
                                                 double sg, double iT, double K, double cs, double cq, double c5,
                                                 double cr, double h1, bool dia, int sub, double out[6])
 {
     constexpr int T1 = (A + 1) % 3, T2 = (A + 2) % 3;
     constexpr int ax[3] = {A, T1, T2};
-    // sq slot of sigma_{pq} in the face's axes: the diagonal 0..2, xy 3, xz 4, yz 5
-    auto sslot = [](int x, int y) constexpr { return x == y ? x : 2 + x + y; };
+    // sq slot of sigma_{pq}, p != q: xy 3, xz 4, yz 5
+    auto sslot = [](int x, int y) constexpr { return 2 + x + y; };
     double N[6] = {0, 0, 0, 0, 0, 0}, S1[6] = {0, 0, 0, 0, 0, 0}, S2[6] = {0, 0, 0, 0, 0, 0};
-    for (int k = sub; k < g.n1[A]; k += FG) {
+    for (int k = sub; k < g.n1[A]; k += GW) {
         const double x = G(d.xi64[A])[k];
         if (!(sg * x > 0.0)) continue;
         const double c = x - u[A];
@@ -318,7 +354,7 @@ __device__ __forceinline__ void g13_tensor_flux(const Geo &g, const Dev &d, cons
             e *= c;
         }
     }
-    for (int k = sub; k < g.n1[T1]; k += FG) {
+    for (int k = sub; k < g.n1[T1]; k += GW) {
         const double c = G(d.xi64[T1])[k] - u[T1];
         double e = G(d.w64[T1])[k] * exp_core(fmax(-c * c * iT, -745.0));
 #pragma unroll
@@ -327,7 +363,7 @@ __device__ __forceinline__ void g13_tensor_flux(const Geo &g, const Dev &d, cons
             e *= c;
         }
     }
-    for (int k = sub; k < g.n1[T2]; k += FG) {
+    for (int k = sub; k < g.n1[T2]; k += GW) {
         const double c = G(d.xi64[T2])[k] - u[T2];
         double e = G(d.w64[T2])[k] * exp_core(fmax(-c * c * iT, -745.0));
 #pragma unroll
@@ -338,26 +374,25 @@ __device__ __forceinline__ void g13_tensor_flux(const Geo &g, const Dev &d, cons
     }
 #pragma unroll
     for (int p = 0; p < 6; ++p) {
-        N[p] = group_sum(N[p]);
-        S1[p] = group_sum(S1[p]);
-        S2[p] = group_sum(S2[p]);
+        N[p] = group_sum<GW>(N[p]);
+        S1[p] = group_sum<GW>(S1[p]);
+        S2[p] = group_sum<GW>(S2[p]);
     }
-    double sl[3][3], ql[3], rl[3], ul[3];
+    const double sl[6] = {sq[ax[0]], sq[ax[1]], sq[ax[2]], sq[sslot(A, T1)], sq[sslot(A, T2)], sq[sslot(T1, T2)]};
+    double ql[3], rl[3], ul[3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) sl[p][q] = sq[sslot(ax[p], ax[q])];
         ql[p] = sq[6 + ax[p]];
         rl[p] = sq[9 + ax[p]];
         ul[p] = u[ax[p]];
     }
-    const double b0 = g13_bsum<0, 0, 0>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double bn = g13_bsum<1, 0, 0>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double b1 = g13_bsum<0, 1, 0>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double b2 = g13_bsum<0, 0, 1>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double bnn = g13_bsum<2, 0, 0>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double b11 = g13_bsum<0, 2, 0>(N, S1, S2, sl, ql, cs, cq, c5);
-    const double b22 = g13_bsum<0, 0, 2>(N, S1, S2, sl, ql, cs, cq, c5);
+    const double b0 = g13_bsum((const double *)N, (const double *)S1, (const double *)S2, sl, ql, cs, cq, c5);
+    const double bn = g13_bsum((const double *)N + 1, (const double *)S1, (const double *)S2, sl, ql, cs, cq, c5);
+    const double b1 = g13_bsum((const double *)N, (const double *)S1 + 1, (const double *)S2, sl, ql, cs, cq, c5);
+    const double b2 = g13_bsum((const double *)N, (const double *)S1, (const double *)S2 + 1, sl, ql, cs, cq, c5);
+    const double bnn = g13_bsum((const double *)N + 2, (const double *)S1, (const double *)S2, sl, ql, cs, cq, c5);
+    const double b11 = g13_bsum((const double *)N, (const double *)S1 + 2, (const double *)S2, sl, ql, cs, cq, c5);
+    const double b22 = g13_bsum((const double *)N, (const double *)S1, (const double *)S2 + 2, sl, ql, cs, cq, c5);
     out[0] = K * b0;
     out[1 + A] = K * (bn + ul[0] * b0);
     out[1 + T1] = K * (b1 + ul[1] * b0);
@@ -376,9 +411,9 @@ __device__ __forceinline__ void g13_tensor_flux(const Geo &g, const Dev &d, cons
 //   f0 = M [1 + sigma:cc / (rho Tt^2) + 2 (q.c) / (rho Tt^2) (2 |c|^2 / (5 Tt) - 1)],
 //   f1 = (dr/2) Tr f0 + 2 M (qr.c) / (rho Tt),
 // velocities in sqrt(2 R T0) (these forms give back rho, u, Tt, sigma, q, Tr
-// and qr as the moments of Eq. getmoment).  A group of FG lanes per face, as
+// and qr as the moments of Eq. getmoment).  A group of GW lanes per face, as
 // group_equilibrium_flux.
-template <class PV>
+template <int GW, bool LIST, class PV>
 __device__ __forceinline__ void group_g13_flux(const Geo &g, const BcInfo &bc, const Dev &d, const PV &P, const double sq[12], int dir,
                                int b, int sub, double F[6])
 {
@@ -395,10 +430,10 @@ __device__ __forceinline__ void group_g13_flux(const Geo &g, const BcInfo &bc, c
     const double h1 = dia ? 0.5 * g.dr * P[5] : 0.0;
     const gptr<const double> in = G((const double *)d.inpsi) + (b * 6 + dir) * 6;
     double out[6];
-    if (g.vlist) {
+    if constexpr (LIST) {
         double s0 = 0.0, s1[3] = {0.0, 0.0, 0.0}, s4 = 0.0, sr = 0.0;
         const gptr<const double> nt = G((const double *)d.nt64);
-        for (int k = sub; k < g.nv; k += FG) {
+        for (int k = sub; k < g.nv; k += GW) {
             const double x = nt[4 * (size_t)k + a];
             if (!(sg * x > 0.0)) continue;
             const double v0 = nt[4 * (size_t)k], v1 = nt[4 * (size_t)k + 1], v2 = nt[4 * (size_t)k + 2];
@@ -416,11 +451,11 @@ __device__ __forceinline__ void group_g13_flux(const Geo &g, const BcInfo &bc, c
             s4 += eb * (v0 * v0 + v1 * v1 + v2 * v2);
             if (dia) sr += e * (sq[9] * cx + sq[10] * cy + sq[11] * cz);
         }
-        s0 = group_sum(s0);
+        s0 = group_sum<GW>(s0);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) s1[q] = group_sum(s1[q]);
-        s4 = group_sum(s4);
-        sr = group_sum(sr);
+        for (int q = 0; q < 3; ++q) s1[q] = group_sum<GW>(s1[q]);
+        s4 = group_sum<GW>(s4);
+        sr = group_sum<GW>(sr);
         out[0] = K * s0;
 #pragma unroll
         for (int q = 0; q < 3; ++q) out[1 + q] = K * s1[q];
@@ -428,21 +463,22 @@ __device__ __forceinline__ void group_g13_flux(const Geo &g, const BcInfo &bc, c
         out[4] = K * s4 + f1;
         out[5] = f1;
     } else {
-        if (a == 0) g13_tensor_flux<0>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
-        else if (a == 1) g13_tensor_flux<1>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
-        else g13_tensor_flux<2>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
+        if (a == 0) g13_tensor_flux<GW, 0>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
+        else if (a == 1) g13_tensor_flux<GW, 1>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
+        else g13_tensor_flux<GW, 2>(g, d, u, sq, sg, iT, K, cs, cq, c5, cr, h1, dia, sub, out);
     }
     const double sc = bc.kind[b] == 1 ? bc.rho[b] : out[0] / (-in[0]);
 #pragma unroll
     for (int k = 0; k < 6; ++k) F[k] = out[k] + sc * in[k];
 }
 
-// Gamma of a boundary face: outward speed plus the diffusive term of the cell
-template <class PV>
-__device__ __forceinline__ double boundary_gamma(const Geo &g, const PV &P, int a, bool euler)
-{
-    return fabs(P[1 + a]) + P[8] + (euler ? 0.0 : g.Cd * P[9] / (P[0] * g.h[a]));
-}
+// The box's solve keeps a cell's W (5, diatomic 6) and its residual R side by
+// side, and for the diatomic gas the rotational relaxation rate of that state
+// and a pad: a row of a tile's cells is then one stretch of memory, whose
+// lines are used whole (as [field][cell] every line gave 48 of its 128 bytes,
+// and filling them bound the loads).
+constexpr int WS_MONO = 10, WS_DIA = 14, WSRC = 12;
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // W^{n+1/2} and the old half of the correction record.
 __global__ __launch_bounds__(128) void k_mac_init(GSIS_SPAN_ARGS)
@@ -463,56 +499,39 @@ __global__ __launch_bounds__(128) void k_mac_init(GSIS_SPAN_ARGS)
     W[1] = rho * m[1]; W[2] = rho * m[2]; W[3] = rho * m[3];
     W[4] = rho * uu + 1.5 * rho * Tt + Er;
     W[5] = Er;
-    const Soa<double> Wd = soa(d.W, n, cell);
-    for (int k = 0; k < 6; ++k) Wd[k] = W[k];
+    if (g.umesh) {
+        const Soa<double> Wd = soa(d.W, n, cell);
+        for (int k = 0; k < 6; ++k) Wd[k] = W[k];
+    } else {
+        const bool dia = g.species == 1;
+        const gptr<double> Wd = G(d.W) + (size_t)cell * (dia ? WS_DIA : WS_MONO);
+        for (int k = 0; k < (dia ? 6 : 5); ++k) Wd[k] = W[k];
+    }
     const gptr<double> c = G(d.corr) + (size_t)cell * NCORR;
     c[6] = rho; c[7] = m[1]; c[8] = m[2]; c[9] = m[3]; c[10] = Tt;
     c[11] = g.species == 1 ? m[14] : Tt;
     prim_from_W(g, W, soa(d.P, n, cell));
 }
 
-// Column a of the velocity gradient of one cell: central differences, one-sided
+// Central gradients of u at W^{n+1/2}, one (cell, axis) per thread: one-sided
 // next to a non-fluid neighbour, zero with none.
-__device__ void cell_grad_col(const Geo &g, const Dev &d, int cell, int a)
-{
-    const int nm = G(d.nbr)[(size_t)(2 * a) * g.ncell + cell], np = G(d.nbr)[(size_t)(2 * a + 1) * g.ncell + cell];
-    const size_t n = g.ncell;
-    const Soa<double> Pm = soa(d.P, n, nm >= 0 ? nm : cell);
-    const Soa<double> Pp = soa(d.P, n, np >= 0 ? np : cell);
-    const double iden = (nm >= 0 && np >= 0) ? 0.5 * g.invh[a] : g.invh[a];
-    const Soa<double> G = soa(d.grad, n, cell);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) G[b * 3 + a] = (nm < 0 && np < 0) ? 0.0 : (Pp[1 + b] - Pm[1 + b]) * iden;
-}
-
-// Blocks [0, nfb): boundary faces, FG lanes per face: F_b = fixed part +
-// F_eq(W^m) and its Gamma (skipped when with_faces is 0).  Blocks [nfb, ...):
-// central gradients of u, one (cell, axis) per thread.
-__global__ __launch_bounds__(256) void k_mac_grad(GSIS_SPAN_ARGS, int with_faces, int euler)
+__global__ __launch_bounds__(256) void k_mac_grad(GSIS_SPAN_ARGS)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
     const Dev &d = C.d;
-    const BcInfo &bc = C.bc;
-    const int nfb = face_blocks(g);
-    if (blk >= nfb) {
-        const int gb = blk - nfb, npa = grad_axis_blocks(g), a = gb / npa;
-        const int cell = (gb - a * npa) * (int)blockDim.x + (int)threadIdx.x;
-        if (cell < g.ncell && G(d.cflag)[cell]) cell_grad_col(g, d, cell, a);
-        return;
-    }
-    if (!with_faces) return;
-    // whole groups of FG lanes share f, so the group butterflies stay inside live lanes
-    const int f = (blk * (int)blockDim.x + (int)threadIdx.x) / FG;
-    const int sub = threadIdx.x & (FG - 1);
-    if (f >= g.nface) return;
-    const int cell = G(d.face_cell)[f], dir = G(d.face_dir)[f];
-    const Soa<double> P = soa(d.P, g.ncell, cell);
-    double Fe[6];
-    group_equilibrium_flux(g, bc, d, P, dir, G(d.face_bc)[f], sub, Fe);
-    if (sub < 6) G(d.Fb)[(size_t)sub * g.nface + f] = G(d.fbfix)[(size_t)sub * g.nface + f] + Fe[sub];
-    if (sub == 7) G(d.Gb)[f] = boundary_gamma(g, P, dir / 2, euler);
+    const int npa = grad_axis_blocks(g), a = blk / npa;
+    const int cell = (blk - a * npa) * (int)blockDim.x + (int)threadIdx.x;
+    if (cell >= g.ncell || !G(d.cflag)[cell]) return;
+    const int nm = G(d.nbr)[(size_t)(2 * a) * g.ncell + cell], np = G(d.nbr)[(size_t)(2 * a + 1) * g.ncell + cell];
+    const size_t n = g.ncell;
+    const Soa<double> Pm = soa(d.P, n, nm >= 0 ? nm : cell);
+    const Soa<double> Pp = soa(d.P, n, np >= 0 ? np : cell);
+    const double iden = (nm >= 0 && np >= 0) ? 0.5 * g.invh[a] : g.invh[a];
+    const Soa<double> Gd = soa(d.grad, n, cell);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) Gd[b * 3 + a] = (nm < 0 && np < 0) ? 0.0 : (Pp[1 + b] - Pm[1 + b]) * iden;
 }
 
 // High-order terms at the faces (cell, cell + e_a), frozen at the kinetic
@@ -532,7 +551,7 @@ __global__ __launch_bounds__(128) void k_mac_hot(GSIS_SPAN_ARGS, int euler)
     const size_t n = g.ncell;
     const int m2row[3][3] = {{4, 7, 8}, {7, 5, 9}, {8, 9, 6}};
     for (int a = 0; a < 3; ++a) {
-        const Soa<double> fx = soa(d.hot + (size_t)a * 6 * n, n, cell);
+        const gptr<double> fx = G(d.hot) + ((size_t)a * n + cell) * 6;
         const int nb = G(d.nbr)[(size_t)(2 * a + 1) * g.ncell + cell];
         if (euler || nb < 0) {
             for (int k = 0; k < 6; ++k) fx[k] = 0.0;
@@ -555,8 +574,7 @@ __global__ __launch_bounds__(128) void k_mac_hot(GSIS_SPAN_ARGS, int euler)
     }
 }
 
-// Fixed part of each boundary face flux, F_kin(f^{n+1/2}) - F_eq(W^{n+1/2}), and
-// the face flux of the first inner iteration, fixed part + F_eq(W^{n+1/2}).
+// Fixed part of each boundary face flux, F_kin(f^{n+1/2}) - F_eq(W^{n+1/2}).
 // One group of FG lanes per face.
 // G13: compiled with the Grad-13 wall flux for the cases that take it (the
 // plain instantiation keeps its registers for the common path).
@@ -603,7 +621,7 @@ __global__ __launch_bounds__(256) void k_mac_fbfix(GSIS_SPAN_ARGS, int euler)
         const Soa<double> Pw = soa(d.P, g.ncell, who);
         const double v[5] = {Pw[1], Pw[2], Pw[3], Pw[4], Pw[5]};
         double sq[12];
-        group_cell_nsf(g, v, has, P[9], sq);
+        group_cell_nsf<FG>(g, v, has, P[9], sq);
         const gptr<const double> m = G((const double *)d.cm) + (size_t)cell * NMOM;
         const bool dia = g.species == 1;
 #pragma unroll
@@ -614,272 +632,594 @@ __global__ __launch_bounds__(256) void k_mac_fbfix(GSIS_SPAN_ARGS, int euler)
             if ((k & (FG - 1)) == sub) G(d.ghot)[(size_t)k * g.nface + f] = hot;
             sq[k] += hot;
         }
-        group_g13_flux(g, bc, d, P, sq, dir, b, sub, Fe);
+        if (g.vlist) group_g13_flux<FG, true>(g, bc, d, P, sq, dir, b, sub, Fe);
+        else group_g13_flux<FG, false>(g, bc, d, P, sq, dir, b, sub, Fe);
+    } else if (g.vlist) {
+        group_equilibrium_flux<FG, true>(g, bc, d, P, dir, b, sub, Fe);
     } else {
-        group_equilibrium_flux(g, bc, d, P, dir, b, sub, Fe);
+        group_equilibrium_flux<FG, false>(g, bc, d, P, dir, b, sub, Fe);
     }
     if (sub < 6) {
         // Euler: the boundary flux is the iterate's own F_eq, no fixed kinetic part
-        const double fix = euler ? 0.0 : out[sub] + sc * in[sub] - Fe[sub];
-        G(d.fbfix)[(size_t)sub * g.nface + f] = fix;
-        G(d.Fb)[(size_t)sub * g.nface + f] = fix + Fe[sub];
-    }
-    if (sub == 7) G(d.Gb)[f] = boundary_gamma(g, P, a, euler);
-}
-
-// Flux of face dir of a cell divided by h (outward positive), and Gamma / h.
-// dir is a compile-time constant so every index is static.
-// Index of the neighbour across face dir on the uniform grid (cell -+ 1, nx,
-// nx ny), clamped into the array: equal to the neighbour whenever the face is
-// interior, and a valid address otherwise, so the neighbour's data can be
-// loaded without waiting for the neighbour table.
-__device__ __forceinline__ int grid_neighbour(const Geo &g, int cell, int dir)
-{
-    const int a = dir / 2;
-    const int step = a == 0 ? 1 : (a == 1 ? g.nx : g.nx * g.ny);
-    return (dir & 1) ? min(cell + step, g.ncell - 1) : max(cell - step, 0);
-}
-
-// With KEEP the cell's own prims 0..10 are also returned in own[], loaded with
-// the face data, so the caller needs no second round trip to memory.
-template <int DIR, int NW, bool KEEP, bool EULER>
-__device__ __forceinline__ void face_term(const Geo &g, const Dev &d, int cell, double out[NW], double &gam,
-                                          double *own)
-{
-    constexpr int a = DIR / 2;
-    const double ih = g.invh[a];
-    const size_t nc = g.ncell;
-    // both sides' data into registers first, in parallel with the table lookup
-    const int nb = grid_neighbour(g, cell, DIR);
-    const int L = (DIR & 1) ? cell : nb, R = (DIR & 1) ? nb : cell;
-    // only what the face flux reads: no Tr, Er, qr for the monatomic gas and no
-    // normal gradient column (the normal derivative is the two-cell difference)
-    constexpr bool DIA = NW == 6;
-    double PL[NP], PR[NP], GL[9], GR[9], HO[6];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-        const bool use = DIA || (k != 5 && k != 7);
-        PL[k] = use ? G(d.P)[(size_t)k * nc + L] : 0.0;
-        PR[k] = use ? G(d.P)[(size_t)k * nc + R] : 0.0;
-        const bool tan = k % 3 != a;
-        GL[k] = tan ? G(d.grad)[(size_t)k * nc + L] : 0.0;
-        GR[k] = tan ? G(d.grad)[(size_t)k * nc + R] : 0.0;
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) HO[k] = (DIA || k < 5) ? G(d.hot)[(size_t)(a * 6 + k) * nc + L] : 0.0;
-    if (KEEP) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) own[k] = (DIR & 1) ? PL[k] : PR[k];
-        own[9] = G(d.P)[(size_t)9 * nc + cell];
-        own[10] = G(d.P)[(size_t)10 * nc + cell];
-    }
-    const int n = G(d.nbr)[(size_t)DIR * g.ncell + cell];
-    if (n >= 0) {
-        double F[6], Gam;
-        face_flux(g, PL, PR, GL, GR, a, ih, EULER, F, &Gam);
-#pragma unroll
-        for (int k = 0; k < NW; ++k) out[k] = ((DIR & 1) ? F[k] + HO[k] : -(F[k] + HO[k])) * ih;
-        gam = Gam * ih;
-    } else {
-        const int f = -n - 1;
-#pragma unroll
-        for (int k = 0; k < NW; ++k) out[k] = G(d.Fb)[(size_t)k * g.nface + f] * ih;
-        gam = G(d.Gb)[f] * ih;
+        G(d.fbfix)[(size_t)sub * g.nface + f] = euler ? 0.0 : out[sub] + sc * in[sub] - Fe[sub];
     }
 }
 
-// Residual and diagonal of every cell; D* = max D_i by an atomic max on the
-// bit pattern (positive doubles order like their bits), so it is exact and
-// order independent.  A block holds 64 cells and six waves; wave j evaluates
-// face j of every cell, LDS collects the six terms, and the first wave adds
-// them in face order, finishes the cells and issues one atomic for the wave's
-// largest D_i.
-constexpr int RES_CELLS = 64;
-
-// Six waves per SIMD (at most 80 VGPRs): four blocks per CU instead of three.
-template <bool DIA, bool EULER>
-__global__ __launch_bounds__(384) __attribute__((amdgpu_waves_per_eu(6))) void k_mac_res(GSIS_SPAN_ARGS, int slot)
+// What the residual of a cell keeps through the whole solve: minus the sum
+// over its faces, outward, of the high-order terms of the interior ones and
+// the fixed parts of the boundary ones, over h.  Six values per cell instead
+// of six per face in every iteration.
+__global__ __launch_bounds__(128) void k_mac_const(GSIS_SPAN_ARGS)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
     const Dev &d = C.d;
+    const int cell = blk * blockDim.x + threadIdx.x;
+    if (cell >= g.ncell || !G(d.cflag)[cell]) return;
+    const size_t n = g.ncell;
+    double s[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int dir = 0; dir < 6; ++dir) {
+        const int a = dir >> 1, nb = G(d.nbr)[(size_t)dir * n + cell];
+        const double ih = g.invh[a];
+        if (nb < 0) {
+            for (int k = 0; k < 6; ++k) s[k] -= G(d.fbfix)[(size_t)k * g.nface - nb - 1] * ih;
+        } else {
+            const gptr<const double> h = G((const double *)d.hot) + ((size_t)a * n + ((dir & 1) ? cell : nb)) * 6;
+            for (int k = 0; k < 6; ++k) s[k] -= ((dir & 1) ? h[k] : -h[k]) * ih;
+        }
+    }
+    for (int k = 0; k < 6; ++k) G(d.Rc)[(size_t)cell * 6 + k] = s[k];
+}
 
+// ------------------------------------------------------- one inner iteration
+// One launch per inner iteration.  A block owns a 4 x 4 x 4 tile of cells:
+//   1. its threads step the tile's cells and their halo to the new state,
+//      W' = W + R / D* (D* the largest diagonal of the launch before), and
+//      stage the prims in LDS (the tile writes its own W');
+//   2. one thread per face of the tile (240) forms the face flux with the
+//      gradients taken from the staged velocities; boundary faces go into a
+//      list, whose 1-D half-range sums are shared out over the block (four
+//      lanes per face and axis) and finished by one thread (four with the
+//      Grad-13 wall flux) per face;
+//   3. a thread per cell and pair of components adds the six face terms into
+//      the residual R of the new state, and D goes into the partial maxima.
+// The halo is one cell wide without its corners: a face needs its two cells
+// and, for the tangential gradients, their neighbours across the other axes.
+// It is stepped again by every tile that sees it (208 cells for 64), which
+// costs less than the launch and the round trip through memory that writing
+// the prims first would take; every face is formed once per tile (3.75 per
+// cell) instead of once from each side, and what the high-order terms and the
+// fixed boundary parts add to a cell is summed once per solve (k_mac_const).
+// Measured, us per inner iteration, against a residual launch (every face from
+// both sides) and an advance launch per iteration: cavity of 48^3 cells 18.9
+// (32.6), nitrogen block of 64 x 48 x 48 cells 29.2 (45.7), cavity of 12 x 11
+// x 13 cells with the Grad-13 wall flux 11.8 (20.7).  What bounds it now: an
+// iteration moves about 30 MB between the XCDs' caches and the memory side
+// (half of the time on 48^3 cells), then the latency of the three dependent
+// phases, twice over for the tiles that do not fit the chip at once (five
+// blocks of 30 KB LDS per CU); the boundary faces' 1-D sums add 3.6 us.
+constexpr int MT = 4, MH = MT + 2, MHN = MH * MH * MH;
+constexpr int MFN = 3 * (MT + 1) * MT * MT;   // faces of a tile
+constexpr int MBC = 48;                       // boundary faces finished together
+
+// Half of an axis in tiles, rounded up.  Blocks go to the 8 XCDs in turn, so
+// block b takes a tile of octant b mod 8 of the box: an XCD reads its own
+// octant and one layer of cells around it, which fit its L2, where tiles dealt
+// out in turn had every XCD fetch nearly every line of every field from the
+// memory side (48^3 cells: 35 against 20 us per iteration).  An octant that an
+// odd number of tiles leaves smaller has blocks without a tile.
+__host__ __device__ inline int mtile_half(int n) { return ((n + MT - 1) / MT + 1) / 2; }
+__host__ __device__ inline int mtile_blocks(const Geo &g)
+{
+    return 8 * mtile_half(g.nx) * mtile_half(g.ny) * mtile_half(g.nz);
+}
+
+// D* of the launch that filled partial set `set`: 16 lanes share out the
+// partial slots, and every row of 16 lanes does the same
+constexpr int BSLOT = 16;
+__device__ __forceinline__ double partial_diagonal(const Dev &d, int set)
+{
+    return __longlong_as_double((long long)G(d.dmax)[(size_t)(set * DSLOT + (threadIdx.x & (BSLOT - 1))) * DSTRIDE]);
+}
+__device__ __forceinline__ double row_max(double v)
+{
+    v = fmax(v, row_perm<0xB1>(v));
+    v = fmax(v, row_perm<0x4E>(v));
+    v = fmax(v, row_perm<0x141>(v));
+    return fmax(v, row_perm<0x140>(v));
+}
+__device__ __forceinline__ double largest_diagonal(const Dev &d, int set) { return row_max(partial_diagonal(d, set)); }
+
+// W of a cell after the pseudo-time step of launch it (none before the first)
+// from its record: W + R / D* (as R times 1/D*), the rotational-energy row with
+// its relaxation source on the diagonal.
+template <bool DIA, class PV>
+__device__ __forceinline__ void stepped_W(PV rec, int it, double Dm, double iDm, double Wn[6])
+{
     constexpr int NW = DIA ? 6 : 5;
-    __shared__ double red[6][NW + 1][RES_CELLS];
-    const int lane = threadIdx.x & 63;
-    const int dir = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int cell = blk * RES_CELLS + lane;
-    const bool live = cell < g.ncell && G(d.cflag)[cell];
-    double out[NW], gam = 0.0, Pi[11];
 #pragma unroll
-    for (int k = 0; k < NW; ++k) out[k] = 0.0;
-    if (live) {
-        switch (dir) {
-        case 0: face_term<0, NW, true, EULER>(g, d, cell, out, gam, Pi); break;
-        case 1: face_term<1, NW, false, EULER>(g, d, cell, out, gam, nullptr); break;
-        case 2: face_term<2, NW, false, EULER>(g, d, cell, out, gam, nullptr); break;
-        case 3: face_term<3, NW, false, EULER>(g, d, cell, out, gam, nullptr); break;
-        case 4: face_term<4, NW, false, EULER>(g, d, cell, out, gam, nullptr); break;
-        default: face_term<5, NW, false, EULER>(g, d, cell, out, gam, nullptr); break;
-        }
+    for (int k = 0; k < 6; ++k) Wn[k] = k < NW ? rec[k] : 0.0;
+    if (it > 0) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) Wn[k] += rec[NW + k] * iDm;
+        if (DIA) Wn[5] += rec[NW + 5] * recip(Dm + rec[DIA ? WSRC : 0]);
     }
-#pragma unroll
-    for (int k = 0; k < NW; ++k) red[dir][k][lane] = out[k];
-    red[dir][NW][lane] = gam;
-    __syncthreads();
-    if (dir != 0) return;
-    double D = 0.0;
-    if (live) {
-        double res[6], sumG = 0.0;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) res[k] = 0.0;
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-#pragma unroll
-            for (int k = 0; k < NW; ++k) res[k] -= red[j][k][lane];
-            sumG += red[j][NW][lane];
-        }
-        const double invtau = Pi[10];
-        if (DIA) {
-            double T = (3.0 * Pi[4] + g.dr * Pi[5]) / (3.0 + g.dr);
-            res[5] += 0.5 * g.dr * Pi[0] * (T - Pi[5]) * invtau / g.Zr;
-        }
-        double umag = sqrt(Pi[1] * Pi[1] + Pi[2] * Pi[2] + Pi[3] * Pi[3]);
-        double idt = (umag + Pi[8] + (EULER ? 0.0 : g.Cd * Pi[9] / (Pi[0] * g.hmin))) / (g.macro_cfl * g.hmin);
-        D = idt + 0.5 * sumG;
-        const Soa<double> r = soa(d.R, g.ncell, cell);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) r[k] = res[k];
-        G(d.Src)[cell] = DIA ? invtau / g.Zr : 0.0;
-        if (!(D > 0.0 && isfinite(D))) {
-            atomicOr(d.errflag, 2);
-            D = 0.0;
-        }
-    }
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) D = fmax(D, __shfl_xor(D, m, 64));
-    if (lane == 0 && D > 0.0)
-        atomicMax(&d.dmax[(size_t)(slot * DSLOT + (blk & (DSLOT - 1))) * DSTRIDE],
-                  (unsigned long long)__double_as_longlong(D));
 }
 
-// W of a cell after the pseudo-time step: W + R / D* (as R times 1/D*), the
-// rotational-energy row with its relaxation source on the diagonal.
-__device__ __forceinline__ void stepped_W(const Geo &g, const Dev &d, gptr<const double> Ws, int cell, double Dm, double iDm,
-                                          double Wn[6])
+// rho, u, Tt, Tr, E, Er, c_s of a state
+template <bool DIA>
+__device__ __forceinline__ void short_prims(const Geo &g, const double W[6], double P[9])
 {
-    const Soa<const double> W = soa(Ws, g.ncell, cell);
-    const Soa<double> r = soa(d.R, g.ncell, cell);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) Wn[k] = W[k] + r[k] * iDm;
-    Wn[5] = g.species == 1 ? W[5] + r[5] / (Dm + G(d.Src)[cell]) : W[5];
+    const double rho = W[0], irho = recip(rho);
+    const double u0 = W[1] * irho, u1 = W[2] * irho, u2 = W[3] * irho;
+    const double Er = DIA ? W[5] : 0.0;
+    const double Tt = (2.0 / 3.0) * (W[4] - Er - rho * (u0 * u0 + u1 * u1 + u2 * u2)) * irho;
+    P[0] = rho; P[1] = u0; P[2] = u1; P[3] = u2; P[4] = Tt;
+    P[5] = DIA ? 2.0 * Er / (g.dr * rho) : Tt;
+    P[6] = W[4];
+    P[7] = Er;
+    P[8] = sqrt(0.5 * g.gam * Tt);
 }
 
-// Density and momentum rows of stepped_W only (what a neighbour's velocity needs).
-__device__ __forceinline__ void stepped_mass_momentum(const Geo &g, const Dev &d, gptr<const double> Ws, int cell,
-                                                      double iDm, double Wn[4])
-{
-    const Soa<const double> W = soa(Ws, g.ncell, cell);
-    const Soa<double> r = soa(d.R, g.ncell, cell);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) Wn[k] = W[k] + r[k] * iDm;
-}
-
-// End of an inner iteration: W' = W + R / D* with the new prims, and -- unless
-// it is the last iteration -- the velocity gradient and the boundary-face
-// fluxes of the new state, in one launch.  Grid as k_mac_grad: FG lanes per
-// boundary face, then (cell, axis) threads (the axis-0 blocks also write W'
-// and the prims).  Neighbours' new velocities and the face cells' new prims are
-// formed from W and R directly, so W is double buffered (read src, write dst).
-template <bool G13>
-__global__ __launch_bounds__(256) void k_mac_advance(GSIS_SPAN_ARGS, int slot, int parity, int last, int euler)
+// Node list: the boundary-face fluxes of the state that launch it steps to,
+// one wave per face (the sums run over every node, too long for a tile's
+// share of lanes); k_mac_iter takes them from Fb and Gb.
+template <bool DIA, bool EULER, bool G13>
+__global__ __launch_bounds__(256) void k_mac_bface(GSIS_SPAN_ARGS, int it)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
     const Dev &d = C.d;
     const BcInfo &bc = C.bc;
-    const gptr<const double> Ws = G((const double *)(parity ? d.W2 : d.W));
-    const gptr<double> Wd = G(parity ? d.W : d.W2);
-    // D*: each lane loads one partial slot, the wave takes their max
-    double Dm = __longlong_as_double((long long)G(d.dmax)[(size_t)(slot * DSLOT + (threadIdx.x & (DSLOT - 1))) * DSTRIDE]);
-#pragma unroll
-    for (int m = 1; m < DSLOT; m <<= 1) Dm = fmax(Dm, __shfl_xor(Dm, m, 64));
-    const double iDm = 1.0 / Dm;
-    const int nfb = face_blocks(g);
-    if (blk >= nfb) {
-        const int gb = blk - nfb;
-        // the other slot was last used by the previous iteration
-        if (gb == 0 && (int)threadIdx.x < DSLOT) G(d.dmax)[(size_t)((slot ^ 1) * DSLOT + threadIdx.x) * DSTRIDE] = 0ull;
-        const int npa = grad_axis_blocks(g), a = gb / npa;
-        if (a != 0 && last) return;
-        const int cell = (gb - a * npa) * (int)blockDim.x + (int)threadIdx.x;
-        if (cell >= g.ncell || !G(d.cflag)[cell]) return;
-        double Wn[6];
-        stepped_W(g, d, Ws, cell, Dm, iDm, Wn);
-        if (a == 0) {
-            const Soa<double> Wc = soa(Wd, g.ncell, cell);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) Wc[k] = Wn[k];
-            prim_from_W(g, Wn, soa(d.P, g.ncell, cell));
-        }
-        if (last) return;
-        // neighbours' states loaded at grid indices, in parallel with the table lookup
-        double Wm[4], Wp[4];
-        stepped_mass_momentum(g, d, Ws, grid_neighbour(g, cell, 2 * a), iDm, Wm);
-        stepped_mass_momentum(g, d, Ws, grid_neighbour(g, cell, 2 * a + 1), iDm, Wp);
-        const int nm = G(d.nbr)[(size_t)(2 * a) * g.ncell + cell], np = G(d.nbr)[(size_t)(2 * a + 1) * g.ncell + cell];
-        double um[3], up[3];
-        const double ic = 1.0 / Wn[0], im = 1.0 / Wm[0], ip = 1.0 / Wp[0];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const double uc = Wn[1 + b] * ic;
-            um[b] = nm >= 0 ? Wm[1 + b] * im : uc;
-            up[b] = np >= 0 ? Wp[1 + b] * ip : uc;
-        }
-        const double iden = (nm >= 0 && np >= 0) ? 0.5 * g.invh[a] : g.invh[a];
-        const Soa<double> G = soa(d.grad, g.ncell, cell);
-#pragma unroll
-        for (int b = 0; b < 3; ++b) G[b * 3 + a] = (nm < 0 && np < 0) ? 0.0 : (up[b] - um[b]) * iden;
-        return;
-    }
-    if (last) return;
-    const int f = (blk * (int)blockDim.x + (int)threadIdx.x) / FG;
-    const int sub = threadIdx.x & (FG - 1);
+    const int f = __builtin_amdgcn_readfirstlane(blk * 4 + (int)(threadIdx.x >> 6));
     if (f >= g.nface) return;
-    const int cell = G(d.face_cell)[f], dir = G(d.face_dir)[f];
-    double Wn[6], P[NP];
-    stepped_W(g, d, Ws, cell, Dm, iDm, Wn);
-    prim_from_W(g, Wn, P);
-    double Fe[6];
-    if (G13 && g.wall_flux == 1 && !euler) {
-        // Grad-13 wall flux of the new state: NSF_c from the new states of the
-        // cell and its neighbours (one per lane) plus the cell's HoT_c
+    const int sub = threadIdx.x & 63;
+    const gptr<const double> src = G((const double *)((it & 1) ? d.W2 : d.W));
+    double Dm = 1.0;
+    if (it > 0) Dm = largest_diagonal(d, (it - 1) % DSETS);
+    const double iDm = 1.0 / Dm;
+    const int cell = G(d.face_cell)[f], dir = G(d.face_dir)[f], b = G(d.face_bc)[f];
+    double Wn[6], P[9], Fe[6];
+    constexpr int WS = DIA ? WS_DIA : WS_MONO;
+    stepped_W<DIA>(src + (size_t)cell * WS, it, Dm, iDm, Wn);
+    short_prims<DIA>(g, Wn, P);
+    const double mu = pow_line(P[4], g.omega) * g.idelta;
+    if (G13 && !EULER && g.wall_flux == 1) {
+        // NSF_c from the new states of the cell and its neighbours (one per lane) plus the cell's HoT_c
         int who = cell;
         bool has = false;
         if (sub < 6) {
             const int nb = G(d.nbr)[(size_t)sub * g.ncell + cell];
             if (nb >= 0) { who = nb; has = true; }
         }
-        double Ww[6];
-        stepped_W(g, d, Ws, who, Dm, iDm, Ww);
-        // u, Tt, Tr of the new state, as prim_from_W forms them
-        const double irho = 1.0 / Ww[0];
-        const double w0 = Ww[1] * irho, w1 = Ww[2] * irho, w2 = Ww[3] * irho;
-        const double wEr = g.species == 1 ? Ww[5] : 0.0;
-        const double wTt = (2.0 / 3.0) * (Ww[4] - wEr - Ww[0] * (w0 * w0 + w1 * w1 + w2 * w2)) * irho;
-        const double v[5] = {w0, w1, w2, wTt, g.species == 1 ? 2.0 * wEr / (g.dr * Ww[0]) : wTt};
-        double sq[12];
-        group_cell_nsf(g, v, has, P[9], sq);
+        double Ww[6], Pw[9], sq[12];
+        stepped_W<DIA>(src + (size_t)who * WS, it, Dm, iDm, Ww);
+        short_prims<DIA>(g, Ww, Pw);
+        const double v[5] = {Pw[1], Pw[2], Pw[3], Pw[4], Pw[5]};
+        group_cell_nsf<64>(g, v, has, mu, sq);
 #pragma unroll
         for (int k = 0; k < 12; ++k) sq[k] += G(d.ghot)[(size_t)k * g.nface + f];
-        group_g13_flux(g, bc, d, P, sq, dir, G(d.face_bc)[f], sub, Fe);
+        group_g13_flux<64, true>(g, bc, d, P, sq, dir, b, sub, Fe);
     } else {
-        group_equilibrium_flux(g, bc, d, P, dir, G(d.face_bc)[f], sub, Fe);
+        group_equilibrium_flux<64, true>(g, bc, d, P, dir, b, sub, Fe);
     }
-    if (sub < 6) G(d.Fb)[(size_t)sub * g.nface + f] = G(d.fbfix)[(size_t)sub * g.nface + f] + Fe[sub];
-    if (sub == 7) G(d.Gb)[f] = boundary_gamma(g, P, dir / 2, euler);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        if (sub == k) G(d.Fb)[(size_t)k * g.nface + f] = Fe[k];
+    if (sub == 0)
+        G(d.Gb)[f] = fabs(P[1 + dir / 2]) + P[8] + (EULER ? 0.0 : g.Cd * mu / (P[0] * g.h[dir / 2]));
+}
+
+// sum over the four lanes of a quad, the same bits in each
+__device__ __forceinline__ double quad_sum(double v)
+{
+    v += row_perm<0xB1>(v);
+    return v + row_perm<0x4E>(v);
+}
+
+template <bool DIA, bool EULER, bool G13>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_mac_iter(GSIS_SPAN_ARGS, int it)
+{
+    constexpr int NW = DIA ? 6 : 5;
+    constexpr int WS = DIA ? WS_DIA : WS_MONO;
+    constexpr int NS = G13 ? 6 : 3;      // 1-D sums of a boundary face per axis
+    // staged prims: rho, u, Tt, E, c_s, then Tr, Er
+    enum { QR = 0, QU = 1, QT = 4, QE = 5, QC = 6, QTR = DIA ? 7 : 4, QER = DIA ? 8 : 5, NQ = DIA ? 9 : 7 };
+    // Records as read (WS words per halo cell), then, in the same space, the
+    // prims, the face terms along +axis and Gamma, and the boundary faces' sums
+    constexpr int NB = MBC * (3 * NS + (G13 ? 8 : 0));
+    constexpr int NLDS = NQ * MHN + (NW + 1) * MFN + NB > WS * MHN ? NQ * MHN + (NW + 1) * MFN + NB : WS * MHN;
+    __shared__ __attribute__((aligned(16))) double lds[NLDS];
+    double(&sp)[NQ][MHN] = *(double(*)[NQ][MHN])lds;
+    double(&sf)[NW + 1][MFN] = *(double(*)[NW + 1][MFN])(lds + NQ * MHN);
+    double *const ssum = lds + NQ * MHN + (NW + 1) * MFN, *const sb = ssum + MBC * 3 * NS;
+    __shared__ int sflag[MHN];
+    __shared__ int2 slist[MFN];          // boundary faces: (face | the cell's halo position << 8 | direction << 16 | slot << 20, index)
+    __shared__ int scount;
+
+    int blk;
+    const Case &C = case_of(span_cases, span_map, blk);
+    const Geo &g = C.g;
+    const Dev &d = C.d;
+    const BcInfo &bc = C.bc;
+    const int t = threadIdx.x;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const gptr<const double> src = G((const double *)((it & 1) ? d.W2 : d.W));
+    const gptr<double> dst = G((it & 1) ? d.W : d.W2);
+    const size_t nc = (size_t)g.ncell;
+    // The tile in its octant, counted from the octant's outer corner: the layers
+    // on the box's boundary (z, then y, then x) first, as their tiles take longest
+    const int mx = mtile_half(nx), my = mtile_half(ny), mz = mtile_half(nz);
+    int q = blk >> 3, ox, oy, oz;
+    if (q < mx * my) {
+        oz = 0; oy = q / mx; ox = q - oy * mx;
+    } else if ((q -= mx * my) < mx * (mz - 1)) {
+        oy = 0; oz = q / mx; ox = q - oz * mx; ++oz;
+    } else if ((q -= mx * (mz - 1)) < (my - 1) * (mz - 1)) {
+        ox = 0; oz = q / (my - 1); oy = q - oz * (my - 1) + 1; ++oz;
+    } else {
+        q -= (my - 1) * (mz - 1);
+        const int r = q / (mx - 1);
+        ox = q - r * (mx - 1) + 1; oz = r / (my - 1); oy = r - oz * (my - 1) + 1; ++oz;
+    }
+    // the upper half of an axis counts down from its last tile
+    const int ntx = (nx + MT - 1) / MT, nty = (ny + MT - 1) / MT, ntz = (nz + MT - 1) / MT;
+    const int tx = blk & 1 ? ntx - 1 - ox : ox, ty = blk & 2 ? nty - 1 - oy : oy, tz = blk & 4 ? ntz - 1 - oz : oz;
+    const bool none = (blk & 1 && tx < mx) || (blk & 2 && ty < my) || (blk & 4 && tz < mz);
+    const int x0 = tx * MT - 1, y0 = ty * MT - 1, z0 = tz * MT - 1;
+    if (blk == 0 && t < BSLOT) G(d.dmax)[(size_t)((it + 1) % DSETS * DSLOT + t) * DSTRIDE] = 0ull;
+    if (none) return;   // an octant with fewer tiles; uniform over the block
+    if (t == 0) scount = 0;
+
+    // the reads of D* (a partial slot per lane) and of this thread's cell of the halo
+    double Dp = 1.0;
+    if (it > 0) Dp = partial_diagonal(d, (it - 1) % DSETS);
+    const int hx = t % MH, hy = t / MH % MH, hz = t / (MH * MH);
+    const bool ex = hx == 0 || hx == MH - 1, ey = hy == 0 || hy == MH - 1, ez = hz == 0 || hz == MH - 1;
+    const int hi = x0 + hx, hj = y0 + hy, hk = z0 + hz;
+    const int hcell = hi + nx * (hj + ny * hk);
+    const bool staged = t < MHN && hi >= 0 && hi < nx && hj >= 0 && hj < ny && hk >= 0 && hk < nz && !(ex && ey && ez);
+    const bool solids = g.nfluid != g.ncell;
+    const int hfl = staged ? (solids ? G(d.cflag)[hcell] : 1) : 0;
+    // the records of the halo box, row after row, 16 bytes a thread and step
+    constexpr int VC = WS / 2, VR = MH * VC, VN = MH * MH * VR, NV = (VN + 255) / 256;
+    f64x2 rec[NV];
+#pragma unroll
+    for (int r = 0; r < NV; ++r) {
+        const int v = t + 256 * r, row = v / VR, c = v - row * VR;
+        const int i = x0 + c / VC, j = y0 + row % MH, k = z0 + row / MH;
+        rec[r] = f64x2{0.0, 0.0};
+        if (v < VN && i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz)
+            rec[r] = ((gptr<const f64x2>)src)[(ptrdiff_t)(x0 + nx * (j + ny * k)) * VC + c];
+    }
+
+    // This thread's face: axis a, position fq along it and (fv, fw) along the
+    // other axes b1, b2.  Waves 0 to 2 take the faces 0..3 of axes 0 to 2, the
+    // last wave face 4 of each axis (48 lanes).
+    const bool isface = t < MFN;
+    const int fl6 = t & 63;
+    const bool wave3 = t >= 192;
+    const int a = wave3 ? fl6 >> 4 : t >> 6;
+    const int fq = wave3 ? MT : fl6 & 3, fv = wave3 ? fl6 & 3 : (fl6 >> 2) & 3, fw = wave3 ? (fl6 >> 2) & 3 : fl6 >> 4;
+    const int Sa = a == 0 ? 1 : (a == 1 ? MH : MH * MH);
+    const int S1 = a == 0 ? MH : (a == 1 ? MH * MH : 1), S2 = a == 0 ? MH * MH : (a == 1 ? 1 : MH);
+    const int b1 = a == 2 ? 0 : a + 1, b2 = a == 0 ? 2 : a - 1;
+    const int hL = fq * Sa + (fv + 1) * S1 + (fw + 1) * S2, hR = hL + Sa;
+    int nL = 0, nR = 0, fbc = 0;
+    if (isface && (solids || x0 < 0 || y0 < 0 || z0 < 0 || x0 + MT + 2 > nx || y0 + MT + 2 > ny || z0 + MT + 2 > nz)) {
+        // the neighbour table of a face that may be a boundary face, read before the prims are there
+        const int step = a == 0 ? 1 : (a == 1 ? nx : nx * ny);
+        const int s1 = a == 0 ? nx : (a == 1 ? nx * ny : 1), s2 = a == 0 ? nx * ny : (a == 1 ? 1 : nx);
+        const int at = (a == 0 ? x0 : (a == 1 ? y0 : z0)) + fq, na = a == 0 ? nx : (a == 1 ? ny : nz);
+        const int p1 = (b1 == 0 ? x0 : (b1 == 1 ? y0 : z0)) + 1 + fv, n1 = b1 == 0 ? nx : (b1 == 1 ? ny : nz);
+        const int p2 = (b2 == 0 ? x0 : (b2 == 1 ? y0 : z0)) + 1 + fw, n2 = b2 == 0 ? nx : (b2 == 1 ? ny : nz);
+        const int cL = at * step + p1 * s1 + p2 * s2;
+        if (at < na && p1 < n1 && p2 < n2) {
+            if (at >= 0) {
+                if (solids || at + 1 == na) nL = G(d.nbr)[(size_t)(2 * a + 1) * nc + cL];
+            }
+            if ((solids || at < 0) && at + 1 < na) nR = G(d.nbr)[(size_t)(2 * a) * nc + cL + step];
+        }
+    }
+    // the cell and the pair of components this thread adds up at the end, and their constant part
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), c = t & 63;
+    const int cx = c & 3, cy = (c >> 2) & 3, cz = c >> 4;
+    const int ci = x0 + 1 + cx, cj = y0 + 1 + cy, ck = z0 + 1 + cz, cell = ci + nx * (cj + ny * ck);
+    f64x2 rc = {0.0, 0.0};
+    if (w < 3 && ci < nx && cj < ny && ck < nz) rc = ((gptr<const f64x2>)d.Rc)[(size_t)cell * 3 + w];
+
+    // 1. the new state of the tile and its halo
+#pragma unroll
+    for (int r = 0; r < NV; ++r)
+        if (t + 256 * r < VN) ((f64x2 *)lds)[t + 256 * r] = rec[r];
+    const double Dm = row_max(Dp), iDm = recip(Dm);
+    if (t < MHN) sflag[t] = hfl;
+    __syncthreads();
+    double Wn[6];
+    if (staged) stepped_W<DIA>(lds + t * WS, it, Dm, iDm, Wn);
+    __syncthreads();
+    if (staged) {
+        double P[9];
+        short_prims<DIA>(g, Wn, P);   // a solid cell's is not used
+#pragma unroll
+        for (int q = 0; q < 5; ++q) sp[q][t] = P[q];
+        sp[QE][t] = P[6];
+        sp[QC][t] = P[8];
+        if (DIA) {
+            sp[QTR][t] = P[5];
+            sp[QER][t] = P[7];
+        }
+        if (hfl && !ex && !ey && !ez) {
+            const gptr<double> w = dst + (size_t)hcell * WS;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) w[q] = Wn[q];
+        }
+    }
+    // A boundary face's slot, read while the prims are staged.  The table holds
+    // -1 for a solid cell, so the smaller entry is the fluid cell's.
+    if (isface && g.nface > 0 && min(nL, nR) < 0) fbc = G(d.face_bc)[-min(nL, nR) - 1];
+    __syncthreads();
+
+    // 2. faces
+    if (isface) {
+        const bool fL = sflag[hL] != 0, fR = sflag[hR] != 0;
+        const double ih = a == 0 ? g.invh[0] : (a == 1 ? g.invh[1] : g.invh[2]);
+        if (fL && fR) {
+            const double rl = sp[QR][hL], rr = sp[QR][hR];
+            const double ul = sp[QU + a][hL], ur = sp[QU + a][hR];
+            const double vl = sp[QU + b1][hL], vr = sp[QU + b1][hR];
+            const double wl = sp[QU + b2][hL], wr = sp[QU + b2][hR];
+            const double tl = sp[QT][hL], tr = sp[QT][hR];
+            const double el = sp[QE][hL], er = sp[QE][hR];
+            double sA = 0.0, s1 = 0.0, s2 = 0.0, qn = 0.0, qr = 0.0, mu = 0.0;
+            if (!EULER) {
+                mu = pow_line(0.5 * (tl + tr), g.omega) * g.idelta;
+                // twice the mean over the face's two cells of the derivatives along the axis of stride S
+                // of the velocity components qa (normal) and qb (that axis)
+                auto tangential = [&](int S, int qa, int qb, double invh, double &da, double &db) {
+                    da = db = 0.0;
+#pragma unroll
+                    for (int side = 0; side < 2; ++side) {
+                        const int h = side ? hR : hL;
+                        const bool m = sflag[h - S] != 0, p = sflag[h + S] != 0;
+                        const int hm = m ? h - S : h, hp = p ? h + S : h;
+                        const double id = (m && p) ? 0.5 * invh : invh;
+                        da += (sp[qa][hp] - sp[qa][hm]) * id;
+                        db += (sp[qb][hp] - sp[qb][hm]) * id;
+                    }
+                };
+                double da1, d11, da2, d22;
+                tangential(S1, QU + a, QU + b1, b1 == 0 ? g.invh[0] : (b1 == 1 ? g.invh[1] : g.invh[2]), da1, d11);
+                tangential(S2, QU + a, QU + b2, b2 == 0 ? g.invh[0] : (b2 == 1 ? g.invh[1] : g.invh[2]), da2, d22);
+                const double dn = (ur - ul) * ih;
+                const double div = dn + 0.5 * (d11 + d22);
+                sA = -mu * (2.0 * dn - (2.0 / 3.0) * div);
+                s1 = -mu * ((vr - vl) * ih + 0.5 * da1);
+                s2 = -mu * ((wr - wl) * ih + 0.5 * da2);
+                qn = -g.kt * mu * (tr - tl) * ih;
+                if (DIA) qr = -g.kr * mu * (sp[QTR][hR] - sp[QTR][hL]) * ih;
+            }
+            const double sL = fabs(ul) + sp[QC][hL], sR = fabs(ur) + sp[QC][hR];
+            const double smax = sL > sR ? sL : sR, hs = 0.5 * smax;
+            const double pl = rl * tl, pr = rr * tr, ml = rl * ul, mr = rr * ur;
+            const double Fa = 0.5 * (ml * ul + 0.5 * pl + (mr * ur + 0.5 * pr)) - hs * (mr - ml) + 0.5 * sA;
+            const double F1 = 0.5 * (ml * vl + mr * vr) - hs * (rr * vr - rl * vl) + 0.5 * s1;
+            const double F2 = 0.5 * (ml * wl + mr * wr) - hs * (rr * wr - rl * wl) + 0.5 * s2;
+            const double Fe = 0.5 * ((el + pl) * ul + (er + pr) * ur) - hs * (er - el)
+                              + (sA * (0.5 * (ul + ur)) + s1 * (0.5 * (vl + vr)) + s2 * (0.5 * (wl + wr)) + qn + qr);
+            sf[0][t] = (0.5 * (ml + mr) - hs * (rr - rl)) * ih;
+            sf[1 + a][t] = Fa * ih;
+            sf[1 + b1][t] = F1 * ih;
+            sf[1 + b2][t] = F2 * ih;
+            sf[4][t] = Fe * ih;
+            if (DIA) {
+                const double gl = sp[QER][hL], gr = sp[QER][hR];
+                sf[NW - 1][t] = (0.5 * (gl * ul + gr * ur) - hs * (gr - gl) + qr) * ih;
+            }
+            sf[NW][t] = (EULER ? smax : fma(g.Cd * mu * ih, recip(0.5 * (rl + rr)), smax)) * ih;
+        } else if ((fL && fq > 0) || (fR && fq < MT)) {
+            // the boundary face of a cell of this tile (at most one of the two is fluid)
+            const int e = atomicAdd(&scount, 1);
+            slist[e] = make_int2(t | (fR ? hR : hL) << 8 | (2 * a + (fR ? 0 : 1)) << 16 | fbc << 20, -(fR ? nR : nL) - 1);
+        }
+    }
+    __syncthreads();
+    const int nbf = scount;
+    for (int base = 0; base < nbf; base += MBC) {   // uniform over the block
+        const int nf = min(MBC, nbf - base);
+        constexpr int QF = G13 ? 4 : 1;   // lanes that finish a face
+        double in[6];                     // the finishing lane's incoming moments, read ahead
+        if (!g.vlist && t < nf * QF) {
+            const int2 fe = slist[base + t / QF];
+            const gptr<const double> inp = G((const double *)d.inpsi) + ((fe.x >> 20) * 6 + ((fe.x >> 16) & 7)) * 6;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) in[k] = inp[k];
+        }
+        if (!g.vlist) {
+            // 1-D sums of w e^{-(xi - u)^2 / T} z^p (times xi on the outgoing half
+            // along the normal), z = xi, with the Grad-13 wall flux xi - u: a quad
+            // of lanes per face and axis
+            for (int task = t; task < nf * 12; task += 256) {
+                const int fa = task >> 2, e = fa / 3, j = fa - 3 * e;
+                const int2 fe = slist[base + e];
+                const int h = (fe.x >> 8) & 255, dir = (fe.x >> 16) & 7;
+                int ax = (dir >> 1) + j;
+                ax = ax > 2 ? ax - 3 : ax;
+                const gptr<const double> xs = G((const double *)(ax == 0 ? d.xi64[0] : (ax == 1 ? d.xi64[1] : d.xi64[2])));
+                const gptr<const double> ws = G((const double *)(ax == 0 ? d.w64[0] : (ax == 1 ? d.w64[1] : d.w64[2])));
+                const int n = ax == 0 ? g.n1[0] : (ax == 1 ? g.n1[1] : g.n1[2]);
+                const int kz = ax == 0 ? g.k0[0] : (ax == 1 ? g.k0[1] : g.k0[2]);
+                const int lo = j == 0 && (dir & 1) ? kz : 0, hi = j == 0 && !(dir & 1) ? kz : n;
+                const double u = sp[QU + ax][h], niT = -recip(sp[QT][h]);
+                const bool g13 = G13 && !EULER && g.wall_flux == 1;
+                double S[NS];
+#pragma unroll
+                for (int p = 0; p < NS; ++p) S[p] = 0.0;
+                // two nodes a step: two exponentials under way (past the end, the last node with weight 0)
+                for (int k = lo + (task & 3); k < hi; k += 8) {
+                    const int kb = min(k + 4, hi - 1);
+                    const double x[2] = {xs[k], xs[kb]}, wt[2] = {ws[k], k + 4 < hi ? ws[kb] : 0.0};
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const double c = x[q] - u, z = g13 ? c : x[q];
+                        double v = wt[q] * exp_core(fmax(c * c * niT, -745.0));
+                        if (j == 0) v *= x[q];
+#pragma unroll
+                        for (int p = 0; p < NS; ++p) {
+                            S[p] += v;
+                            v *= z;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < NS; ++p) S[p] = quad_sum(S[p]);
+                if ((task & 3) == 0) {
+#pragma unroll
+                    for (int p = 0; p < NS; ++p) ssum[fa * NS + p] = S[p];
+                }
+            }
+            __syncthreads();
+        }
+        if (t < nf * QF) {
+            const int e = t / QF;
+            const int2 fe = slist[base + e];
+            const int tf = fe.x & 255, h = (fe.x >> 8) & 255, dir = (fe.x >> 16) & 7, f = fe.y, ba = dir >> 1;
+            const double ih = ba == 0 ? g.invh[0] : (ba == 1 ? g.invh[1] : g.invh[2]);
+            const double sg = (dir & 1) ? ih : -ih;
+            double Fe[6], gam;
+            if (g.vlist) {
+#pragma unroll
+                for (int k = 0; k < NW; ++k) Fe[k] = G(d.Fb)[(size_t)k * g.nface + f];
+                gam = G(d.Gb)[f];
+            } else {
+                const int b = fe.x >> 20;
+                const double rho = sp[QR][h], T = sp[QT][h];
+                const double mu = EULER ? 0.0 : pow_line(T, g.omega) * g.idelta;
+                const double piT = PI * T;
+                const double K = rho * recip(piT * sqrt(piT)) * ((dir & 1) ? 1.0 : -1.0);
+                const double e1 = DIA ? 0.5 * g.dr * sp[QTR][h] : 0.0;
+                const double *S0 = ssum + e * 3 * NS, *S1 = S0 + NS, *S2 = S1 + NS;
+                const int bb1 = ba == 2 ? 0 : ba + 1;
+                double oA, o1, o2;   // momentum along the normal, b1 and b2
+                if (G13 && !EULER && g.wall_flux == 1) {
+                    double dv[3][5], sq[12];
+                    bool hm[3], hp[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const int S = c == 0 ? 1 : (c == 1 ? MH : MH * MH);
+                        hm[c] = sflag[h - S] != 0;
+                        hp[c] = sflag[h + S] != 0;
+                        const int m = hm[c] ? h - S : h, p = hp[c] ? h + S : h;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) dv[c][k] = sp[QU + k][p] - sp[QU + k][m];
+                        dv[c][4] = sp[QTR][p] - sp[QTR][m];
+                    }
+                    cell_nsf(g, dv, hm, hp, mu, sq);
+#pragma unroll
+                    for (int k = 0; k < 12; ++k) sq[k] += G(d.ghot)[(size_t)k * g.nface + f];
+                    // sigma, q, qr in the face's axes (ba, b1, b2): the diagonal 0..2, then (ba b1), (ba b2), (b1 b2)
+                    auto rot = [&](int i, int ax) { return ax == 0 ? sq[i] : (ax == 1 ? sq[i + 1] : sq[i + 2]); };
+                    const int bb2 = ba == 0 ? 2 : ba - 1;
+                    const double sl[6] = {rot(0, ba), rot(0, bb1), rot(0, bb2),
+                                          ba == 0 ? sq[3] : (ba == 1 ? sq[5] : sq[4]),
+                                          ba == 0 ? sq[4] : (ba == 1 ? sq[3] : sq[5]),
+                                          ba == 0 ? sq[5] : (ba == 1 ? sq[4] : sq[3])};
+                    const double ql[3] = {rot(6, ba), rot(6, bb1), rot(6, bb2)};
+                    const double rl[3] = {rot(9, ba), rot(9, bb1), rot(9, bb2)};
+                    const double cs = recip(rho * T * T), c5 = 0.4 * recip(T);
+                    // the seven bracketed sums (1, c_n, c_1, c_2, c_n^2, c_1^2, c_2^2), shared out over the quad
+                    double *B = sb + e * 8;
+                    for (int k = t & 3; k < 7; k += 4) {
+                        const int en = k == 1 ? 1 : (k == 4 ? 2 : 0), f1 = k == 2 ? 1 : (k == 5 ? 2 : 0),
+                                  f2 = k == 3 ? 1 : (k == 6 ? 2 : 0);
+                        B[k] = g13_bsum(S0 + en, S1 + f1, S2 + f2, sl, ql, cs, 2.0 * cs, c5);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    const double ul0 = sp[QU + ba][h], ul1 = sp[QU + bb1][h], ul2 = sp[QU + bb2][h];
+                    Fe[0] = K * B[0];
+                    oA = K * (B[1] + ul0 * B[0]);
+                    o1 = K * (B[2] + ul1 * B[0]);
+                    o2 = K * (B[3] + ul2 * B[0]);
+                    const double uu = ul0 * ul0 + ul1 * ul1 + ul2 * ul2;
+                    const double e0 = B[4] + B[5] + B[6] + 2.0 * (ul0 * B[1] + ul1 * B[2] + ul2 * B[3]) + uu * B[0];
+                    const double sr = rl[0] * S0[1] * S1[0] * S2[0] + rl[1] * S0[0] * S1[1] * S2[0] + rl[2] * S0[0] * S1[0] * S2[1];
+                    Fe[5] = DIA ? K * (e1 * B[0] + 2.0 * recip(rho * T) * sr) : 0.0;
+                    Fe[4] = K * e0 + Fe[5];
+                } else {
+                    const double s12 = S1[0] * S2[0];
+                    Fe[0] = K * S0[0] * s12;
+                    oA = K * S0[1] * s12;
+                    o1 = K * S0[0] * S1[1] * S2[0];
+                    o2 = K * S0[0] * S1[0] * S2[1];
+                    Fe[5] = e1 * Fe[0];
+                    Fe[4] = K * (S0[2] * s12 + S0[0] * (S1[2] * S2[0] + S1[0] * S2[2])) + Fe[5];
+                }
+                Fe[1] = ba == 0 ? oA : (ba == 1 ? o2 : o1);
+                Fe[2] = ba == 1 ? oA : (ba == 2 ? o2 : o1);
+                Fe[3] = ba == 2 ? oA : (ba == 0 ? o2 : o1);
+                const double sc = bc.kind[b] == 1 ? bc.rho[b] : Fe[0] * recip(-in[0]);
+#pragma unroll
+                for (int k = 0; k < NW; ++k) Fe[k] += sc * in[k];
+                gam = fabs(sp[QU + ba][h]) + sp[QC][h] + (EULER ? 0.0 : g.Cd * mu * ih * recip(rho));
+            }
+            if (QF == 1 || (t & 3) == 0) {
+#pragma unroll
+                for (int k = 0; k < NW; ++k) sf[k][tf] = Fe[k] * sg;
+                sf[NW][tf] = gam * ih;
+            }
+        }
+        __syncthreads();
+    }
+
+    // 3. residual and diagonal: wave w adds components 2 w and 2 w + 1, the last wave D
+    const int h = (cx + 1) + MH * ((cy + 1) + MH * (cz + 1));
+    const bool live = sflag[h] != 0;
+    // the faces below and above the cell along each axis
+    const int xl = cx + 4 * cy + 16 * cz, xh = cx < 3 ? xl + 1 : 192 + cy + 4 * cz;
+    const int yl = 64 + cy + 4 * cz + 16 * cx, yh = cy < 3 ? yl + 1 : 208 + cz + 4 * cx;
+    const int zl = 128 + cz + 4 * cx + 16 * cy, zh = cz < 3 ? zl + 1 : 224 + cx + 4 * cy;
+    if (w < 3) {
+        if (!live) return;
+        const gptr<double> R = dst + (size_t)cell * WS;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int k = 2 * w + q;
+            if (k >= NW) break;
+            double res = rc[q] + (sf[k][xl] - sf[k][xh]) + (sf[k][yl] - sf[k][yh]) + (sf[k][zl] - sf[k][zh]);
+            if (DIA && k == 5) {
+                const double T = sp[QT][h], Tr = sp[QTR][h], rho = sp[QR][h];
+                const double rate = g.delta * rho * T / (pow_line(T, g.omega) * g.Zr);   // 1 / (Z tau)
+                const double Tm = (3.0 * T + g.dr * Tr) / (3.0 + g.dr);
+                res += 0.5 * g.dr * rho * (Tm - Tr) * rate;
+                R[WSRC] = rate;
+            }
+            R[NW + k] = res;
+        }
+        return;
+    }
+    double D = 0.0;
+    if (live) {
+        const double u0 = sp[QU][h], u1 = sp[QU + 1][h], u2 = sp[QU + 2][h], T = sp[QT][h];
+        const double sumG = ((sf[NW][xl] + sf[NW][xh]) + (sf[NW][yl] + sf[NW][yh])) + (sf[NW][zl] + sf[NW][zh]);
+        const double vis = EULER ? 0.0 : g.Cd * (pow_line(T, g.omega) * g.idelta) * recip(sp[QR][h] * g.hmin);
+        const double idt = (sqrt(u0 * u0 + u1 * u1 + u2 * u2) + sp[QC][h] + vis) / (g.macro_cfl * g.hmin);
+        D = idt + 0.5 * sumG;
+        if (!(D > 0.0 && isfinite(D))) {
+            atomicOr(d.errflag, 2);
+            D = 0.0;
+        }
+    }
+    D = row_max(D);
+    D = fmax(D, __shfl_xor(D, 16, 64));
+    D = fmax(D, __shfl_xor(D, 32, 64));
+    if (c == 0 && D > 0.0)
+        atomicMax(&d.dmax[(size_t)(it % DSETS * DSLOT + (blk & (BSLOT - 1))) * DSTRIDE],
+                  (unsigned long long)__double_as_longlong(D));
 }
 
 // one block per case
@@ -887,7 +1227,7 @@ __global__ void k_mac_reset(GSIS_SPAN_ARGS)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
-    for (int j = threadIdx.x; j < 2 * DSLOT; j += blockDim.x) G(C.d.dmax)[(size_t)j * DSTRIDE] = 0ull;
+    for (int j = threadIdx.x; j < DSETS * DSLOT; j += blockDim.x) G(C.d.dmax)[(size_t)j * DSTRIDE] = 0ull;
 }
 
 // New half of the correction record; flags non-physical states.
@@ -906,37 +1246,66 @@ __global__ __launch_bounds__(128) void k_mac_final(GSIS_SPAN_ARGS)
     if (!(P[0] > 0.0) || !(P[4] > 0.0) || !isfinite(P[6]) || (g.species == 1 && !(P[5] > 0.0))) atomicOr(d.errflag, 4);
 }
 
+// The last step of the solve on the box (none for iters = 0) and the new half
+// of the correction record; flags non-physical states.
+template <bool DIA>
+__global__ __launch_bounds__(128) void k_mac_close(GSIS_SPAN_ARGS, int iters)
+{
+    int blk;
+    const Case &C = case_of(span_cases, span_map, blk);
+    const Geo &g = C.g;
+    const Dev &d = C.d;
+    double Dm = 1.0;
+    if (iters > 0) Dm = largest_diagonal(d, (iters - 1) % DSETS);
+    const int cell = blk * blockDim.x + threadIdx.x;
+    if (cell >= g.ncell || !G(d.cflag)[cell]) return;
+    double W[6], P[9];
+    stepped_W<DIA>(G((const double *)((iters & 1) ? d.W2 : d.W)) + (size_t)cell * (DIA ? WS_DIA : WS_MONO), iters, Dm,
+                   1.0 / Dm, W);
+    short_prims<DIA>(g, W, P);
+    const gptr<double> c = G(d.corr) + (size_t)cell * NCORR;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) c[k] = P[k];
+    if (!(P[0] > 0.0) || !(P[4] > 0.0) || !isfinite(P[6]) || (DIA && !(P[5] > 0.0))) atomicOr(d.errflag, 4);
+}
+
+// Launch it of an inner loop of iters forms the residual of iterate it (from
+// iterate it - 1, its residual and D*); k_mac_close takes the last step.
+template <bool DIA, bool EULER, bool G13>
+static void mac_loop(const Target &t, int iters, hipStream_t s)
+{
+    for (int it = 0; it < iters; ++it) {
+        if (t.vlist && t.host[0].g.nface > 0)
+            hipLaunchKernelGGL((k_mac_bface<DIA, EULER, G13>), dim3((t.host[0].g.nface + 3) / 4), dim3(256), 0, s,
+                               GSIS_SPAN(t.span(K_CELL1)), it);
+        hipLaunchKernelGGL((k_mac_iter<DIA, EULER, G13>), dim3(t.nblk[K_MTILE]), dim3(256), 0, s,
+                           GSIS_SPAN(t.span(K_MTILE)), it);
+    }
+    hipLaunchKernelGGL(k_mac_close<DIA>, dim3(t.nblk[K_CELL128]), dim3(128), 0, s, GSIS_SPAN(t.span(K_CELL128)), iters);
+}
+
 hipError_t launch_gsis_macro(const Target &t, int iters, hipStream_t s, int euler)
 {
     hipLaunchKernelGGL(k_mac_reset, dim3(t.nblk[K_CASE]), dim3(64), 0, s, GSIS_SPAN(t.span(K_CASE)));
     hipLaunchKernelGGL(k_mac_init, dim3(t.nblk[K_CELL128]), dim3(128), 0, s, GSIS_SPAN(t.span(K_CELL128)));
-    hipLaunchKernelGGL(k_mac_grad, dim3(t.nblk[K_GRAD]), dim3(256), 0, s, GSIS_SPAN(t.span(K_GRAD)), 0, euler);
+    hipLaunchKernelGGL(k_mac_grad, dim3(t.nblk[K_GRAD]), dim3(256), 0, s, GSIS_SPAN(t.span(K_GRAD)));
     hipLaunchKernelGGL(k_mac_hot, dim3(t.nblk[K_CELL128]), dim3(128), 0, s, GSIS_SPAN(t.span(K_CELL128)), euler);
     if (t.nblk[K_FACE8] > 0) {
         if (t.g13) hipLaunchKernelGGL(k_mac_fbfix<true>, dim3(t.nblk[K_FACE8]), dim3(256), 0, s, GSIS_SPAN(t.span(K_FACE8)), euler);
         else hipLaunchKernelGGL(k_mac_fbfix<false>, dim3(t.nblk[K_FACE8]), dim3(256), 0, s, GSIS_SPAN(t.span(K_FACE8)), euler);
     }
-    for (int it = 0; it < iters; ++it) {
-        const int slot = it & 1;
-        // the Euler form is its own instantiation: a run-time flag costs the
-        // residual registers (and spills) on the common path
-        const dim3 gr(t.nblk[K_RES]), bl(384);
-        const Span sp = t.span(K_RES);
-        if (t.dia) {
-            if (euler) hipLaunchKernelGGL((k_mac_res<true, true>), gr, bl, 0, s, GSIS_SPAN(sp), slot);
-            else hipLaunchKernelGGL((k_mac_res<true, false>), gr, bl, 0, s, GSIS_SPAN(sp), slot);
-        } else {
-            if (euler) hipLaunchKernelGGL((k_mac_res<false, true>), gr, bl, 0, s, GSIS_SPAN(sp), slot);
-            else hipLaunchKernelGGL((k_mac_res<false, false>), gr, bl, 0, s, GSIS_SPAN(sp), slot);
-        }
-        if (t.g13)
-            hipLaunchKernelGGL(k_mac_advance<true>, dim3(t.nblk[K_GRAD]), dim3(256), 0, s, GSIS_SPAN(t.span(K_GRAD)), slot,
-                               it & 1, it == iters - 1 ? 1 : 0, euler);
-        else
-            hipLaunchKernelGGL(k_mac_advance<false>, dim3(t.nblk[K_GRAD]), dim3(256), 0, s, GSIS_SPAN(t.span(K_GRAD)), slot,
-                               it & 1, it == iters - 1 ? 1 : 0, euler);
+    hipLaunchKernelGGL(k_mac_const, dim3(t.nblk[K_CELL128]), dim3(128), 0, s, GSIS_SPAN(t.span(K_CELL128)));
+    // the Euler form and the Grad-13 wall flux are their own instantiations: as
+    // run-time flags they would cost the common path registers
+    if (t.dia) {
+        if (euler) mac_loop<true, true, false>(t, iters, s);
+        else if (t.g13) mac_loop<true, false, true>(t, iters, s);
+        else mac_loop<true, false, false>(t, iters, s);
+    } else {
+        if (euler) mac_loop<false, true, false>(t, iters, s);
+        else if (t.g13) mac_loop<false, false, true>(t, iters, s);
+        else mac_loop<false, false, false>(t, iters, s);
     }
-    hipLaunchKernelGGL(k_mac_final, dim3(t.nblk[K_CELL128]), dim3(128), 0, s, GSIS_SPAN(t.span(K_CELL128)));
     return hipGetLastError();
 }
 
@@ -1511,8 +1880,8 @@ int kind_blocks(const Geo &g, Kind k)
     case K_CELL1: return g.ncell;
     case K_FACE256: return (g.nface + 255) / 256;
     case K_FACE8: return face_blocks(g);
-    case K_GRAD: return grad_blocks(g) + face_blocks(g);
-    case K_RES: return (g.ncell + RES_CELLS - 1) / RES_CELLS;
+    case K_GRAD: return grad_blocks(g);
+    case K_MTILE: return mtile_blocks(g);
     case K_CASE: return 1;
     default: return 0;
     }
