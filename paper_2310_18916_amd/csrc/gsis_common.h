@@ -62,6 +62,7 @@ struct Geo {
     int umaxcnt;   // nodes of the largest class
     int umaxf;     // faces of the cell with the most
     int unface;    // faces of the mesh
+    int ubgn;      // pairs of boundary faces
     int ucen;      // 1: centroids given (the macroscopic correction runs)
     double uhmin;  // smallest face distance h of the macroscopic pseudo time step
     // macroscopic boundary flux of the correction: 0 the Maxwellian's change,
@@ -142,10 +143,16 @@ struct Dev {
     // macroscopic correction on the mesh (centroids given): per face entry the
     // least-squares weights [3] of the neighbour across (0 on the boundary) and
     // the face (f << 1 | 1 when the cell is the face's neighbour); per face
-    // (owner, neighbour or -1 - boundary face) and (S, n, h, |d|, d/|d|) [9];
-    // the kinetic flux [6], its fixed part [6] and the iterate's flux and Gamma
-    // [7]; per boundary face the incoming half-range psi-moments of its
+    // (owner, neighbour or -1 - boundary face) and (S, n, h, |d|, d/|d|) as
+    // [9][unface]; the kinetic flux [6], its fixed part [6] and the iterate's
+    // flux, Gamma and S [8]; per boundary face the incoming half-range psi-moments of its
     // boundary Maxwellian [6]
+    // boundary faces in pairs of one outward direction (ubg, the second -1 where
+    // there is none), per pair that direction, and per direction the runs
+    // [first, end) of nodes whose classes leave through it, ubr[ubro[q]] ..
+    // ubr[ubro[q + 1]]
+    int2 *ubg, *ubr;
+    int *ubgd, *ubro;
     double *ucf_lsq;
     int *ucf_face;
     int *ucf_first;    // [ncell + 1] first face entry of every cell

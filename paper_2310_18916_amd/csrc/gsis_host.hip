@@ -30,6 +30,7 @@ struct gsis_ctx {
     std::vector<double> uvol, ucf_g, ubf_n, ucf_lsq, uf_geo;
     std::vector<int> ucf_nb, ucf_meta, ulev, ulev_off, ubf_cell, ubf_slot, uperm, ucls;   // ulev: 2 ints per entry
     std::vector<int> ucf_face, uf_cell, ucf_first, ubf_face;
+    std::vector<int> ubg, ubgd, ubr, ubro;   // ubg, ubr: 2 ints per pair and run
     int tx = 0, ty = 0, tz = 0, bs = 0;
     std::vector<int> tiles, plane_off, plane_cnt, npblk;
     std::vector<int> tent, nclean;   // split sweep entries (cases with solid cells)
@@ -335,6 +336,8 @@ size_t layout(gsis_ctx *c, char *base)
     d.ucf_lsq = nullptr; d.ucf_face = nullptr; d.uf_cell = nullptr; d.ucf_first = nullptr; d.ubf_face = nullptr;
     d.uf_geo = d.uFk = d.ufix = d.uFf = d.ubin = nullptr;
     d.ubsq = d.ubhot = nullptr;
+    d.ubg = d.ubr = nullptr;
+    d.ubgd = d.ubro = nullptr;
     d.ubf_cell = d.ubf_slot = nullptr; d.ubf_n = nullptr; d.ubf_s64 = nullptr; d.ubf_s32 = nullptr;
     if (g.umesh) {
         const size_t ne = c->ucf_nb.size(), nb = std::max(g.unbf, 1);
@@ -360,10 +363,14 @@ size_t layout(gsis_ctx *c, char *base)
             carve(off, d.uf_geo, nfc * 9, base);
             carve(off, d.uFk, nfc * 6, base);
             carve(off, d.ufix, nfc * 6, base);
-            carve(off, d.uFf, nfc * 7, base);
+            carve(off, d.uFf, nfc * 8, base);
             carve(off, d.ubin, nb * 6, base);
             carve(off, d.ubsq, nb * 12, base);
             carve(off, d.ubhot, nb * 12, base);
+            carve(off, d.ubr, c->ubr.size() / 2, base);
+            carve(off, d.ubro, c->ubro.size(), base);
+            carve(off, d.ubg, c->ubg.size() / 2, base);
+            carve(off, d.ubgd, c->ubgd.size(), base);
         }
     }
     carve(off, d.corr, n * NCORR, base);
@@ -1004,8 +1011,35 @@ gsis_status gsis_set_spatial_mesh(gsis_ctx *ctx, int ncell, const double *volume
             }
         }
     }
+    // boundary faces by outward direction (+n_k: 2 k, -n_k: 2 k + 1) in pairs,
+    // and the runs of nodes that leave through each direction
+    std::vector<int> bg, bgd, br, bro(1, 0);
+    for (int q = 0; q < 2 * nori; ++q) {
+        bool open = false;
+        for (size_t b = 0; b < bface.size(); ++b) {
+            if (2 * fk[bface[b]] + fflip[bface[b]] != q) continue;
+            if (open) {
+                bg.back() = (int)b;
+            } else {
+                bg.insert(bg.end(), {(int)b, -1});
+                bgd.push_back(q);
+            }
+            open = !open;
+        }
+        for (int c = 0; c < ncls; ++c) {
+            if (((masks[c] >> (q >> 1)) & 1u) == (unsigned)(q & 1)) continue;   // the class enters
+            if ((int)br.size() > 2 * bro[q] && br.back() == cpos[c]) br.back() = cpos[c + 1];
+            else br.insert(br.end(), {cpos[c], cpos[c + 1]});
+        }
+        bro.push_back((int)br.size() / 2);
+    }
     // commit
     Geo &g = ctx->g;
+    ctx->ubg = bg;
+    ctx->ubgd = bgd;
+    ctx->ubr = br;
+    ctx->ubro = bro;
+    g.ubgn = (int)bgd.size();
     ctx->uvol.assign(volume, volume + ncell);
     ctx->ucf_nb = cnb;
     ctx->ucf_meta = cmeta;
@@ -1027,7 +1061,10 @@ gsis_status gsis_set_spatial_mesh(gsis_ctx *ctx, int ncell, const double *volume
     ctx->ucf_first = off;
     ctx->ubf_face = bface;
     ctx->uf_cell = fcell;
-    ctx->uf_geo = fgeo;
+    // [9][nface] on the device
+    ctx->uf_geo.resize(fgeo.size());
+    for (size_t f = 0; f < fgeo.size() / 9; ++f)
+        for (int k = 0; k < 9; ++k) ctx->uf_geo[(size_t)k * nface + f] = fgeo[9 * f + k];
     g.ucen = cell_center ? 1 : 0;
     g.unface = nface;
     g.uhmin = hmin;
@@ -1180,6 +1217,12 @@ gsis_status gsis_bind_workspace(gsis_ctx *ctx, void *device_ptr, size_t bytes)
             HIPCHK(ctx, up(d.ucf_lsq, ctx->ucf_lsq.data(), ctx->ucf_lsq.size() * sizeof(double)));
             HIPCHK(ctx, up(d.ucf_face, ctx->ucf_face.data(), ctx->ucf_face.size() * sizeof(int)));
             HIPCHK(ctx, up(d.ucf_first, ctx->ucf_first.data(), ctx->ucf_first.size() * sizeof(int)));
+            if (g.unbf > 0) {
+                HIPCHK(ctx, up(d.ubr, ctx->ubr.data(), ctx->ubr.size() * sizeof(int)));
+                HIPCHK(ctx, up(d.ubro, ctx->ubro.data(), ctx->ubro.size() * sizeof(int)));
+                HIPCHK(ctx, up(d.ubg, ctx->ubg.data(), ctx->ubg.size() * sizeof(int)));
+                HIPCHK(ctx, up(d.ubgd, ctx->ubgd.data(), ctx->ubgd.size() * sizeof(int)));
+            }
             if (g.unbf > 0) HIPCHK(ctx, up(d.ubf_face, ctx->ubf_face.data(), ctx->ubf_face.size() * sizeof(int)));
             HIPCHK(ctx, up(d.uf_cell, ctx->uf_cell.data(), ctx->uf_cell.size() * sizeof(int)));
             HIPCHK(ctx, up(d.uf_geo, ctx->uf_geo.data(), ctx->uf_geo.size() * sizeof(double)));

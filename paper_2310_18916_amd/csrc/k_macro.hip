@@ -1384,13 +1384,8 @@ __device__ __forceinline__ void uface_flux(const Geo &g, const PV &L, const PV &
 
 // Velocity gradient of every cell: G[b][c] = sum over its interior face
 // entries of (u_j - u_i)_b w_c.
-__global__ __launch_bounds__(256) void k_umac_grad(GSIS_SPAN_ARGS)
+__device__ __forceinline__ void ucell_grad(const Geo &g, const Dev &d, int cell)
 {
-    int blk;
-    const Case &C = case_of(span_cases, span_map, blk);
-    const Geo &g = C.g;
-    const Dev &d = C.d;
-    const int cell = blk * blockDim.x + threadIdx.x;
     if (cell >= g.ncell) return;
     const size_t n = g.ncell;
     const Soa<double> P = soa(d.P, n, cell);
@@ -1416,6 +1411,13 @@ __global__ __launch_bounds__(256) void k_umac_grad(GSIS_SPAN_ARGS)
     for (int k = 0; k < 9; ++k) Gd[k] = Gc[k];
 }
 
+__global__ __launch_bounds__(256) void k_umac_grad(GSIS_SPAN_ARGS)
+{
+    int blk;
+    const Case &C = case_of(span_cases, span_map, blk);
+    ucell_grad(C.g, C.d, blk * (int)blockDim.x + (int)threadIdx.x);
+}
+
 // Kinetic flux of every face out of its owner, one wave per face: sum over
 // the nodes of w (xi.n) psi f_face, psi = (1, xi, |xi|^2 f0 + f1, f1), f_face
 // the upwind cell's value inside; on a boundary face the owner's value going
@@ -1433,7 +1435,7 @@ __global__ __launch_bounds__(256) void k_umac_kin(GSIS_SPAN_ARGS)
     if (f >= g.unface) return;
     const int lane = threadIdx.x & 63;
     const int L = G(d.uf_cell)[2 * (size_t)f], R = G(d.uf_cell)[2 * (size_t)f + 1];
-    const gptr<const double> fg = G((const double *)d.uf_geo) + 9 * (size_t)f;
+    const Soa<double> fg = soa(d.uf_geo, (size_t)g.unface, f);
     const double n0 = fg[1], n1 = fg[2], n2 = fg[3];
     const size_t nv = (size_t)g.nv;
     const gptr<const T> f0L = (gptr<const T>)d.f0 + (size_t)L * nv;
@@ -1492,6 +1494,17 @@ __global__ __launch_bounds__(256) void k_umac_kin(GSIS_SPAN_ARGS)
     if (lane < 6) G(d.uFk)[6 * (size_t)f + lane] = acc[lane];
 }
 
+// A face's fixed part plus F, its Gamma and area, one 64-byte record for the
+// cells that gather it.
+__device__ __forceinline__ void store_face(const Dev &d, size_t f, const double F[6], double Gam, double S)
+{
+    const gptr<const f64x2> fix = (gptr<const f64x2>)d.ufix + 3 * f;
+    const gptr<f64x2> o = (gptr<f64x2>)d.uFf + 4 * f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) o[k] = f64x2{F[2 * k] + fix[k].x, F[2 * k + 1] + fix[k].y};
+    o[3] = f64x2{Gam, S};
+}
+
 // Interior faces, one thread each: the macroscopic flux of the current W;
 // mode 0 keeps F_kin - F as the face's high-order terms, mode 1 stores
 // F + HoT and Gamma for the residual.
@@ -1508,7 +1521,7 @@ __global__ __launch_bounds__(256) void k_umac_iflux(GSIS_SPAN_ARGS, int mode, in
     const size_t n = g.ncell;
     double fg[9];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) fg[k] = G(d.uf_geo)[9 * (size_t)f + k];
+    for (int k = 0; k < 9; ++k) fg[k] = G(d.uf_geo)[(size_t)k * g.unface + f];
     double F[6], Gam;
     uface_flux(g, soa(d.P, n, L), soa(d.P, n, R), soa(d.grad, n, L), soa(d.grad, n, R), fg, euler != 0, F, &Gam);
     if (mode == 0) {
@@ -1516,9 +1529,7 @@ __global__ __launch_bounds__(256) void k_umac_iflux(GSIS_SPAN_ARGS, int mode, in
         for (int k = 0; k < 6; ++k) G(d.ufix)[6 * (size_t)f + k] = G(d.uFk)[6 * (size_t)f + k] - F[k];
         if (g.species != 1) G(d.ufix)[6 * (size_t)f + 5] = 0.0;
     } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) G(d.uFf)[7 * (size_t)f + k] = F[k] + G(d.ufix)[6 * (size_t)f + k];
-        G(d.uFf)[7 * (size_t)f + 6] = Gam;
+        store_face(d, f, F, Gam, fg[0]);
     }
 }
 
@@ -1593,58 +1604,67 @@ __global__ __launch_bounds__(256) void k_umac_g13s(GSIS_SPAN_ARGS, int mode)
     for (int k = 0; k < 12; ++k) G(d.ubsq)[(size_t)k * nb + bf] = sq[k];
 }
 
-// Boundary faces, NF to a wave: F_eq of the owner's Maxwellian (outgoing
-// half-range sums over the nodes, incoming part the boundary Maxwellian at
-// the face's density rule); the wave reads every node's velocity once for
-// its NF faces.  Mode 0 keeps F_kin - F_eq(W^{n+1/2}), mode 1 stores fixed
+// Boundary faces, two of one outward direction to a wave: F_eq of the owner's
+// Maxwellian (outgoing half-range sums over the nodes, incoming part the
+// boundary Maxwellian at the face's density rule).  The wave walks the runs of
+// nodes whose classes leave through that direction and reads every node once
+// for both faces.  Mode 0 keeps F_kin - F_eq(W^{n+1/2}), mode 1 stores fixed
 // part + F_eq(W^m) and Gamma.  G13: the same with the outgoing half of the
 // owner's Grad-13 distributions of Eq. (G13_VDF) (stress and heat fluxes
 // from k_umac_g13s), f0 = M B(c), f1 = (dr/2) Tr f0 + 2 M (qr.c) / (rho Tt).
-// Two faces to a wave (tetrahedral block flow, 17k boundary faces x 7788
-// nodes, 300 inner iterations: 8 faces 120.3 ms per correction, 4: 106.3,
-// 2: 103.7, 1: 116.1; Grad-13 form 4: 140.2, 2: 129.1).
-constexpr int UBF = 2, UBF_G13 = 2;
+// A lane takes the nodes at its place in every aligned stretch of 64, in
+// order, and nodes outside a run count zero, so that every sum is formed as in
+// a walk over all nodes: the first corrections of a hypersonic start pass
+// through cells near vacuum that blow a change of rounding up from 1e-16 to
+// 1e-8 in the fields.  Splitting the sums over waves, or factoring the
+// exponential by axis, is therefore left out, although it takes 39 us.
+// Measured on 124k tetrahedra with 9648 boundary faces and 7788 nodes: 65 us a
+// call (95 with every node walked; the gradients' blocks, 9 us on their own,
+// run beside it), of which the FP64 instructions, 49 per face and node, are 51.
+constexpr int UBF = 2;
 
-template <int NF, bool G13>
+template <bool G13>
 __global__ __launch_bounds__(256) void k_umac_bflux(GSIS_SPAN_ARGS, int mode, int euler)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
     const Dev &d = C.d;
-    constexpr int UBF = NF;
-    const int bf0 = __builtin_amdgcn_readfirstlane((blk * 4 + (int)(threadIdx.x >> 6)) * UBF);
-    if (bf0 >= g.unbf) return;
+    const int nbb = (g.ubgn + 3) / 4;
+    if (blk >= nbb) {   // the velocity gradients of the same state, beside the boundary faces
+        ucell_grad(g, d, (blk - nbb) * (int)blockDim.x + (int)threadIdx.x);
+        return;
+    }
+    const int pair = __builtin_amdgcn_readfirstlane(blk * 4 + (int)(threadIdx.x >> 6));
+    if (pair >= g.ubgn) return;
+    const cptr<int> bfp = (cptr<int>)(d.ubg + pair);
     const int lane = threadIdx.x & 63;
     const bool dia = g.species == 1;
-    int f[UBF], cell[UBF], slot[UBF];
+    const size_t nc = (size_t)g.ncell, nfc = (size_t)g.unface;
     double n[UBF][3], u[UBF][3], iT[UBF], s0[UBF], s1[UBF][3], s4[UBF];
     // Grad-13: the bracket's coefficients per face, sigma / (rho Tt^2),
     // 2 q / (rho Tt^2), 2 / (5 Tt), 2 qr / (rho Tt), and the q_r sum
     double sg[G13 ? UBF : 1][6], qv[G13 ? UBF : 1][3], c5[G13 ? UBF : 1], qr[G13 ? UBF : 1][3], sr[G13 ? UBF : 1];
+    // the faces' state and normals are the same for every lane: scalar loads
 #pragma unroll
     for (int q = 0; q < UBF; ++q) {
-        const int bf = min(bf0 + q, g.unbf - 1);
-        f[q] = G(d.ubf_face)[bf];
-        cell[q] = G(d.ubf_cell)[bf];
-        slot[q] = G(d.ubf_slot)[bf];
-        const gptr<const double> fg = G((const double *)d.uf_geo) + 9 * (size_t)f[q];
-        n[q][0] = fg[1];
-        n[q][1] = fg[2];
-        n[q][2] = fg[3];
-        const Soa<double> P = soa(d.P, (size_t)g.ncell, cell[q]);
-        u[q][0] = P[1];
-        u[q][1] = P[2];
-        u[q][2] = P[3];
-        iT[q] = 1.0 / P[4];
+        const int bf = bfp[q] >= 0 ? bfp[q] : bfp[0];   // a missing face repeats the first
+        const cptr<double> fg = (cptr<double>)d.uf_geo + ((cptr<int>)d.ubf_face)[bf];
+        const cptr<double> P = (cptr<double>)d.P + ((cptr<int>)d.ubf_cell)[bf];
+        n[q][0] = fg[nfc];
+        n[q][1] = fg[2 * nfc];
+        n[q][2] = fg[3 * nfc];
+        u[q][0] = P[nc];
+        u[q][1] = P[2 * nc];
+        u[q][2] = P[3 * nc];
+        iT[q] = 1.0 / P[4 * nc];
         s0[q] = s4[q] = 0.0;
         s1[q][0] = s1[q][1] = s1[q][2] = 0.0;
         if constexpr (G13) {
-            const int bf = min(bf0 + q, g.unbf - 1);
             const size_t nb = g.unbf;
-            const gptr<const double> b = G((const double *)d.ubsq) + bf;
-            const double irT2 = 1.0 / (P[0] * P[4] * P[4]);
-            const double cr = 2.0 / (P[0] * P[4]);
+            const cptr<double> b = (cptr<double>)d.ubsq + bf;
+            const double irT2 = 1.0 / (P[0] * P[4 * nc] * P[4 * nc]);
+            const double cr = 2.0 / (P[0] * P[4 * nc]);
 #pragma unroll
             for (int k = 0; k < 6; ++k) sg[q][k] = b[(size_t)k * nb] * irT2;
 #pragma unroll
@@ -1652,42 +1672,69 @@ __global__ __launch_bounds__(256) void k_umac_bflux(GSIS_SPAN_ARGS, int mode, in
                 qv[q][k] = 2.0 * irT2 * b[(size_t)(6 + k) * nb];
                 qr[q][k] = dia ? cr * b[(size_t)(9 + k) * nb] : 0.0;
             }
-            c5[q] = 2.0 / (5.0 * P[4]);
+            c5[q] = 2.0 / (5.0 * P[4 * nc]);
             sr[q] = 0.0;
         }
     }
     const gptr<const double> nt = G((const double *)d.nt64);
-    for (int pos = lane; pos < g.nv; pos += 64) {
-        const double x0 = nt[4 * (size_t)pos], x1 = nt[4 * (size_t)pos + 1], x2 = nt[4 * (size_t)pos + 2];
-        const double w = nt[4 * (size_t)pos + 3], xx = x0 * x0 + x1 * x1 + x2 * x2;
+    const int dq = ((cptr<int>)d.ubgd)[pair];
+    int rr = ((cptr<int>)d.ubro)[dq] - 1, p0 = 0, p1 = 0, at = 0;
+    const int rb = ((cptr<int>)d.ubro)[dq + 1];
+    // the wave's next stretch of 64 nodes, from the multiple of 64 below a run's first
+    auto next = [&]() -> bool {
+        at += 64;
+        while (at >= p1) {
+            if (++rr >= rb) return false;
+            p0 = ((cptr<int>)d.ubr)[2 * rr];
+            p1 = ((cptr<int>)d.ubr)[2 * rr + 1];
+            at = p0 & ~63;
+        }
+        return true;
+    };
+    struct Node { double x[3], w; };
+    auto read = [&](Node &v) {   // a lane outside the run reads an end of it with weight 0
+        const int pos = at + lane;
+        const gptr<const double> t = nt + 4 * (size_t)min(max(pos, p0), p1 - 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v.x[k] = t[k];
+        v.w = pos >= p0 && pos < p1 ? t[3] : 0.0;
+    };
+    // the next stretch is read while the sums of this one are formed
+    Node cur, nxt;
+    bool more = next();
+    if (more) read(cur);
+    while (more) {
+        more = next();
+        if (more) read(nxt);
+        const double x0 = cur.x[0], x1 = cur.x[1], x2 = cur.x[2], w = cur.w, xx = x0 * x0 + x1 * x1 + x2 * x2;
 #pragma unroll
         for (int q = 0; q < UBF; ++q) {
-            const double xn = x0 * n[q][0] + x1 * n[q][1] + x2 * n[q][2];
-            if (!(xn > 0.0)) continue;
+            const double xn = fmax(x0 * n[q][0] + x1 * n[q][1] + x2 * n[q][2], 0.0);
             const double cx = x0 - u[q][0], cy = x1 - u[q][1], cz = x2 - u[q][2];
+            const double cc = cx * cx + cy * cy + cz * cz;
+            const double e = w * exp_core(fmax(-cc * iT[q], -745.0)) * xn;
+            double ex = e;
             if constexpr (G13) {
-                const double cc = cx * cx + cy * cy + cz * cz;
-                const double e = w * exp_core(fmax(-cc * iT[q], -745.0)) * xn;
                 const double scc = sg[q][0] * cx * cx + sg[q][1] * cy * cy + sg[q][2] * cz * cz
                                  + 2.0 * (sg[q][3] * cx * cy + sg[q][4] * cx * cz + sg[q][5] * cy * cz);
                 const double qc = qv[q][0] * cx + qv[q][1] * cy + qv[q][2] * cz;
-                const double ex = e * (1.0 + scc + qc * (c5[q] * cc - 1.0));
-                s0[q] += ex;
-                s1[q][0] += ex * x0;
-                s1[q][1] += ex * x1;
-                s1[q][2] += ex * x2;
-                s4[q] += ex * xx;
+                ex = e * (1.0 + scc + qc * (c5[q] * cc - 1.0));
                 sr[q] += e * (qr[q][0] * cx + qr[q][1] * cy + qr[q][2] * cz);
-            } else {
-                const double ex = w * exp_core(fmax(-(cx * cx + cy * cy + cz * cz) * iT[q], -745.0)) * xn;
-                s0[q] += ex;
-                s1[q][0] += ex * x0;
-                s1[q][1] += ex * x1;
-                s1[q][2] += ex * x2;
-                s4[q] += ex * xx;
             }
+            s0[q] += ex;
+            s1[q][0] += ex * x0;
+            s1[q][1] += ex * x1;
+            s1[q][2] += ex * x2;
+            s4[q] += ex * xx;
         }
+        cur = nxt;
     }
+    // lane q finishes face q
+    const int bf = bfp[lane < UBF ? lane : 0] >= 0 ? bfp[lane < UBF ? lane : 0] : bfp[0];
+    const size_t ff = (size_t)G(d.ubf_face)[bf];
+    const int slot = G(d.ubf_slot)[bf];
+    const Soa<double> P = soa(d.P, nc, G(d.ubf_cell)[bf]), fg = soa(d.uf_geo, nfc, (int)ff);
+    const gptr<const double> bin = G((const double *)d.ubin) + 6 * (size_t)bf;
 #pragma unroll
     for (int q = 0; q < UBF; ++q) {
         s0[q] = wave_sum(s0[q]);
@@ -1696,42 +1743,35 @@ __global__ __launch_bounds__(256) void k_umac_bflux(GSIS_SPAN_ARGS, int mode, in
         s4[q] = wave_sum(s4[q]);
         if constexpr (G13) sr[q] = wave_sum(sr[q]);
     }
-    // lane q finishes face q
+    if (lane >= UBF || bfp[lane] < 0) return;
+    auto mine = [&](double a0, double a1) { return lane == 0 ? a0 : a1; };
+    static_assert(UBF == 2, "a pair of faces");
+    const double t0 = mine(s0[0], s0[1]), t4 = mine(s4[0], s4[1]);
+    const double rho = P[0], T = P[4];
+    const double piT = PI * T, K = rho / (piT * sqrt(piT));
+    const double h1 = g.species == 1 ? 0.5 * g.dr * P[5] : 0.0;
+    double out[6];
+    out[0] = K * t0;
 #pragma unroll
-    for (int q = 0; q < UBF; ++q) {
-        if (lane != q || bf0 + q >= g.unbf) continue;
-        const Soa<double> P = soa(d.P, (size_t)g.ncell, cell[q]);
-        const double rho = P[0], T = P[4];
-        const double piT = PI * T, K = rho / (piT * sqrt(piT));
-        const double h1 = g.species == 1 ? 0.5 * g.dr * P[5] : 0.0;
-        double out[6];
-        out[0] = K * s0[q];
+    for (int k = 0; k < 3; ++k) out[1 + k] = K * mine(s1[0][k], s1[1][k]);
+    if constexpr (G13) {
+        const double f1 = dia ? K * (h1 * t0 + mine(sr[0], sr[1])) : 0.0;
+        out[4] = K * t4 + f1;
+        out[5] = f1;
+    } else {
+        out[4] = K * t4 + h1 * out[0];
+        out[5] = h1 * out[0];
+    }
+    const double sc = C.bc.kind[slot] == 1 ? C.bc.rho[slot] : out[0] / (-bin[0]);
+    double Fe[6];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) out[1 + k] = K * s1[q][k];
-        if constexpr (G13) {
-            const double f1 = dia ? K * (h1 * s0[q] + sr[q]) : 0.0;
-            out[4] = K * s4[q] + f1;
-            out[5] = f1;
-        } else {
-            out[4] = K * s4[q] + h1 * out[0];
-            out[5] = h1 * out[0];
-        }
-        const int bf = bf0 + q;
-        const gptr<const double> bin = G((const double *)d.ubin) + 6 * (size_t)bf;
-        const double sc = C.bc.kind[slot[q]] == 1 ? C.bc.rho[slot[q]] : out[0] / (-bin[0]);
-        double Fe[6];
+    for (int k = 0; k < 6; ++k) Fe[k] = out[k] + sc * bin[k];
+    if (mode == 0) {
 #pragma unroll
-        for (int k = 0; k < 6; ++k) Fe[k] = out[k] + sc * bin[k];
-        const size_t ff = f[q];
-        if (mode == 0) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) G(d.ufix)[6 * ff + k] = G(d.uFk)[6 * ff + k] - Fe[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) G(d.uFf)[7 * ff + k] = G(d.ufix)[6 * ff + k] + Fe[k];
-            const double un = u[q][0] * n[q][0] + u[q][1] * n[q][1] + u[q][2] * n[q][2];
-            G(d.uFf)[7 * ff + 6] = fabs(un) + P[8] + (euler ? 0.0 : g.Cd * P[9] / (rho * G(d.uf_geo)[9 * ff + 4]));
-        }
+        for (int k = 0; k < 6; ++k) G(d.ufix)[6 * ff + k] = G(d.uFk)[6 * ff + k] - Fe[k];
+    } else {
+        const double un = P[1] * fg[1] + P[2] * fg[2] + P[3] * fg[3];
+        store_face(d, ff, Fe, fabs(un) + P[8] + (euler ? 0.0 : g.Cd * P[9] / (rho * fg[4])), fg[0]);
     }
 }
 
@@ -1754,11 +1794,13 @@ __global__ __launch_bounds__(256) void k_umac_res(GSIS_SPAN_ARGS, int slot, int 
         const int first = G(d.ucf_first)[cell], cnt = G(d.ucf_first)[cell + 1] - first;
         for (int k = 0; k < cnt; ++k) {
             const int fs = G(d.ucf_face)[first + k], f = fs >> 1;
-            const double sv = G(d.uf_geo)[9 * (size_t)f] * iV, sg = (fs & 1) ? -1.0 : 1.0;
-            const gptr<const double> o = G((const double *)d.uFf) + 7 * (size_t)f;
+            const gptr<const f64x2> r = (gptr<const f64x2>)d.uFf + 4 * (size_t)f;
+            const f64x2 r0 = r[0], r1 = r[1], r2 = r[2], r3 = r[3];
+            const double o[6] = {r0.x, r0.y, r1.x, r1.y, r2.x, r2.y};
+            const double sv = r3.y * iV, sg = (fs & 1) ? -1.0 : 1.0;
 #pragma unroll
             for (int q = 0; q < 6; ++q) res[q] -= sg * o[q] * sv;
-            sumG += o[6] * sv;
+            sumG += r3.x * sv;
         }
         if (g.species != 1) res[5] = 0.0;
         const double invtau = P[10];
@@ -1829,16 +1871,20 @@ hipError_t launch_umacro(const Target &t, int iters, hipStream_t s, int euler)
     const Geo &g = t.host->g;
     const Span sp{t.cases, nullptr};
     const dim3 cells((g.ncell + 255) / 256), faces((g.unface + 255) / 256);
-    const dim3 fwaves((g.unface + 3) / 4), bwaves(((std::max(g.unbf, 1) + UBF - 1) / UBF + 3) / 4);
-    const dim3 gwaves(((std::max(g.unbf, 1) + UBF_G13 - 1) / UBF_G13 + 3) / 4), bthreads((std::max(g.unbf, 1) + 255) / 256);
+    const dim3 fwaves((g.unface + 3) / 4), bwaves((g.ubgn + 3) / 4), bthreads((std::max(g.unbf, 1) + 255) / 256);
     // the Grad-13 wall flux: its stress and heat fluxes first, then its flux
     const bool g13 = t.g13 && !euler;
-    auto bflux = [&](int mode) {
+    // the boundary faces' fluxes, with grad the velocity gradients in the same
+    // launch (those of the Grad-13 stress are needed before it)
+    auto bflux = [&](int mode, bool grad) {
+        const dim3 gr(bwaves.x + (grad && !g13 ? cells.x : 0));
         if (g13) {
+            if (grad) hipLaunchKernelGGL(k_umac_grad, cells, dim3(256), 0, s, GSIS_SPAN(sp));
+            if (gr.x == 0) return;
             hipLaunchKernelGGL(k_umac_g13s, bthreads, dim3(256), 0, s, GSIS_SPAN(sp), mode);
-            hipLaunchKernelGGL((k_umac_bflux<UBF_G13, true>), gwaves, dim3(256), 0, s, GSIS_SPAN(sp), mode, euler);
-        } else {
-            hipLaunchKernelGGL((k_umac_bflux<UBF, false>), bwaves, dim3(256), 0, s, GSIS_SPAN(sp), mode, euler);
+            hipLaunchKernelGGL(k_umac_bflux<true>, gr, dim3(256), 0, s, GSIS_SPAN(sp), mode, euler);
+        } else if (gr.x > 0) {
+            hipLaunchKernelGGL(k_umac_bflux<false>, gr, dim3(256), 0, s, GSIS_SPAN(sp), mode, euler);
         }
     };
     hipLaunchKernelGGL(k_mac_reset, dim3(1), dim3(64), 0, s, GSIS_SPAN(sp));
@@ -1856,13 +1902,12 @@ hipError_t launch_umacro(const Target &t, int iters, hipStream_t s, int euler)
         hipLaunchKernelGGL(k_umac_nofix, dim3((6 * g.unface + 255) / 256), dim3(256), 0, s, GSIS_SPAN(sp));
     } else {
         hipLaunchKernelGGL(k_umac_iflux, faces, dim3(256), 0, s, GSIS_SPAN(sp), 0, 0);
-        if (g.unbf > 0) bflux(0);
+        if (g.unbf > 0) bflux(0, false);
     }
     for (int it = 0; it < iters; ++it) {
         const int slot = it & 1;
-        if (it > 0) hipLaunchKernelGGL(k_umac_grad, cells, dim3(256), 0, s, GSIS_SPAN(sp));
+        bflux(1, it > 0);
         hipLaunchKernelGGL(k_umac_iflux, faces, dim3(256), 0, s, GSIS_SPAN(sp), 1, euler);
-        if (g.unbf > 0) bflux(1);
         hipLaunchKernelGGL(k_umac_res, cells, dim3(256), 0, s, GSIS_SPAN(sp), slot, euler);
         hipLaunchKernelGGL(k_umac_advance, cells, dim3(256), 0, s, GSIS_SPAN(sp), slot);
     }
