@@ -281,7 +281,7 @@ gsis_status gsis_set_state(gsis_ctx *ctx, const void *src_device);
 
 /* Sweep tile (cells per tile along x, y, z in the octant's upwind frame) and
  * threads per block (64, 128 or 256); all zeros pick the built-in default for the
- * VDF precision.  Only compiled (tx, ty) are accepted (see gsis_tile_shapes). */
+ * VDF precision, the gas and the sizes.  Only compiled (tx, ty) are accepted (see gsis_tile_shapes). */
 gsis_status gsis_set_tile(gsis_ctx *ctx, int tx, int ty, int tz, int block);
 
 /* Current sweep configuration (tx, ty, tz, block) into tile[4]. */

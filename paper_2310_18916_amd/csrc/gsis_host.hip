@@ -32,6 +32,7 @@ struct gsis_ctx {
     std::vector<int> ucf_face, uf_cell, ucf_first, ubf_face;
     std::vector<int> ubg, ubgd, ubr, ubro;   // ubg, ubr: 2 ints per pair and run
     int tx = 0, ty = 0, tz = 0, bs = 0;
+    bool tile_auto = true;   // the built-in choice (until gsis_set_tile or the autotuner names one)
     std::vector<int> tiles, plane_off, plane_cnt, npblk;
     std::vector<int> tent, nclean;   // split sweep entries (cases with solid cells)
     int vw = 1;
@@ -83,11 +84,93 @@ template <class P> void carve(size_t &off, P *&ptr, size_t count, char *base)
     off += count * sizeof(P);
 }
 
+// The built-in sweep tile of one case, or of the average case of a batch.
+//
+// A launch runs one tile plane, so what decides is the waves a plane has, W =
+// tiles x nodes / 64 / planes (1024 SIMDs want several each).  Larger tiles
+// read fewer inflow values again; smaller ones make more and wider planes and
+// shorter chains.  Each line below stands where two neighbours measured equal
+// (sweep ms per pass, boxes of 8 to 96 cells by 12 to 40 nodes a side):
+//  FP64, one VDF: 4 x 4.  Depth 16 against 8: 10.12 and 10.37 at W16 = 8800
+//    (48^3 x 32^3), 3.25 and 3.18 at 4100 (32^3 x 32^3); 8 against 4: 4.75 and
+//    4.95 at W8 = 6700 (48^3 x 24^3), 0.79 and 0.73 at 1800; 4 against 2: 0.173
+//    and 0.162 at W4 = 410 (16^3 x 16^3), 0.344 and 0.377 at 860.  A box within
+//    8 cells a side is one 8 x 8 wave-grid tile: 0.045 against 0.068.
+//  FP64 with a per-point term (finite time step, second order): 8 x 4, whose
+//    terms are read a whole slab ahead: 9.5 against 11.0 (40^3 x 32^3), unless
+//    rounding x up to whole tiles costs more (41 cells: 4.28 against 4.18).
+//  FP64, two VDFs: 8 x 4 from W = 2400 on (16.4 against 17.3 on 64 x 48 x 48
+//    x 24^3; 1.52 against 1.39 on 32 x 24 x 24 x 18^3).
+//  FP32, one VDF: 8 x 4 from W = 4000 on (4.66 against 5.0 for 8 x 8 on 48^3 x
+//    32^3), 4 x 4 below (0.82 against 0.85 on 32^3 x 24^3).
+//  FP32, two VDFs: 4 x 4 (7.2 against 11.6 for 8 x 4 on 64 x 48 x 48 x 24^3).
+// Blocks of 256 threads: 10.1 against 10.6 with 128 on 48^3 x 32^3, as much or
+// more on smaller boxes.
+struct Tile { int tx, ty, tz, bs; };
+Tile tile_by_size(const gsis_ctx *const *cs, size_t nc)
+{
+    const gsis_ctx *c0 = cs[0];
+    const bool fp32 = c0->fp32, dia = c0->g.species == GSIS_DIATOMIC;
+    const bool term = c0->g.inv_dt != 0.0 || c0->g.order == 2;
+    auto up = [](int n, int t) { return (n + t - 1) / t; };
+    bool tiny = true;      // every box within 8 cells a side
+    double wide = 0, narrow = 0;
+    for (size_t k = 0; k < nc; ++k) {
+        const Geo &g = cs[k]->g;
+        tiny = tiny && g.nx <= 8 && g.ny <= 8 && g.nz <= 8;
+        wide += 8.0 * up(g.nx, 8);
+        narrow += 4.0 * up(g.nx, 4);
+    }
+    auto W = [&](int tx, int ty, int tz) {
+        double w = 0;
+        for (size_t k = 0; k < nc; ++k) {
+            const Geo &g = cs[k]->g;
+            const int a = up(g.nx, tx), b = up(g.ny, ty), c = up(g.nz, tz);
+            w += (double)a * b * c / (a + b + c - 2) * g.nv / 64.0;
+        }
+        return w / (double)nc;
+    };
+    const bool fits8 = wide <= 1.08 * narrow;
+    if (fp32) {
+        if (!dia && fits8 && W(8, 4, 4) >= 4000) {
+            const int tz = W(8, 4, 16) >= 5500 ? 16 : (W(8, 4, 8) >= 4000 ? 8 : 4);
+            return {8, 4, tz, 256};
+        }
+        if (dia) return {4, 4, W(4, 4, 8) >= 5000 ? 8 : (W(4, 4, 4) < 1500 ? 2 : 4), 256};
+        return {4, 4, W(4, 4, 4) < 1000 ? 2 : 4, 256};
+    }
+    if (dia) {
+        if (fits8 && !term && W(8, 4, 4) >= 2400) return {8, 4, W(8, 4, 8) >= 3000 ? 8 : 4, 256};
+        return {4, 4, W(4, 4, 8) >= 2500 ? 8 : (W(4, 4, 4) < 1000 ? 2 : 4), 256};
+    }
+    if (term && fits8)
+        return {8, 4, W(8, 4, 16) >= 4500 ? 16 : (W(8, 4, 8) >= 2500 ? 8 : (W(8, 4, 4) < 500 ? 2 : 4)), 256};
+    if (tiny && !term) return {8, 8, 8, 256};
+    return {4, 4, W(4, 4, 16) >= 8000 ? 16 : (W(4, 4, 8) >= 4000 ? 8 : (W(4, 4, 4) < 500 ? 2 : 4)), 256};
+}
+
+// ... and within the 1023 tiles per axis that a packed tile index holds.
+Tile pick_tile(const gsis_ctx *const *cs, size_t nc)
+{
+    Tile t = tile_by_size(cs, nc);
+    const bool dia = cs[0]->g.species == GSIS_DIATOMIC;
+    for (size_t k = 0; k < nc; ++k) {
+        const Geo &g = cs[k]->g;
+        while ((g.nz + t.tz - 1) / t.tz > 1023 && t.tz < 1024) t.tz *= 2;
+        if ((g.nx + t.tx - 1) / t.tx > 1023 || (g.ny + t.ty - 1) / t.ty > 1023) {
+            t.tx = 8;
+            t.ty = cs[0]->fp32 && !dia ? 8 : 4;
+            t.bs = 256;
+        }
+    }
+    return t;
+}
+
 void default_tile(gsis_ctx *c)
 {
-    bool dia = c->g.species == GSIS_DIATOMIC;
-    if (c->fp32) { c->tx = 8; c->ty = dia ? 4 : 8; c->tz = 8; c->bs = 128; }
-    else { c->tx = 4; c->ty = 4; c->tz = 4; c->bs = 128; }
+    const Tile t = pick_tile(&c, 1);
+    c->tile_auto = true;
+    c->tx = t.tx; c->ty = t.ty; c->tz = t.tz; c->bs = t.bs;
 }
 
 int sweep_nvb(const Geo &g, int bs)
@@ -207,6 +290,7 @@ void build_meta(gsis_ctx *c)
         c->meta_ready = true;
         return;
     }
+    if (c->tile_auto) default_tile(c);   // the velocity set is final now
     if (c->mask.empty()) c->mask.assign(n, 0);
     c->cflag.assign(n, 0);
     c->nbr.assign((size_t)n * 6, 0);
@@ -1533,6 +1617,7 @@ gsis_status gsis_set_tile(gsis_ctx *ctx, int tx, int ty, int tz, int block)
         int ntx = (ctx->g.nx + tx - 1) / tx, nty = (ctx->g.ny + ty - 1) / ty, ntz = (ctx->g.nz + tz - 1) / tz;
         if (ntx > 1023 || nty > 1023 || ntz > 1023) return fail(ctx, GSIS_EINVAL, "too many tiles per axis");
         ctx->tx = tx; ctx->ty = ty; ctx->tz = tz; ctx->bs = block;
+        ctx->tile_auto = false;
     }
     if (ctx->meta_ready) build_tiles(ctx);
     if (ctx->bound) HIPCHK(ctx, upload_tiles(ctx));
@@ -1597,6 +1682,7 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
     size_t best = 0;
     for (size_t k = 1; k < cands.size(); ++k)
         if (cands[k].ms < cands[best].ms) best = k;
+    ctx->tile_auto = false;
     ctx->tx = cands[best].tx; ctx->ty = cands[best].ty; ctx->tz = cands[best].tz; ctx->bs = cands[best].bs;
     build_tiles(ctx);
     HIPCHK(ctx, upload_tiles(ctx));
@@ -1622,6 +1708,11 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
 gsis_status gsis_get_tile(const gsis_ctx *ctx, int *tile)
 {
     if (!ctx || !tile) return GSIS_EINVAL;
+    if (ctx->tile_auto && !ctx->meta_ready) {   // the choice for the sizes set so far
+        const Tile t = pick_tile(&ctx, 1);
+        tile[0] = t.tx; tile[1] = t.ty; tile[2] = t.tz; tile[3] = t.bs;
+        return GSIS_OK;
+    }
     tile[0] = ctx->tx; tile[1] = ctx->ty; tile[2] = ctx->tz; tile[3] = ctx->bs;
     return GSIS_OK;
 }
@@ -1885,6 +1976,10 @@ hipError_t batch_build_maps(gsis_batch *b)
 // One tile shape on every case, then the tables that depend on it.
 gsis_status batch_apply_tile(gsis_batch *b, int tx, int ty, int tz, int bs)
 {
+    if (tx == 0 && ty == 0 && tz == 0 && bs == 0) {
+        const Tile t = pick_tile(b->cs.data(), b->cs.size());
+        tx = t.tx; ty = t.ty; tz = t.tz; bs = t.bs;
+    }
     for (gsis_ctx *c : b->cs) {
         gsis_status st = gsis_set_tile(c, tx, ty, tz, bs);
         if (st) return bfail(b, st, std::string("tile: ") + c->err);
