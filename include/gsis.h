@@ -290,7 +290,8 @@ gsis_status gsis_get_tile(const gsis_ctx *ctx, int *tile);
 /* Autotuner: performs the next kinetic pass, running its sweep reps >= 1 times
  * under every compiled (tx, ty) tile shape, tile depths tz in {tx/2, tx, 2 tx}
  * and blocks of 128 and 256 threads, timed with HIP events; selects the
- * fastest configuration for the context.  Valid because every configuration
+ * configuration with the fastest sweep and moment sums (which some
+ * configurations form in the sweep) for the context.  Valid because every configuration
  * gives a bitwise-identical sweep; requires source iteration (inv_dt = 0)
  * and order 1, where the sweep does not read f^n (an order-2 context takes
  * the tile found for its first-order twin through gsis_set_tile).  Writes up to max entries of

@@ -38,6 +38,7 @@ struct Geo {
     int on[8][3];
     int osize[8];
     int obase[8];
+    int oseg[9];   // first segment of the moment sums of octant o; oseg[8] all of them
     int species;
     double delta, idelta, omega, dr, Zr, A[4];   // idelta = 1 / delta
     double inv_dt;
@@ -93,6 +94,9 @@ struct Dev {
     void *ho0, *ho1;   // order 2: inv_dt f^n - (second-order - first-order flux divergence), [ncell + 1][nv]
     void *lim0, *lim1; // order 2: Venkatakrishnan limiter per point, [ncell][nv]
     double *mom8;      // [ncell][8][NRS]
+    // segments of the octant sums formed by the sweep, [oseg[8]][ncell][16] of f0 and
+    // [..][..][4] of f1 (null: the sums are taken from the stored VDF)
+    double *mseg, *mseg1;
     double *cm;        // [ncell][NMOM]
     double *par;       // [ncell][NPAR]
     float *parf;       // [ncell][NPAR]
@@ -109,9 +113,6 @@ struct Dev {
     double *xi64[3];   // per-axis nodes (tensor grid)
     float *xi32[3];
     double *w64[3];    // per-axis trapezoid weights
-    double *xtab;      // [n1x][4]: w, w xi, w xi^2, w xi^3 along x
-    double *ytab;      // [n1y][2]: w, xi
-    double *ztab;      // [n1z][2]
     double *mb64, *mb1_64;   // [NBC][nv] boundary Maxwellian M(1,u_b,T_b), and (dr/2) T_b times it
     float *mb32, *mb1_32;
     double *inpsi;     // [NBC][6][6] incoming half-range psi-moments of M(1,u_b,T_b)
@@ -400,5 +401,31 @@ __device__ __forceinline__ double maxwell64(double rho, const double *u, double 
     double cx = x - u[0], cy = y - u[1], cz = z - u[2];
     return rho * pow(PI * T, -1.5) * exp(-(cx * cx + cy * cy + cz * cz) / T);
 }
+
+// Octant sums as a matrix product over the nodes (k_moments, k_sweep): chunks of
+// MCHUNK nodes, segments of MSEG.
+constexpr int MCHUNK = 64, MSEG = 4 * MCHUNK;
+constexpr int MOM_GROUPS = 2;   // groups of 16 cells a block of k_moments takes
+
+// Monomial i of a node times its weight: 1, x, y, z, xx, yy, zz, xy, xz, yz,
+// x|xi|^2, y|xi|^2, z|xi|^2, and zero from 13 on.  As (w a) b with a of 1, x, y,
+// z and b of 1, x, y, z, |xi|^2, picked by 0/1 coefficients, so that lanes with
+// different i run the same instructions.
+struct Monomial {
+    double a1, ax, ay, az, b1, bx, by, bz, br;
+    __device__ __forceinline__ explicit Monomial(int i)
+    {
+        auto pick = [&](unsigned m) { return (m >> i) & 1 ? 1.0 : 0.0; };
+        a1 = pick(0x0001); ax = pick(0x0592); ay = pick(0x0a24); az = pick(0x1048);
+        b1 = pick(0x000f); bx = pick(0x0010); by = pick(0x00a0); bz = pick(0x0340); br = pick(0x1c00);
+    }
+    __device__ __forceinline__ double operator()(double x, double y, double z, double w) const
+    {
+        const double r2 = fma(z, z, fma(y, y, x * x));
+        const double a = fma(az, z, fma(ay, y, fma(ax, x, a1)));
+        const double b = fma(br, r2, fma(bz, z, fma(by, y, fma(bx, x, b1))));
+        return (w * a) * b;
+    }
+};
 
 }  // namespace gsis

@@ -32,10 +32,10 @@ struct gsis_ctx {
     std::vector<int> ucf_face, uf_cell, ucf_first, ubf_face;
     std::vector<int> ubg, ubgd, ubr, ubro;   // ubg, ubr: 2 ints per pair and run
     int tx = 0, ty = 0, tz = 0, bs = 0;
+    bool segments = false;   // the workspace holds the segments of the moment sums
     bool tile_auto = true;   // the built-in choice (until gsis_set_tile or the autotuner names one)
     std::vector<int> tiles, plane_off, plane_cnt, npblk;
     std::vector<int> tent, nclean;   // split sweep entries (cases with solid cells)
-    int vw = 1;
     Dev d;
     Case hcase;              // host copy of the device-resident case record
     Case *dcase = nullptr;   // in the workspace
@@ -84,26 +84,51 @@ template <class P> void carve(size_t &off, P *&ptr, size_t count, char *base)
     off += count * sizeof(P);
 }
 
+double vdf_bytes(const gsis_ctx *c)
+{
+    return (double)c->g.ncell * c->g.nv * (c->fp32 ? 4 : 8) * (c->g.species == GSIS_DIATOMIC ? 2 : 1);
+}
+
+// Whether the sweep forms the moment sums of these cases (on boxes): where
+// reading the VDF again costs more than the products in the sweep, that is once
+// it no longer fits the 256 MB of memory-side cache.  Sweep + moments, formed and
+// not: 0.24 and 0.21 ms on 16^3 cells x 16^3 nodes FP64 (134 MB), 0.69 and 0.75 on
+// 24^3 x 20^3 (0.9 GB), 4.2 and 4.6 on 32^3 x 32^3, 34.7 and 37.6 on 64 x 48 x 48
+// x 40^3; FP32 0.20 and 0.17, 0.48 and 0.50, 2.3 and 2.65; with
+// a finite time step, FP64, 0.90 and 1.06 on 24^3 x 20^3.  The segments take 6% of
+// an FP64 VDF, 12% of an FP32 one; not where that would leave no room on a 288 GB
+// card.
+bool forms_sums(const gsis_ctx *const *cs, size_t nc)
+{
+    const Geo &g0 = cs[0]->g;
+    double bytes = 0, all = 0;
+    for (size_t k = 0; k < nc; ++k) {
+        const Geo &g = cs[k]->g;
+        double seg = 0;
+        for (int o = 0; o < 8; ++o) seg += (g.osize[o] + MSEG - 1) / MSEG;
+        bytes += vdf_bytes(cs[k]);
+        all += vdf_bytes(cs[k]) * (g.order == 2 ? 3 : 1) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
+    }
+    return !g0.umesh && all <= 240e9 && bytes > 256e6;
+}
+
 // The built-in sweep tile of one case, or of the average case of a batch.
 //
 // A launch runs one tile plane, so what decides is the waves a plane has, W =
 // tiles x nodes / 64 / planes (1024 SIMDs want several each).  Larger tiles
 // read fewer inflow values again; smaller ones make more and wider planes and
-// shorter chains.  Each line below stands where two neighbours measured equal
-// (sweep ms per pass, boxes of 8 to 96 cells by 12 to 40 nodes a side):
-//  FP64, one VDF: 4 x 4.  Depth 16 against 8: 10.12 and 10.37 at W16 = 8800
-//    (48^3 x 32^3), 3.25 and 3.18 at 4100 (32^3 x 32^3); 8 against 4: 4.75 and
-//    4.95 at W8 = 6700 (48^3 x 24^3), 0.79 and 0.73 at 1800; 4 against 2: 0.173
-//    and 0.162 at W4 = 410 (16^3 x 16^3), 0.344 and 0.377 at 860.  A box within
-//    8 cells a side is one 8 x 8 wave-grid tile: 0.045 against 0.068.
-//  FP64 with a per-point term (finite time step, second order): 8 x 4, whose
-//    terms are read a whole slab ahead: 9.5 against 11.0 (40^3 x 32^3), unless
-//    rounding x up to whole tiles costs more (41 cells: 4.28 against 4.18).
-//  FP64, two VDFs: 8 x 4 from W = 2400 on (16.4 against 17.3 on 64 x 48 x 48
-//    x 24^3; 1.52 against 1.39 on 32 x 24 x 24 x 18^3).
-//  FP32, one VDF: 8 x 4 from W = 4000 on (4.66 against 5.0 for 8 x 8 on 48^3 x
-//    32^3), 4 x 4 below (0.82 against 0.85 on 32^3 x 24^3).
-//  FP32, two VDFs: 4 x 4 (7.2 against 11.6 for 8 x 4 on 64 x 48 x 48 x 24^3).
+// shorter chains.  Each line stands where two neighbours measured equal (ms per
+// pass, sweep and moments, boxes of 8 to 96 cells by 12 to 40 nodes a side):
+//  4 x 4 with the moment sums.  Depth 16 against 8: 6.42 and 6.55 at W16 = 3700
+//    (48^3 x 24^3, FP64), 2.13 and 2.05 at 1000 (32^3 x 24^3); 8 against 4: 0.69
+//    and 0.73 at W8 = 1000 (24^3 x 20^3), 0.34 and 0.26 at 230 (16^3 x 16^3).
+//    FP32 and the per-point term turn at the same sizes.
+//  Two VDFs, FP64: 8 x 4 from W = 2400 on (20.1 against 20.6 on 64 x 48 x 48 x
+//    24^3; 3.19 and 3.18 at 2200).  FP32: 4 x 4 (10.4 against 15.4).
+//  Without the sums (small boxes): depth 4 against 2: 0.222 and 0.211 at W4 = 410
+//    (16^3 x 16^3, FP64); a box within 8 cells a side is one 8 x 8 wave-grid
+//    tile: 0.074 against 0.093.  With a per-point term, FP64: 8 x 4, whose terms
+//    are read a whole slab ahead (0.32 against 0.34 on 16^3 x 16^3).
 // Blocks of 256 threads: 10.1 against 10.6 with 128 on 48^3 x 32^3, as much or
 // more on smaller boxes.
 struct Tile { int tx, ty, tz, bs; };
@@ -111,7 +136,7 @@ Tile tile_by_size(const gsis_ctx *const *cs, size_t nc)
 {
     const gsis_ctx *c0 = cs[0];
     const bool fp32 = c0->fp32, dia = c0->g.species == GSIS_DIATOMIC;
-    const bool term = c0->g.inv_dt != 0.0 || c0->g.order == 2;
+    const bool sums = forms_sums(cs, nc), term = c0->g.inv_dt != 0.0 || c0->g.order == 2;
     auto up = [](int n, int t) { return (n + t - 1) / t; };
     bool tiny = true;      // every box within 8 cells a side
     double wide = 0, narrow = 0;
@@ -130,23 +155,15 @@ Tile tile_by_size(const gsis_ctx *const *cs, size_t nc)
         }
         return w / (double)nc;
     };
-    const bool fits8 = wide <= 1.08 * narrow;
-    if (fp32) {
-        if (!dia && fits8 && W(8, 4, 4) >= 4000) {
-            const int tz = W(8, 4, 16) >= 5500 ? 16 : (W(8, 4, 8) >= 4000 ? 8 : 4);
-            return {8, 4, tz, 256};
-        }
-        if (dia) return {4, 4, W(4, 4, 8) >= 5000 ? 8 : (W(4, 4, 4) < 1500 ? 2 : 4), 256};
-        return {4, 4, W(4, 4, 4) < 1000 ? 2 : 4, 256};
-    }
     if (dia) {
-        if (fits8 && !term && W(8, 4, 4) >= 2400) return {8, 4, W(8, 4, 8) >= 3000 ? 8 : 4, 256};
-        return {4, 4, W(4, 4, 8) >= 2500 ? 8 : (W(4, 4, 4) < 1000 ? 2 : 4), 256};
+        // 8 wide unless whole tiles make x more than 8% longer
+        if (!fp32 && !term && wide <= 1.08 * narrow && W(8, 4, 4) >= 2400) return {8, 4, W(8, 4, 8) >= 3000 ? 8 : 4, 256};
+        return {4, 4, W(4, 4, 8) >= (fp32 ? 5000 : 2500) ? 8 : (W(4, 4, 4) < (fp32 ? 1500 : 1000) ? 2 : 4), 256};
     }
-    if (term && fits8)
-        return {8, 4, W(8, 4, 16) >= 4500 ? 16 : (W(8, 4, 8) >= 2500 ? 8 : (W(8, 4, 4) < 500 ? 2 : 4)), 256};
-    if (tiny && !term) return {8, 8, 8, 256};
-    return {4, 4, W(4, 4, 16) >= 8000 ? 16 : (W(4, 4, 8) >= 4000 ? 8 : (W(4, 4, 4) < 500 ? 2 : 4)), 256};
+    if (sums) return {4, 4, W(4, 4, 16) >= 3500 ? 16 : (W(4, 4, 8) >= 900 ? 8 : (W(4, 4, 4) < 500 ? 2 : 4)), 256};
+    if (!fp32 && term && wide <= 1.08 * narrow) return {8, 4, W(8, 4, 4) < 500 ? 2 : 4, 256};
+    if (!fp32 && tiny) return {8, 8, 8, 256};
+    return {4, 4, W(4, 4, 4) < (fp32 ? 1000 : 500) ? 2 : 4, 256};
 }
 
 // ... and within the 1023 tiles per axis that a packed tile index holds.
@@ -284,13 +301,15 @@ void build_meta(gsis_ctx *c)
         g.nface = 0;
         g.nfluid = n;
         c->perm = c->uperm;
-        c->vw = 1;
         c->tiles.clear(); c->plane_off.clear(); c->plane_cnt.clear(); c->npblk.clear();
         c->tent.clear(); c->nclean.clear();
         c->meta_ready = true;
         return;
     }
-    if (c->tile_auto) default_tile(c);   // the velocity set is final now
+    g.oseg[0] = 0;
+    for (int o = 0; o < 8; ++o) g.oseg[o + 1] = g.oseg[o] + (g.osize[o] + MSEG - 1) / MSEG;
+    c->segments = forms_sums(&c, 1);   // the velocity set is final now
+    if (c->tile_auto) default_tile(c);
     if (c->mask.empty()) c->mask.assign(n, 0);
     c->cflag.assign(n, 0);
     c->nbr.assign((size_t)n * 6, 0);
@@ -339,15 +358,6 @@ void build_meta(gsis_ctx *c)
             int kz = ((o & 4) ? 0 : g.k0[2]) + lz;
             c->perm[g.obase[o] + l] = kx + g.n1[0] * (ky + g.n1[1] * kz);
         }
-    int vw = g.vlist ? 1 : (c->fp32 ? 4 : 2);
-    while (vw > 1) {
-        bool ok = true;
-        for (int o = 0; o < 8; ++o)
-            if (g.osize[o] > 0 && g.on[o][0] % vw) ok = false;
-        if (ok) break;
-        vw >>= 1;
-    }
-    c->vw = vw;
     build_tiles(c);
     c->meta_ready = true;
 }
@@ -379,6 +389,11 @@ size_t layout(gsis_ctx *c, char *base)
         d.rs0 = h0; d.rs1 = h1;
     }
     carve(off, d.mom8, n * 8 * NRS, base);
+    d.mseg = d.mseg1 = nullptr;
+    if (c->segments) {
+        carve(off, d.mseg, n * g.oseg[8] * 16, base);
+        if (g.species == 1) carve(off, d.mseg1, n * g.oseg[8] * 4, base);
+    }
     carve(off, d.cm, n * NMOM, base);
     carve(off, d.par, n * NPAR, base);
     carve(off, d.parf, n * NPAR, base);
@@ -400,9 +415,6 @@ size_t layout(gsis_ctx *c, char *base)
         carve(off, d.xi32[a], (size_t)g.n1[a], base);
         carve(off, d.w64[a], (size_t)g.n1[a], base);
     }
-    carve(off, d.xtab, (size_t)g.n1[0] * 4, base);
-    carve(off, d.ytab, (size_t)g.n1[1] * 2, base);
-    carve(off, d.ztab, (size_t)g.n1[2] * 2, base);
     carve(off, d.mb64, (size_t)NBC * nv, base);
     carve(off, d.mb1_64, (size_t)NBC * nv, base);
     carve(off, d.mb32, (size_t)NBC * nv, base);
@@ -477,7 +489,6 @@ size_t layout(gsis_ctx *c, char *base)
     return align256(off);
 }
 
-int vw_class(int vw) { return vw >= 4 ? 2 : (vw == 2 ? 1 : 0); }
 
 // The launch target of this context alone.
 Target target_of(const gsis_ctx *c)
@@ -493,8 +504,8 @@ Target target_of(const gsis_ctx *c)
     t.dia = c->g.species == GSIS_DIATOMIC;
     t.mask = c->g.nfluid != c->g.ncell;
     t.rfn = c->g.inv_dt != 0.0 || c->g.order == 2;
-    t.mom_nblk[vw_class(c->vw)] = c->g.ncell;
     t.vlist = c->g.vlist != 0;
+    t.mseg = c->segments;
     t.g13 = c->g.wall_flux == GSIS_WALLFLUX_G13;
     if (!c->nclean.empty()) {
         t.nclean = c->nclean.data();
@@ -533,11 +544,12 @@ gsis_status reset_flags(gsis_ctx *c)
     return GSIS_OK;
 }
 
-// moments of the stored VDF (octant sums, then central moments)
-gsis_status reduce_vdf(gsis_ctx *c)
+// moments of the stored VDF (octant sums, then central moments); swept: it is
+// what the last launch_sweep left
+gsis_status reduce_vdf(gsis_ctx *c, bool swept)
 {
     const Target t = target_of(c);
-    HIPCHK(c, launch_moments(t, c->stream));
+    HIPCHK(c, launch_moments(t, c->stream, swept));
     HIPCHK(c, launch_derive(t, c->stream));
     return GSIS_OK;
 }
@@ -1249,22 +1261,12 @@ gsis_status gsis_bind_workspace(gsis_ctx *ctx, void *device_ptr, size_t bytes)
     }
     if (!g.vlist) {
         // per-axis tables of the separable kernels (tensor grid)
-        std::vector<double> xt((size_t)g.n1[0] * 4), yt((size_t)g.n1[1] * 2), zt((size_t)g.n1[2] * 2);
         for (int a = 0; a < 3; ++a) {
             std::vector<float> x32(ctx->xi[a].begin(), ctx->xi[a].end());
             HIPCHK(ctx, up(d.xi64[a], ctx->xi[a].data(), g.n1[a] * sizeof(double)));
             HIPCHK(ctx, up(d.xi32[a], x32.data(), g.n1[a] * sizeof(float)));
             HIPCHK(ctx, up(d.w64[a], ctx->w[a].data(), g.n1[a] * sizeof(double)));
         }
-        for (int k = 0; k < g.n1[0]; ++k) {
-            double x = ctx->xi[0][k], w = ctx->w[0][k];
-            xt[4 * k] = w; xt[4 * k + 1] = w * x; xt[4 * k + 2] = w * x * x; xt[4 * k + 3] = w * x * x * x;
-        }
-        for (int k = 0; k < g.n1[1]; ++k) { yt[2 * k] = ctx->w[1][k]; yt[2 * k + 1] = ctx->xi[1][k]; }
-        for (int k = 0; k < g.n1[2]; ++k) { zt[2 * k] = ctx->w[2][k]; zt[2 * k + 1] = ctx->xi[2][k]; }
-        HIPCHK(ctx, up(d.xtab, xt.data(), xt.size() * sizeof(double)));
-        HIPCHK(ctx, up(d.ytab, yt.data(), yt.size() * sizeof(double)));
-        HIPCHK(ctx, up(d.ztab, zt.data(), zt.size() * sizeof(double)));
     }
     {
         // every node in the internal order: (xi_x, xi_y, xi_z, weight)
@@ -1344,7 +1346,7 @@ gsis_status gsis_init_maxwellian(gsis_ctx *ctx, double rho, const double u[3], d
     gsis_status st = reset_flags(ctx);
     if (st) return st;
     HIPCHK(ctx, launch_init_maxwellian(ctx->g, ctx->d, ctx->fp32, rho, u, T, Tr, ctx->stream));
-    if ((st = reduce_vdf(ctx))) return st;
+    if ((st = reduce_vdf(ctx, false))) return st;
     HIPCHK(ctx, launch_snapshot(target_of(ctx), ctx->stream));
     ctx->pending = false;
     ctx->inited = true;
@@ -1377,7 +1379,7 @@ gsis_status gsis_kinetic_step(gsis_ctx *ctx, int npasses)
             HIPCHK(ctx, t1.stop());
             ctx->pending = false;   // every point was rewritten
             HIPCHK(ctx, t2.start(ctx, GSIS_PHASE_MOMENTS));
-            gsis_status st = reduce_vdf(ctx);
+            gsis_status st = reduce_vdf(ctx, true);
             if (st) return st;
             HIPCHK(ctx, t2.stop());
             ctx->passes++;
@@ -1398,7 +1400,7 @@ gsis_status gsis_kinetic_step(gsis_ctx *ctx, int npasses)
         HIPCHK(ctx, t1.stop());
         ctx->pending = false;   // every fluid point was rewritten
         HIPCHK(ctx, t2.start(ctx, GSIS_PHASE_MOMENTS));
-        gsis_status st = reduce_vdf(ctx);
+        gsis_status st = reduce_vdf(ctx, true);
         if (st) return st;
         HIPCHK(ctx, t2.stop());
         ctx->passes++;
@@ -1513,7 +1515,7 @@ gsis_status gsis_set_vdf(gsis_ctx *ctx, const double *f0_device, const double *f
     HIPCHK(ctx, launch_from_canonical(ctx->g, ctx->d, ctx->fp32, f0_device, ctx->d.f0, ctx->stream));
     if (ctx->g.species == GSIS_DIATOMIC)
         HIPCHK(ctx, launch_from_canonical(ctx->g, ctx->d, ctx->fp32, f1_device, ctx->d.f1, ctx->stream));
-    if ((st = reduce_vdf(ctx))) return st;
+    if ((st = reduce_vdf(ctx, false))) return st;
     HIPCHK(ctx, launch_snapshot(target_of(ctx), ctx->stream));
     ctx->pending = false;
     ctx->inited = true;
@@ -1636,8 +1638,9 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
     bool dia = g.species == GSIS_DIATOMIC;
     int shapes[32];
     int nsh = sweep_shapes(ctx->fp32, shapes, 16);
-    struct Cand { int tx, ty, tz, bs; double ms; };
+    struct Cand { int tx, ty, tz, bs; double ms, rank = 0.0; };
     std::vector<Cand> cands;
+    float moms[2] = {-1.0f, -1.0f};
     for (int k = 0; k < nsh; ++k) {
         int tx = shapes[2 * k], ty = shapes[2 * k + 1];
         if (!sweep_shape_supported(ctx->fp32, dia, tx, ty)) continue;
@@ -1668,8 +1671,18 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        // ranked with the moment sums, timed once formed in the sweep and once not
+        float &mom = moms[sweep_forms_sums(tc)];
+        if (mom < 0.0f) {
+            if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
+            if (e == hipSuccess) e = launch_moments(tc, ctx->stream, true);
+            if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            if (e == hipSuccess) e = hipEventElapsedTime(&mom, e0, e1);
+        }
         if (e != hipSuccess) { st = fail(ctx, GSIS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e)); break; }
         c.ms = ms / reps;
+        c.rank = c.ms + mom;
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
@@ -1681,14 +1694,14 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
     }
     size_t best = 0;
     for (size_t k = 1; k < cands.size(); ++k)
-        if (cands[k].ms < cands[best].ms) best = k;
+        if (cands[k].rank < cands[best].rank) best = k;
     ctx->tile_auto = false;
     ctx->tx = cands[best].tx; ctx->ty = cands[best].ty; ctx->tz = cands[best].tz; ctx->bs = cands[best].bs;
     build_tiles(ctx);
     HIPCHK(ctx, upload_tiles(ctx));
     // the VDF now holds this pass's sweep result (identical under every configuration)
     ctx->pending = false;
-    st = reduce_vdf(ctx);
+    st = reduce_vdf(ctx, false);
     if (st) return st;
     ctx->passes++;
     ctx->stepped = true;
@@ -1857,7 +1870,6 @@ size_t batch_map_cap(const gsis_batch *b)
     size_t n = 0;
     for (const gsis_ctx *c : b->cs) {
         for (int k = 0; k < NKIND; ++k) n += (size_t)kind_blocks(c->g, (Kind)k);
-        n += (size_t)c->g.ncell;   // moment map of its vector-width class
         size_t tiles = (size_t)((c->g.nx + 3) / 4) * ((c->g.ny + 3) / 4) * c->g.nz;
         n += tiles * 8 * (size_t)sweep_nvb(c->g, 64);
     }
@@ -1921,16 +1933,6 @@ hipError_t batch_build_maps(gsis_batch *b)
         }
         t.nblk[k] = (int)(m.size() - koff[k]);
     }
-    size_t moff[3];
-    int mcnt[3];
-    for (int w = 0; w < 3; ++w) {
-        moff[w] = m.size();
-        for (int c = 0; c < nc; ++c) {
-            if (vw_class(b->cs[c]->vw) != w) continue;
-            for (int j = 0; j < b->cs[c]->g.ncell; ++j) m.push_back(make_int2(c, j));
-        }
-        mcnt[w] = (int)(m.size() - moff[w]);
-    }
     int nplane = 0;
     for (const gsis_ctx *c : b->cs) nplane = std::max(nplane, (int)c->plane_cnt.size());
     std::vector<size_t> poff(nplane);
@@ -1947,10 +1949,6 @@ hipError_t batch_build_maps(gsis_batch *b)
     }
     if (m.size() > b->map_cap) return hipErrorInvalidValue;
     for (int k = 0; k < NKIND; ++k) t.map[k] = b->dmap + koff[k];
-    for (int w = 0; w < 3; ++w) {
-        t.mom_map[w] = b->dmap + moff[w];
-        t.mom_nblk[w] = mcnt[w];
-    }
     b->pmap.assign(nplane, nullptr);
     for (int p = 0; p < nplane; ++p) b->pmap[p] = b->dmap + poff[p];
     t.cases = b->dcases;
@@ -1965,6 +1963,7 @@ hipError_t batch_build_maps(gsis_batch *b)
     for (const gsis_ctx *c : b->cs) t.mask = t.mask || c->g.nfluid != c->g.ncell;
     for (const gsis_ctx *c : b->cs) t.g13 = t.g13 || c->g.wall_flux == GSIS_WALLFLUX_G13;
     t.rfn = false;
+    t.mseg = b->cs[0]->segments;
     t.tx = b->tx;
     t.ty = b->ty;
     t.bs = b->bs;
@@ -2002,7 +2001,7 @@ hipError_t batch_enqueue_iteration(gsis_batch *b, int inner)
     hipError_t e = launch_params(t, s);
     if (e == hipSuccess) e = launch_face_scale(t, s);
     if (e == hipSuccess) e = launch_sweep(t, s);
-    if (e == hipSuccess) e = launch_moments(t, s);
+    if (e == hipSuccess) e = launch_moments(t, s, true);
     if (e == hipSuccess) e = launch_derive(t, s);
     if (inner > 0) {
         if (e == hipSuccess) e = launch_gsis_macro(t, inner, s);
@@ -2049,6 +2048,8 @@ gsis_status gsis_batch_create(gsis_batch **out, gsis_ctx *const *cases, int ncas
     }
     for (gsis_ctx *c : b->cs)
         if (!c->meta_ready) build_meta(c);
+    const bool sums = forms_sums(b->cs.data(), b->cs.size());
+    for (gsis_ctx *c : b->cs) c->segments = sums;
     b->map_cap = batch_map_cap(b);
     *out = b;
     return GSIS_OK;
@@ -2145,8 +2146,9 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
     const gsis_ctx *c0 = b->cs[0];
     int shapes[32];
     int nsh = sweep_shapes(b->fp32, shapes, 16);
-    struct Cand { int tx, ty, tz, bs; double ms; };
+    struct Cand { int tx, ty, tz, bs; double ms, rank = 0.0; };
     std::vector<Cand> cands;
+    float moms[2] = {-1.0f, -1.0f};
     for (int k = 0; k < nsh; ++k) {
         int tx = shapes[2 * k], ty = shapes[2 * k + 1];
         if (!sweep_shape_supported(b->fp32, b->dia, tx, ty)) continue;
@@ -2173,8 +2175,18 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        // ranked with the moment sums, timed once formed in the sweep and once not
+        float &mom = moms[sweep_forms_sums(b->t)];
+        if (mom < 0.0f) {
+            if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
+            if (e == hipSuccess) e = launch_moments(b->t, b->stream, true);
+            if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            if (e == hipSuccess) e = hipEventElapsedTime(&mom, e0, e1);
+        }
         if (e != hipSuccess) { st = bfail(b, GSIS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e)); break; }
         c.ms = ms / reps;
+        c.rank = c.ms + mom;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -2184,11 +2196,11 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
     }
     size_t best = 0;
     for (size_t k = 1; k < cands.size(); ++k)
-        if (cands[k].ms < cands[best].ms) best = k;
+        if (cands[k].rank < cands[best].rank) best = k;
     st = batch_apply_tile(b, cands[best].tx, cands[best].ty, cands[best].tz, cands[best].bs);
     if (st) return st;
     // every case now holds this pass's sweep result (identical under every configuration)
-    BHIPCHK(b, launch_moments(b->t, b->stream));
+    BHIPCHK(b, launch_moments(b->t, b->stream, false));
     BHIPCHK(b, launch_derive(b->t, b->stream));
     for (gsis_ctx *c : b->cs) {
         c->pending = false;

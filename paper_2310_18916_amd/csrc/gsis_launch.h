@@ -6,7 +6,7 @@ namespace gsis {
 
 // Grid shapes of the kernels of a GSIS iteration; a launch over several cases
 // concatenates the blocks each case needs (kind_blocks) through a block map.
-enum Kind { K_CELL64, K_CELL128, K_CELL256, K_CELL1, K_FACE256, K_FACE8, K_GRAD, K_MTILE, K_CASE, NKIND };
+enum Kind { K_CELL64, K_CELL128, K_CELL256, K_CELL1, K_FACE256, K_FACE8, K_GRAD, K_MTILE, K_MOM, K_MSUM, K_CASE, NKIND };
 int kind_blocks(const Geo &g, Kind k);
 
 // What a launch covers: one case (maps null) or a batch of cases that share
@@ -29,9 +29,7 @@ struct Target {
     bool fp32 = false, dia = false, mask = false, rfn = false;
     bool vlist = false;               // the node-list kernels (a refined or unstructured velocity mesh)
     bool g13 = false;                 // some case takes the Grad-13 wall flux in its correction
-    // the moment kernel runs once per vector width (1, 2, 4) over the cases of that width
-    const int2 *mom_map[3] = {};
-    int mom_nblk[3] = {};
+    bool mseg = false;                // every case holds the segments of the moment sums
     int tx = 4, ty = 4, bs = 128;     // sweep tile shape and block size
     Span span(Kind k) const { return Span{cases, map[k]}; }
 };
@@ -46,7 +44,8 @@ hipError_t launch_apply_correction(const Geo &g, const Dev &d, bool fp32, hipStr
 // order 2: limiter, then inv_dt f^n - (D2 - D1) into d.ho0/ho1, from the stored f^n
 hipError_t launch_recon(const Geo &g, const Dev &d, bool fp32, hipStream_t s);
 
-hipError_t launch_moments(const Target &t, hipStream_t s);
+// swept: the VDF is the result of the last launch_sweep of this target
+hipError_t launch_moments(const Target &t, hipStream_t s, bool swept);
 hipError_t launch_derive(const Target &t, hipStream_t s);
 hipError_t launch_commit_correction(const Target &t, hipStream_t s);
 
@@ -58,6 +57,8 @@ bool sweep_shape_supported(bool fp32, bool dia, int tx, int ty);
 int sweep_shape_waves(bool fp32, int tx, int ty);
 int sweep_shapes(bool fp32, int *out, int max);
 hipError_t launch_sweep(const Target &t, hipStream_t s);
+// whether launch_sweep also forms the segments of the moment sums (all cases hold the buffer)
+bool sweep_forms_sums(const Target &t);
 // unstructured mesh: boundary-face density scales, then the sweep level by level
 // (lev_off[L] .. lev_off[L + 1] are the entries of level L)
 hipError_t launch_uface_scale(const Target &t, int pending, hipStream_t s);

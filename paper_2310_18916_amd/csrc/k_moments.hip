@@ -1,16 +1,9 @@
 // Moment reduction of Eq. (getmoment).
 //
 // k_moments: raw moments of every (cell, velocity octant) about the origin,
-// accumulated in FP64 whatever the VDF precision.  The tensor grid makes the
-// contraction separable: the x-rows of an octant (contiguous in the
-// octant-grouped layout) give the four sums sum_x w_x xi_x^p f (p = 0..3),
-// which fold with the row's y/z weights into the 13 (+4 for f1) monomials.
-// One block per cell, one wave per octant, so per-octant sums -- from which
-// every half-range wall flux follows -- need only a wave reduction.  Every
-// load instruction reads one contiguous stretch of the VDF: rows of up to 20
-// FP64 (32 FP32) values are staged through the wave's LDS region, 32 (64)
-// rows at a time, and read back one row per lane; longer FP64 rows are read
-// with the lanes along the rows (each keeping its columns and x-weights).
+// accumulated in FP64 whatever the VDF precision: per-octant sums, from which
+// every half-range wall flux follows.  k_moment_totals: the same from the
+// segments that the sweep forms of a large state.
 //
 // k_derive: central moments (rho, u, Tt, sigma, q, Tr, qr) of every cell from
 // the octant sums.
@@ -19,385 +12,187 @@
 // M(W') - M(W) of Eq. (updatef), which factor into 1-D sums on the tensor grid,
 // so the corrected state's moments are exact without touching the VDF.
 //
-// On a node list (a refined or unstructured velocity mesh, Sec. 3.1) nothing
-// factors: k_moments_list and k_commit_correction_list sum over the nodes
-// directly, one wave per (cells, octant).
+// On a node list (a refined or unstructured velocity mesh, Sec. 3.1) the
+// correction doesn't factor: k_commit_correction_list sums over the nodes, one
+// wave per (cell, octant).  k_moments_mesh is the moment kernel of an
+// unstructured spatial mesh.
 #include "gsis_common.h"
 #include "gsis_launch.h"
 
 namespace gsis {
 
-// loads of VW consecutive elements of a row (global memory), widened to FP64
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-template <typename T, int VW> struct VecLoad;
-template <> struct VecLoad<float, 1> { static __device__ void ld(gptr<const float> p, double *o) { o[0] = p[0]; } };
-template <> struct VecLoad<float, 2> {
-    static __device__ void ld(gptr<const float> p, double *o)
-    {
-        f32x2 v = *(gptr<const f32x2>)p;
-        o[0] = v.x; o[1] = v.y;
-    }
-};
-template <> struct VecLoad<float, 4> {
-    static __device__ void ld(gptr<const float> p, double *o)
-    {
-        f32x4 v = *(gptr<const f32x4>)p;
-        o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-    }
-};
-template <> struct VecLoad<double, 1> { static __device__ void ld(gptr<const double> p, double *o) { o[0] = p[0]; } };
-template <> struct VecLoad<double, 2> {
-    static __device__ void ld(gptr<const double> p, double *o)
-    {
-        f64x2 v = *(gptr<const f64x2>)p;
-        o[0] = v.x; o[1] = v.y;
-    }
-};
-
-// y and z (weight, node) tables staged in LDS when an axis has at most TABMAX
-// nodes: the fold reads them once per row, which as global loads would
-// outnumber the VDF loads
-constexpr int TABMAX = 256;
-
-template <typename T, int VW, bool DIA>
-__global__ __launch_bounds__(512) void k_moments(GSIS_SPAN_ARGS)
+// Octant sums of a box case, tensor grid or node list, as a matrix product:
+// [cells x nodes] times [nodes x 13 monomials] on the FP64 matrix cores.
+//
+// The order of a cell's sum depends on the octant's size alone, whoever forms
+// it: MCHUNK = 64 consecutive nodes are one chunk, multiplied in 16 products
+// of v_mfma_f64_16x16x4 (product t takes nodes 16 q + t, q = 0..3); four
+// chunks are a segment, (c0 + c1) + (c2 + c3), a missing one zero; segments
+// are added in order.  The sweep forms the segments of its tiles while the
+// values are in registers (k_sweep), and k_moment_totals adds them up;
+// k_moments does all of it from the stored VDF, for a state that was set and
+// for tiles that don't form segments, with the same result to the bit.
+//
+// k_moments: lane l of a product supplies f(cell l & 15, node 16 (l >> 4) + t)
+// and monomial l & 15 of that node.  A block is one wave for 16 G cells of one
+// octant; its loads take whole stretches of 1 / G KB of a row and pass through
+// LDS, the next chunk's in flight while one is multiplied.  Bound by reading
+// the VDF once in FP64: 12.6 ms for 75.5 GB (64 x 48 x 48 cells, 40^3 nodes), 6.0
+// TB/s; in FP32 by the products' LDS reads, 10.9 ms for 51.5 GB.  (Sums along
+// the rows of the tensor grid with a reduction over lanes read 6.8 and 5.8 TB/s,
+// but in an order that the sweep can't form; with the segments in the sweep
+// this kernel runs for small states, where both take 0.03 to 0.05 ms, and once
+// when a state is set.)
+template <typename T, bool DIA>
+__global__ __launch_bounds__(64) void k_moments(GSIS_SPAN_ARGS)
 {
-    __shared__ double sty[2 * TABMAX], stz[2 * TABMAX];
-    // FP32 rows of 4k values staged through LDS (64 rows per wave at a time)
-    constexpr bool STG = sizeof(T) == 4 && VW == 4;
-    constexpr int SROW = 32;
-    __shared__ __attribute__((aligned(16))) float stg[STG ? 8 * 64 * SROW : 4];
-    // FP64 rows of up to 20 values staged 32 at a time, each in a slot of at most 44 words
-    constexpr bool STG64 = sizeof(T) == 8 && VW == 2;
-    __shared__ __attribute__((aligned(16))) float stg64[STG64 ? 8 * 32 * 44 : 4];
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    constexpr int G = MOM_GROUPS;
+    constexpr int V = 16 / (int)sizeof(T);   // values of one 16-byte load
+    constexpr int LR = 64 / G;               // lanes along a row
+    constexpr int NCH = LR * V / MCHUNK;     // chunks of a stretch
+    constexpr int PITCH = 1024 + 16;         // 16 rows at one offset take all LDS banks
+    constexpr int ND = DIA ? 2 : 1;
+    // a row starts at any element
+    typedef T vec __attribute__((ext_vector_type(V)));
+    typedef T uvec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+    __shared__ __attribute__((aligned(16))) char sv[16 * PITCH];
+    __shared__ d2 sn[NCH * MCHUNK * 2];
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
-    const gptr<const T> f0 = (gptr<const T>)C.d.f0;
-    const gptr<const T> f1 = (gptr<const T>)C.d.f1;
-    const gptr<const int> cflag = (gptr<const int>)C.d.cflag;
-    const gptr<const double> xtab = (gptr<const double>)C.d.xtab;
-    const gptr<const double> ytab = (gptr<const double>)C.d.ytab;
-    const gptr<const double> ztab = (gptr<const double>)C.d.ztab;
-    const gptr<double> mom8 = (gptr<double>)C.d.mom8;
-    const int cell = blk;
-    const int o = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    const gptr<double> out = mom8 + ((size_t)cell * 8 + o) * NRS;
-    if (!cflag[cell]) {
-        if (lane < NRS) out[lane] = 0.0;
-        return;
-    }
-    const bool staged = g.n1[1] <= TABMAX && g.n1[2] <= TABMAX;   // uniform over the block
-    if (staged) {
-        for (int i = threadIdx.x; i < 2 * g.n1[1]; i += blockDim.x) sty[i] = ytab[i];
-        for (int i = threadIdx.x; i < 2 * g.n1[2]; i += blockDim.x) stz[i] = ztab[i];
-    }
-    __syncthreads();
-    const int nox = g.on[o][0], noy = g.on[o][1], noz = g.on[o][2];
-    const int x0 = (o & 1) ? 0 : g.k0[0];
-    const int y0 = (o & 2) ? 0 : g.k0[1];
-    const int z0 = (o & 4) ? 0 : g.k0[2];
-    const size_t base = (size_t)cell * g.nv + g.obase[o];
-    const int nrow = noy * noz;
-    constexpr bool ALONG = sizeof(T) == 8 && VW == 2;   // the faster mapping for this layout (measured)
-    double acc[13];
+    const int o = blk & 7, c0 = (blk >> 3) * 16 * G;
+    const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
+    const int n = g.osize[o], ob = g.obase[o], ncell = g.ncell;
+    const size_t nv = (size_t)g.nv;
+    const gptr<const d2> nt = (gptr<const d2>)C.d.nt64 + 2 * (size_t)ob;
+    // load k reads G cells' rows
+    const int lr = lane / LR, lv = (lane % LR) * V;
+    auto rowp = [&](int d, int k) {
+        const int c = min(c0 + G * k + lr, ncell - 1);
+        return (d ? (gptr<const T>)C.d.f1 : (gptr<const T>)C.d.f0) + (size_t)c * nv + ob;
+    };
+    const Monomial mono(i);
+    d4 tot[ND][G], seg[ND][G], pair[ND][G];
 #pragma unroll
-    for (int k = 0; k < 13; ++k) acc[k] = 0.0;
-    double acc1[4] = {0.0, 0.0, 0.0, 0.0};
-    const float rcp_noy = 1.0f / (float)noy;   // exact row -> (ly, lz) split for rows < 2^16
-    // fold the x-sums s_p = sum_x w_x x^p f of row r with its y/z weights
-    auto fold = [&](int r, double s0, double s1, double s2, double s3, double t0, double t1) {
-        const int lz = (int)(((float)r + 0.5f) * rcp_noy), ly = r - lz * noy;
-        double wy, y, wz, z;
-        if (staged) {
-            wy = sty[2 * (y0 + ly)]; y = sty[2 * (y0 + ly) + 1];
-            wz = stz[2 * (z0 + lz)]; z = stz[2 * (z0 + lz) + 1];
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int k = 0; k < G; ++k) tot[d][k] = seg[d][k] = pair[d][k] = d4{0.0, 0.0, 0.0, 0.0};
+    vec pv[16];
+    d2 pn[NCH * 2];
+    auto load = [&](int d, int n0) {
+        if (n0 + NCH * MCHUNK <= n) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) pv[k] = __builtin_nontemporal_load((gptr<const uvec>)(rowp(d, k) + n0 + lv));
         } else {
-            wy = ytab[2 * (y0 + ly)]; y = ytab[2 * (y0 + ly) + 1];
-            wz = ztab[2 * (z0 + lz)]; z = ztab[2 * (z0 + lz) + 1];
+#pragma unroll
+            for (int k = 0; k < 16; ++k)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const int l = n0 + lv + e;
+                    const T f = rowp(d, k)[min(l, n - 1)];
+                    pv[k][e] = l < n ? f : T(0);
+                }
         }
-        const double W0 = wy * wz;
-        const double Y1 = W0 * y, Z1 = W0 * z;
-        const double Y2 = Y1 * y, Z2 = Z1 * z, YZ = Y1 * z;
-        const double Y3 = Y2 * y, Z3 = Z2 * z, YZ2 = YZ * z, Y2Z = Y2 * z;
-        acc[0] += W0 * s0;
-        acc[1] += W0 * s1;
-        acc[2] += Y1 * s0;
-        acc[3] += Z1 * s0;
-        acc[4] += W0 * s2;
-        acc[5] += Y2 * s0;
-        acc[6] += Z2 * s0;
-        acc[7] += Y1 * s1;
-        acc[8] += Z1 * s1;
-        acc[9] += YZ * s0;
-        acc[10] += W0 * s3 + (Y2 + Z2) * s1;   // x |xi|^2 = x^3 + x y^2 + x z^2
-        acc[11] += Y1 * s2 + (Y3 + YZ2) * s0;  // y |xi|^2 = x^2 y + y^3 + y z^2
-        acc[12] += Z1 * s2 + (Y2Z + Z3) * s0;  // z |xi|^2 = x^2 z + y^2 z + z^3
-        if (DIA) {
-            acc1[0] += W0 * t0;
-            acc1[1] += W0 * t1;
-            acc1[2] += Y1 * t0;
-            acc1[3] += Z1 * t0;
+        if (d == 0) {
+#pragma unroll
+            for (int k = 0; k < NCH * 2; ++k) pn[k] = nt[min(2 * n0 + 64 * k + lane, 2 * n - 1)];
         }
     };
-    // Two mappings, chosen by measurement.  Row per lane: each lane owns an
-    // x-row and reads it in chunks whose loads are issued together (the
-    // x-weights are wave-uniform).  Along the rows (FP64 pairs): lpr lanes
-    // cover a row with VW elements each, 64 / lpr rows per load instruction,
-    // so every load reads one contiguous stretch of the octant; a lane keeps
-    // its columns (x-weights in registers) and issues UN rows' loads first.
-    const int lpr = nox / VW;
-    if (STG64 && nox <= 20) {
-        // FP64 rows of at most 20 values: 32 rows at a time staged through the
-        // wave's LDS region, each row in a slot of W words, W/4 odd, so the
-        // 16 lanes of a b128 pass read disjoint banks
-        const int W0 = nox * 2, W = (W0 >> 2) & 1 ? W0 : W0 + 4;
-        const int vpr = nox >> 1;                  // 16-byte vectors per row
-        float *sw = stg64 + o * 32 * 44;
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        auto stage = [&](gptr<const T> fq, int r0, int nr) {
-            const int nvec = nr * vpr;
-            const gptr<const f4> src = (gptr<const f4>)(fq + base + (size_t)r0 * nox);
-            f4 tmp[10];
+    if (n > 0) load(0, 0);
+    for (int n0 = 0; n0 < n; n0 += NCH * MCHUNK)
 #pragma unroll
-            for (int k = 0; k < 10; ++k)
-                if (lane + 64 * k < nvec) tmp[k] = __builtin_nontemporal_load(src + lane + 64 * k);
+        for (int d = 0; d < ND; ++d) {
 #pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const int v = lane + 64 * k;
-                if (v < nvec) {
-                    const int r = v / vpr, c = v - r * vpr;
-                    *(f4 *)(sw + r * W + 4 * c) = tmp[k];
-                }
+            for (int k = 0; k < 16; ++k) *(vec *)(sv + k * PITCH + lane * 16) = pv[k];
+            if (d == 0) {
+#pragma unroll
+                for (int k = 0; k < NCH * 2; ++k) sn[64 * k + lane] = pn[k];
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        auto done = [&]() {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        for (int r0 = 0; r0 < nrow; r0 += 32) {
-            const int nr = nrow - r0 < 32 ? nrow - r0 : 32;
-            double s0 = 0, s1 = 0, s2 = 0, s3 = 0, t0 = 0, t1 = 0;
-            stage(f0, r0, nr);
-            if (lane < nr) {
-                const double *row = (const double *)(sw + lane * W);
-                for (int c = 0; c < nox; c += 2) {
-                    const double e[2] = {row[c], row[c + 1]};
+            __syncthreads();
+            if (d + 1 < ND) load(d + 1, n0);
+            else if (n0 + NCH * MCHUNK < n) load(0, n0 + NCH * MCHUNK);
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) {
-                        const gptr<const double> xt = xtab + (size_t)(x0 + c + q) * 4;
-                        s0 += xt[0] * e[q];
-                        s1 += xt[1] * e[q];
-                        s2 += xt[2] * e[q];
-                        s3 += xt[3] * e[q];
+            for (int h = 0; h < NCH; ++h) {
+                d4 acc[G];
+#pragma unroll
+                for (int k = 0; k < G; ++k) acc[k] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+                for (int s = 0; s < 16; s += V) {
+                    vec a[G];
+#pragma unroll
+                    for (int k = 0; k < G; ++k)
+                        a[k] = *(const vec *)(sv + i * PITCH + k * (1024 / G) + (h * MCHUNK + 16 * q + s) * sizeof(T));
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const int l = h * MCHUNK + 16 * q + s + e;
+                        const d2 t0 = sn[2 * l], t1 = sn[2 * l + 1];
+                        const double m = mono(t0.x, t0.y, t1.x, t1.y);
+#pragma unroll
+                        for (int k = 0; k < G; ++k)
+                            acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[k][e], m, acc[k], 0, 0, 0);
                     }
                 }
-            }
-            done();
-            if (DIA) {
-                stage(f1, r0, nr);
-                if (lane < nr) {
-                    const double *row = (const double *)(sw + lane * W);
-                    for (int c = 0; c < nox; c += 2) {
-                        const double e[2] = {row[c], row[c + 1]};
+                const int c = (n0 / MCHUNK + h) & 3;   // uniform
+                const bool last = n0 + (h + 1) * MCHUNK >= n;
 #pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            const gptr<const double> xt = xtab + (size_t)(x0 + c + q) * 4;
-                            t0 += xt[0] * e[q];
-                            t1 += xt[1] * e[q];
-                        }
+                for (int k = 0; k < G; ++k) {
+                    if (c == 0) seg[d][k] = acc[k];
+                    else if (c == 1) seg[d][k] += acc[k];
+                    else if (c == 2) pair[d][k] = acc[k];
+                    else pair[d][k] += acc[k];
+                    if (c == 3 || last) {
+                        tot[d][k] += seg[d][k] + (c < 2 ? d4{0.0, 0.0, 0.0, 0.0} : pair[d][k]);
                     }
                 }
-                done();
+                if (last) break;
             }
-            if (lane < nr) fold(r0 + lane, s0, s1, s2, s3, t0, t1);
+            __syncthreads();
         }
-    } else if (STG && nox <= SROW) {
-        // FP32 rows of at most SROW values: 64 rows at a time are staged
-        // through this wave's LDS region with coalesced 16-byte loads (the 64
-        // rows are one contiguous stretch of the octant), then each lane reads
-        // its own row from LDS (rows of 4k floats: conflict-free b128 reads).
-        // f1 passes through the same region after f0.  Only the lanes of one
-        // wave share a region, so a wave barrier orders its writes and reads.
-        float *sw = stg + o * 64 * SROW;
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        auto stage = [&](gptr<const T> fq, int r0, int nr) {
-            const int nvec = (nr * nox) >> 2;
-            const gptr<const f4> src = (gptr<const f4>)(fq + base + (size_t)r0 * nox);
-            f4 tmp[SROW / 4];
+    // lane l holds sum (l & 15) of rows 4 r + (l >> 4), r = 0..3
+    const gptr<double> mom8 = (gptr<double>)C.d.mom8;
+    const gptr<const int> cflag = (gptr<const int>)C.d.cflag;
 #pragma unroll
-            for (int k = 0; k < SROW / 4; ++k)
-                if (lane + 64 * k < nvec) tmp[k] = __builtin_nontemporal_load(src + lane + 64 * k);
+    for (int k = 0; k < G; ++k)
 #pragma unroll
-            for (int k = 0; k < SROW / 4; ++k)
-                if (lane + 64 * k < nvec) ((f4 *)sw)[lane + 64 * k] = tmp[k];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        auto done = [&]() {   // every lane has read its row before the region is overwritten
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        for (int r0 = 0; r0 < nrow; r0 += 64) {
-            const int nr = nrow - r0 < 64 ? nrow - r0 : 64;
-            double s0 = 0, s1 = 0, s2 = 0, s3 = 0, t0 = 0, t1 = 0;
-            stage(f0, r0, nr);
-            if (lane < nr) {
-                const f4 *row = (const f4 *)(sw + lane * nox);
-                for (int c = 0; c < (nox >> 2); ++c) {
-                    const f4 v = row[c];
-                    const double e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const gptr<const double> xt = xtab + (size_t)(x0 + 4 * c + q) * 4;
-                        s0 += xt[0] * e[q];
-                        s1 += xt[1] * e[q];
-                        s2 += xt[2] * e[q];
-                        s3 += xt[3] * e[q];
-                    }
-                }
-            }
-            done();
-            if (DIA) {
-                stage(f1, r0, nr);
-                if (lane < nr) {
-                    const f4 *row = (const f4 *)(sw + lane * nox);
-                    for (int c = 0; c < (nox >> 2); ++c) {
-                        const f4 v = row[c];
-                        const double e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const gptr<const double> xt = xtab + (size_t)(x0 + 4 * c + q) * 4;
-                            t0 += xt[0] * e[q];
-                            t1 += xt[1] * e[q];
-                        }
-                    }
-                }
-                done();
-            }
-            if (lane < nr) fold(r0 + lane, s0, s1, s2, s3, t0, t1);
+        for (int r = 0; r < 4; ++r) {
+            const int cell = c0 + G * (4 * r + q) + k;
+            if (cell >= ncell) continue;
+            const bool live = cflag[cell] != 0;
+            const gptr<double> out = mom8 + ((size_t)cell * 8 + o) * NRS;
+            if (i < 13) out[i] = live ? tot[0][k][r] : 0.0;
+            if (i < 4) out[13 + i] = DIA && live ? tot[ND - 1][k][r] : 0.0;
         }
-    } else if (!ALONG) {
-        // one row per lane, read in chunks of CH vectors issued together
-        constexpr int CH0 = (DIA ? 64 : 128) / (VW * (int)sizeof(T));
-        constexpr int CH = CH0 < 16 ? CH0 : 16;
-        for (int r = lane; r < nrow; r += 64) {
-            const gptr<const T> row0 = f0 + base + (size_t)r * nox;
-            const gptr<const T> row1 = DIA ? f1 + base + (size_t)r * nox : row0;
-            double s0 = 0, s1 = 0, s2 = 0, s3 = 0, t0 = 0, t1 = 0;
-            // a row is read in chunks of CH vectors whose loads are all issued
-            // before any is used, so the lines of a row are fetched together
-            for (int lx0 = 0; lx0 < nox; lx0 += CH * VW) {
-                double v[CH][VW], v1[CH][VW];
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    if (lx0 + c * VW < nox) {
-                        VecLoad<T, VW>::ld(row0 + lx0 + c * VW, v[c]);
-                        if (DIA) VecLoad<T, VW>::ld(row1 + lx0 + c * VW, v1[c]);
-                    }
-                }
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    if (lx0 + c * VW >= nox) break;
-#pragma unroll
-                    for (int e = 0; e < VW; ++e) {
-                        const gptr<const double> xt = xtab + (size_t)(x0 + lx0 + c * VW + e) * 4;
-                        s0 += xt[0] * v[c][e];
-                        s1 += xt[1] * v[c][e];
-                        s2 += xt[2] * v[c][e];
-                        s3 += xt[3] * v[c][e];
-                        if (DIA) {
-                            t0 += xt[0] * v1[c][e];
-                            t1 += xt[1] * v1[c][e];
-                        }
-                    }
-                }
-            }
-            fold(r, s0, s1, s2, s3, t0, t1);
+}
+
+// The octant sums from the segments that the sweep stored: 16 cells of one
+// octant per block, a thread per (cell, sum).
+__global__ __launch_bounds__(256) void k_moment_totals(GSIS_SPAN_ARGS)
+{
+    int blk;
+    const Case &C = case_of(span_cases, span_map, blk);
+    const Geo &g = C.g;
+    const int o = blk & 7, cell = (blk >> 3) * 16 + (threadIdx.x >> 4), j = threadIdx.x & 15;
+    if (cell >= g.ncell) return;
+    const int s0 = g.oseg[o], s1 = g.oseg[o + 1];
+    const bool live = ((gptr<const int>)C.d.cflag)[cell] != 0;
+    const gptr<double> out = (gptr<double>)C.d.mom8 + ((size_t)cell * 8 + o) * NRS;
+    const size_t step = (size_t)g.ncell * 16;
+    gptr<const double> p = (gptr<const double>)C.d.mseg + s0 * step + (size_t)cell * 16 + j;
+    double t = 0.0;
+#pragma unroll 8
+    for (int s = s0; s < s1; ++s, p += step) t += *p;
+    if (j < 13) out[j] = live ? t : 0.0;
+    if (j < 4) {
+        double t1 = 0.0;
+        if (g.species == 1) {
+            gptr<const double> p1 = (gptr<const double>)C.d.mseg1 + s0 * (step / 4) + (size_t)cell * 4 + j;
+#pragma unroll 8
+            for (int s = s0; s < s1; ++s, p1 += step / 4) t1 += *p1;
         }
-    } else if (lpr <= 64) {
-        const int rpi = 64 / lpr;
-        const int my_r = lane / lpr, my_c = lane - my_r * lpr;
-        if (my_r < rpi) {
-            double wx[VW][4];
-#pragma unroll
-            for (int e = 0; e < VW; ++e)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) wx[e][q] = xtab[(size_t)(x0 + my_c * VW + e) * 4 + q];
-            constexpr int UN0 = (DIA ? 64 : 128) / (VW * (int)sizeof(T));
-            constexpr int UN = UN0 < 16 ? UN0 : 16;
-            for (int rb = my_r; rb < nrow; rb += UN * rpi) {
-                double v[UN][VW], v1[UN][VW];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int r = rb + u * rpi;
-                    if (r < nrow) {
-                        VecLoad<T, VW>::ld(f0 + base + (size_t)r * nox + my_c * VW, v[u]);
-                        if (DIA) VecLoad<T, VW>::ld(f1 + base + (size_t)r * nox + my_c * VW, v1[u]);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int r = rb + u * rpi;
-                    if (r >= nrow) break;
-                    double s0 = 0, s1 = 0, s2 = 0, s3 = 0, t0 = 0, t1 = 0;
-#pragma unroll
-                    for (int e = 0; e < VW; ++e) {
-                        s0 += wx[e][0] * v[u][e];
-                        s1 += wx[e][1] * v[u][e];
-                        s2 += wx[e][2] * v[u][e];
-                        s3 += wx[e][3] * v[u][e];
-                        if (DIA) {
-                            t0 += wx[e][0] * v1[u][e];
-                            t1 += wx[e][1] * v1[u][e];
-                        }
-                    }
-                    fold(r, s0, s1, s2, s3, t0, t1);
-                }
-            }
-        }
-    } else {
-        // rows longer than 64 vectors: the lanes take column groups of each row
-        for (int r = 0; r < nrow; ++r) {
-            double s0 = 0, s1 = 0, s2 = 0, s3 = 0, t0 = 0, t1 = 0;
-            for (int c = lane; c < lpr; c += 64) {
-                double v[VW], v1[VW];
-                VecLoad<T, VW>::ld(f0 + base + (size_t)r * nox + c * VW, v);
-                if (DIA) VecLoad<T, VW>::ld(f1 + base + (size_t)r * nox + c * VW, v1);
-#pragma unroll
-                for (int e = 0; e < VW; ++e) {
-                    const gptr<const double> xt = xtab + (size_t)(x0 + c * VW + e) * 4;
-                    s0 += xt[0] * v[e];
-                    s1 += xt[1] * v[e];
-                    s2 += xt[2] * v[e];
-                    s3 += xt[3] * v[e];
-                    if (DIA) {
-                        t0 += xt[0] * v1[e];
-                        t1 += xt[1] * v1[e];
-                    }
-                }
-            }
-            fold(r, s0, s1, s2, s3, t0, t1);
-        }
+        out[13 + j] = live ? t1 : 0.0;
     }
-    // transposing reduction: lane groups end with one of the NRS sums each
-    constexpr int NR = DIA ? 32 : 16;
-    double v[NR];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) v[k] = k < 13 ? acc[k < 13 ? k : 0] : (DIA && k < NRS ? acc1[k < NRS ? k - 13 : 0] : 0.0);
-    int idx;
-    const double r = wave_reduce_scatter<NR>(v, lane, &idx);
-    if ((lane & (64 / NR - 1)) == 0 && idx < NRS) out[idx] = r;
-    if (!DIA && lane == 0) out[NRS - 1] = 0.0;   // 13..15 come from the zero padding
 }
 
 // The 13 raw monomials of one node times its weight: 1, x, y, z, xx, yy, zz,
@@ -440,7 +235,7 @@ __device__ __forceinline__ void store_octant_sums(const double *acc, const doubl
     if (!DIA && !add && lane == 0) out[NRS - 1] = 0.0;
 }
 
-// Node list: one wave (block) per octant of a group of CG consecutive cells.
+// Unstructured spatial mesh: one wave (block) per octant of a group of CG consecutive cells.
 // A lane takes the octant's nodes 64 apart, reads each node's (xi, w) once
 // and applies its monomials to the node's value in every cell of the group,
 // so the node table is read once per CG cells while each VDF load covers 64
@@ -448,7 +243,7 @@ __device__ __forceinline__ void store_octant_sums(const double *acc, const doubl
 // of all cells issued unconditionally (rows clamped to the last cell, a dead
 // or missing cell's sums discarded at the end), keep 2 CG loads in flight.
 template <typename T, bool DIA, int CG>
-__global__ __launch_bounds__(64) void k_moments_list(GSIS_SPAN_ARGS)
+__global__ __launch_bounds__(64) void k_moments_mesh(GSIS_SPAN_ARGS)
 {
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
@@ -703,49 +498,27 @@ __global__ __launch_bounds__(512) void k_commit_correction_list(GSIS_SPAN_ARGS)
 }
 
 // ------------------------------------------------------------------ launches
-template <typename T, int VW>
-static void moments_vw(const Target &t, int cls, hipStream_t s)
-{
-    const Span sp{t.cases, t.mom_map[cls]};
-    const dim3 grid(t.mom_nblk[cls]);
-    if (t.dia) hipLaunchKernelGGL((k_moments<T, VW, true>), grid, dim3(512), 0, s, GSIS_SPAN(sp));
-    else hipLaunchKernelGGL((k_moments<T, VW, false>), grid, dim3(512), 0, s, GSIS_SPAN(sp));
-}
-
-// One launch per vector-width class present (a case's width follows its
-// octant row lengths), so every case is reduced exactly as on its own.
-// cells per block of the node-list moment kernel
-template <bool DIA> constexpr int list_cg() { return DIA ? 2 : 4; }
-
 template <typename T, bool DIA>
-static void moments_list(const Target &t, hipStream_t s)
+static void moments(const Target &t, hipStream_t s)
 {
-    constexpr int CG = list_cg<DIA>();
-    const int ncell = t.host[0].g.ncell;
-    hipLaunchKernelGGL((k_moments_list<T, DIA, CG>), dim3(8 * ((ncell + CG - 1) / CG)), dim3(64), 0, s,
-                       GSIS_SPAN(t.span(K_CELL1)));
+    if (t.host[0].g.umesh) {
+        constexpr int CG = DIA ? 2 : 4;   // cells per block
+        const int ncell = t.host[0].g.ncell;
+        hipLaunchKernelGGL((k_moments_mesh<T, DIA, CG>), dim3(8 * ((ncell + CG - 1) / CG)), dim3(64), 0, s,
+                           GSIS_SPAN(t.span(K_CELL1)));
+        return;
+    }
+    hipLaunchKernelGGL((k_moments<T, DIA>), dim3(t.nblk[K_MOM]), dim3(64), 0, s, GSIS_SPAN(t.span(K_MOM)));
 }
 
-hipError_t launch_moments(const Target &t, hipStream_t s)
+hipError_t launch_moments(const Target &t, hipStream_t s, bool swept)
 {
-    if (t.vlist) {
-        // one case (batches hold tensor grids only)
-        if (t.fp32) { if (t.dia) moments_list<float, true>(t, s); else moments_list<float, false>(t, s); }
-        else { if (t.dia) moments_list<double, true>(t, s); else moments_list<double, false>(t, s); }
+    if (swept && sweep_forms_sums(t)) {
+        hipLaunchKernelGGL(k_moment_totals, dim3(t.nblk[K_MSUM]), dim3(256), 0, s, GSIS_SPAN(t.span(K_MSUM)));
         return hipGetLastError();
     }
-    if (t.mom_nblk[0] > 0) {
-        if (t.fp32) moments_vw<float, 1>(t, 0, s);
-        else moments_vw<double, 1>(t, 0, s);
-    }
-    if (t.mom_nblk[1] > 0) {
-        if (t.fp32) moments_vw<float, 2>(t, 1, s);
-        else moments_vw<double, 2>(t, 1, s);
-    }
-    if (t.mom_nblk[2] > 0) {
-        if (t.fp32) moments_vw<float, 4>(t, 2, s);
-        else moments_vw<double, 2>(t, 2, s);   // FP64 rows load two at a time at most
-    }
+    if (t.fp32) { if (t.dia) moments<float, true>(t, s); else moments<float, false>(t, s); }
+    else { if (t.dia) moments<double, true>(t, s); else moments<double, false>(t, s); }
     return hipGetLastError();
 }
 
