@@ -92,7 +92,6 @@ struct Dev {
     // themselves (order 1, times inv_dt), or ho0/ho1 (order 2)
     void *rs0, *rs1;
     void *ho0, *ho1;   // order 2: inv_dt f^n - (second-order - first-order flux divergence), [ncell + 1][nv]
-    void *lim0, *lim1; // order 2: Venkatakrishnan limiter per point, [ncell][nv]
     double *mom8;      // [ncell][8][NRS]
     // segments of the octant sums formed by the sweep, [oseg[8]][ncell][16] of f0 and
     // [..][..][4] of f1 (null: the sums are taken from the stored VDF)

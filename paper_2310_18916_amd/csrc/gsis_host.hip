@@ -376,21 +376,25 @@ size_t layout(gsis_ctx *c, char *base)
     d.f1 = f1;
     d.rs0 = f0;
     d.rs1 = f1;
-    d.ho0 = d.ho1 = d.lim0 = d.lim1 = nullptr;
+    d.ho0 = d.ho1 = nullptr;
+    char *l0 = nullptr, *l1 = nullptr;   // order 2: one more buffer per VDF
     if (g.order == 2) {
-        char *h0 = nullptr, *h1 = nullptr, *l0 = nullptr, *l1 = nullptr;
+        char *h0 = nullptr, *h1 = nullptr;
         carve(off, h0, (n + 1) * nv * esz, base);
         carve(off, l0, n * nv * esz, base);
         if (g.species == 1) {
             carve(off, h1, (n + 1) * nv * esz, base);
             carve(off, l1, n * nv * esz, base);
         }
-        d.ho0 = h0; d.ho1 = h1; d.lim0 = l0; d.lim1 = l1;
+        d.ho0 = h0; d.ho1 = h1;
         d.rs0 = h0; d.rs1 = h1;
     }
     carve(off, d.mom8, n * 8 * NRS, base);
     d.mseg = d.mseg1 = nullptr;
-    if (c->segments) {
+    if (c->segments && g.order == 2 && (size_t)g.oseg[8] * 16 * sizeof(double) <= nv * esz) {
+        d.mseg = (double *)l0;   // the second-order term needs no buffer but ho0, ho1
+        d.mseg1 = (double *)l1;
+    } else if (c->segments) {
         carve(off, d.mseg, n * g.oseg[8] * 16, base);
         if (g.species == 1) carve(off, d.mseg1, n * g.oseg[8] * 4, base);
     }

@@ -14,7 +14,23 @@
 // The sweep keeps its first-order implicit operator in direct form; the
 // difference of the two divergences, D2 - D1, moves to its right-hand side:
 // it reads inv_dt f^n - (D2 - D1) per point from the buffer written here.
-// Two passes over the VDF: the limiter of every point, then that term.
+//
+// With G_a = phi grad_a f of a cell the term is the sum over the axes of
+//   (xi_a / 2) (G_a of the cell [downwind face interior]
+//               - G_a of the upwind cell [upwind face interior]),
+// so one pass over the VDF does it: a block of four waves takes PX x PY columns
+// of cells for 64 nodes of one octant and walks them downwind in z.  A wave
+// holds one row of PX columns, the x-upwind column beside it and 2 of the PX
+// y-upwind columns, with the values at k - 1, k, k + 1 (and the ones ahead) in
+// registers; a plane's values meet in LDS for the y neighbours, G_y goes
+// through LDS to the next row, G_x and G_z stay in registers.  Limiters are
+// formed for (PX PY + PX + PY) / (PX PY) = 1.375 of the points and VDF values
+// read 2.2 times, mostly from L2.  Bound by two waves per SIMD between the
+// memory floor (33.6 GB, 7.8 ms) and the limiter's arithmetic: 13.4 ms on 40^3
+// cells x 32^3 nodes in FP64, 6.9 without the limiter on 48^3 x 24^3 (24.5 GB,
+// 5.7).  Two passes (every point's limiter stored and read back, neighbours from
+// L2, 15 reads per point, six divisions) took 35.6; this pass with the six
+// divisions replaced by cross products 20.7.
 #include "gsis_common.h"
 #include "gsis_launch.h"
 
@@ -22,320 +38,229 @@
 
 namespace gsis {
 
-constexpr int RB = 256;      // nodes per block: one run of an octant
+constexpr int PX = 8, PY = 4;          // columns of a block
+constexpr int NCOL = PX + 3;           // columns of a wave
 
-// A block walks one column of cells along z for one run of 256 nodes of one
-// octant, keeping the z neighbours in registers (sliding windows), so the
-// only neighbour loads are those of the four x and y neighbour columns,
-// which the blocks of those columns read at about the same time.  Logical
-// block = run * (nx ny) + column; blocks are dealt to the 8 XCDs round
-// robin, so logical block (b mod 8) (nblk / 8) + b / 8 gives every XCD one
-// contiguous range of columns.  Within a run the columns go in patches of
-// RPX x RPY (where nx and ny divide), so that the y neighbours of a column
-// are read by blocks RPX apart instead of nx apart and find their lines in
-// the XCD's L2 (48^3 x 32^3 cavity, FP64: 65.0 -> 59.3 ms per pass).
-constexpr int RPX = 8, RPY = 8;
-struct ReconBlock { int o, l, col, i, j; };
-
-__device__ __forceinline__ ReconBlock recon_block(const Geo &g, int nvb)
+// Venkatakrishnan's psi of a face whose neighbourhood leaves D >= 0 on the side of
+// the reconstruction's change x >= 0; D2 = D^2 + eps^2, y = 2 x.  (0 / 0, of values
+// whose squares underflow, limits nothing: fmin passes over it.)
+template <typename T>
+__device__ __forceinline__ T psi(T D, T D2, T x)
 {
+    const T y = T(2) * x;
+    return fma(D, y, D2) / fma(D, x, fma(y, x, D2));
+}
+
+// Venkatakrishnan phi of one point, the least psi over its interior faces (at most
+// 1), and its gradient G = phi grad f along the octant's axes: f[2 a] the upwind
+// and f[2 a + 1] the downwind neighbour along axis a; e2 = (K h)^3, multiplied
+// here by the square of the stencil's largest |f|.
+//
+// Below 1 (x > D / 2) psi falls with x and grows with D.  Where all six neighbours
+// are fluid cells both faces of an axis have the same x, one with D = max - f and
+// one with f - min, so the least is psi(least D, largest x): one division
+// instead of six.
+template <typename T>
+__device__ __forceinline__ void limited_gradient(const T *invh, bool limited, T fc, const T *f, T e2, T *G)
+{
+    T mx = fc, mn = fc, x = T(0), df[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        mx = fmax(mx, fmax(f[2 * a], f[2 * a + 1]));
+        mn = fmin(mn, fmin(f[2 * a], f[2 * a + 1]));
+        df[a] = f[2 * a + 1] - f[2 * a];
+        x = fmax(x, fabs(df[a]));
+    }
+    T phi = T(0.5);
+    if (limited) {
+        const T S = fmax(fabs(mx), fabs(mn)), D = fmin(mx - fc, fc - mn);
+        phi *= fmin(T(1), psi<T>(D, fma(D, D, e2 * (S * S)), T(0.25) * x));
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) G[a] = phi * (df[a] * invh[a]);
+}
+
+// The same with neighbours missing (has: the neighbour is a fluid cell): a
+// gradient component is one-sided where one is, zero where both are, and only the
+// faces that are there limit it.
+template <typename T>
+__device__ __forceinline__ void limited_gradient(const T *invh, const T *half, bool limited, T fc, const T *f,
+                                                 const bool *has, T e2, T *G)
+{
+    T mx = fc, mn = fc, xu = T(0), xd = T(0), ga[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const T fm = has[2 * a] ? f[2 * a] : fc, fp = has[2 * a + 1] ? f[2 * a + 1] : fc;
+        mx = fmax(mx, fmax(fm, fp));
+        mn = fmin(mn, fmin(fm, fp));
+        ga[a] = (fp - fm) * (has[2 * a] && has[2 * a + 1] ? T(0.5) * invh[a] : invh[a]);
+        const T x = fabs(ga[a]) * half[a];
+        const bool rise = ga[a] > T(0);   // towards the downwind face
+        if (has[2 * a + 1]) { xu = fmax(xu, rise ? x : T(0)); xd = fmax(xd, rise ? T(0) : x); }
+        if (has[2 * a]) { xd = fmax(xd, rise ? x : T(0)); xu = fmax(xu, rise ? T(0) : x); }
+    }
+    T phi = T(1);
+    if (limited) {
+        const T S = fmax(fabs(mx), fabs(mn)), up = mx - fc, dn = fc - mn, eps = e2 * (S * S);
+        phi = fmin(fmin(phi, psi<T>(up, fma(up, up, eps), xu)), psi<T>(dn, fma(dn, dn, eps), xd));
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) G[a] = phi * ga[a];
+}
+
+// Logical block = (octant, 64 nodes) * patches + patch; blocks are dealt to the 8
+// XCDs round robin, so logical block (b mod 8) (nblk / 8) + b / 8 gives every XCD
+// one contiguous range, whose patches share their edges in its L2.
+template <typename T, bool MASK>
+__global__ __launch_bounds__(256) void k_recon(Geo g, Dev d, int nvb, int npx, int npy)
+{
+    constexpr bool F32 = sizeof(T) == 4;
+    constexpr int LX = PX + 3, LY = PY + 3;   // a plane from two upwind to one downwind column
+    __shared__ T sf[LY][LX][64], sg[PY][PX][64];
     const int nblk = (int)gridDim.x;
     int b = (int)blockIdx.x;
     if ((nblk & 7) == 0) b = (b & 7) * (nblk >> 3) + (b >> 3);
-    const int ncol = g.nx * g.ny;
-    const int chunk = b / ncol;
-    ReconBlock r;
-    const int rem = b - chunk * ncol;
-    if (g.nx % RPX == 0 && g.ny % RPY == 0) {
-        const int p = rem / (RPX * RPY), w = rem - p * (RPX * RPY);
-        const int ppr = g.nx / RPX;
-        r.i = (p % ppr) * RPX + w % RPX;
-        r.j = (p / ppr) * RPY + w / RPX;
-        r.col = r.i + g.nx * r.j;
-    } else {
-        r.col = rem;
-        r.i = r.col % g.nx;
-        r.j = r.col / g.nx;
-    }
-    r.o = chunk / nvb;
-    r.l = (chunk - r.o * nvb) * RB + (int)threadIdx.x;
-    return r;
-}
-
-// psi of Venkatakrishnan's limiter for a face: d2 = grad f . (x_face - x_c),
-// D = (max or min of the neighbourhood) - f_c on the side of d2
-template <typename T>
-__device__ __forceinline__ T venkatakrishnan(T D, T d2, T e2)
-{
-    if (d2 == T(0)) return T(1);
-    const T DD = D * D;
-    return (DD + e2 + T(2) * D * d2) / (DD + T(2) * d2 * d2 + D * d2 + e2);
-}
-
-// least-squares gradient component from the cell value and its two neighbours
-// along the axis (hm/hp: the neighbour is a fluid cell)
-template <typename T>
-__device__ __forceinline__ T lsq_component(T fm, T fc, T fp, bool hm, bool hp, T invh)
-{
-    if (hm && hp) return (fp - fm) * (T(0.5) * invh);
-    if (hp) return (fp - fc) * invh;
-    if (hm) return (fc - fm) * invh;
-    return T(0);
-}
-
-// Neighbours of a cell in the x and y directions from its coordinates: the
-// index (the cell itself where there is none, so every load stays in range)
-// and whether it is a fluid cell; per axis also the second cell on the
-// upwind side of octant o.
-struct AroundXY {
-    int nb[4];
-    bool has[4];
-    int uu[2];
-    bool huu[2];
-};
-
-__device__ __forceinline__ AroundXY around_xy(const Geo &g, const gptr<const int> &cflag, int cell, int i, int j, int o)
-{
-    const int co[2] = {i, j}, n[2] = {g.nx, g.ny}, step[2] = {1, g.nx};
-    AroundXY a;
-#pragma unroll
-    for (int ax = 0; ax < 2; ++ax) {
-        const bool lo = co[ax] > 0, hi = co[ax] < n[ax] - 1;
-        a.nb[2 * ax] = lo ? cell - step[ax] : cell;
-        a.nb[2 * ax + 1] = hi ? cell + step[ax] : cell;
-        a.has[2 * ax] = lo && cflag[a.nb[2 * ax]];
-        a.has[2 * ax + 1] = hi && cflag[a.nb[2 * ax + 1]];
-        const int s = (o >> ax) & 1;   // 1: xi < 0, the upwind side is +
-        const bool in2 = s ? co[ax] < n[ax] - 2 : co[ax] > 1;
-        a.uu[ax] = in2 ? (s ? cell + 2 * step[ax] : cell - 2 * step[ax]) : cell;
-        a.huu[ax] = in2 && (s ? a.has[2 * ax + 1] : a.has[2 * ax]) && cflag[a.uu[ax]];
-    }
-    return a;
-}
-
-// Venkatakrishnan phi of one point from the cell value and its six
-// neighbours (value, and whether it is a fluid cell), x-, x+, y-, y+, z-, z+;
-// e2 = (K h)^3, multiplied here by the square of the stencil's largest |f|.
-template <typename T>
-__device__ __forceinline__ T point_limiter(const Geo &g, T fc, const T *fv, const bool *has, T e2)
-{
-    T fn[6];
-#pragma unroll
-    for (int dir = 0; dir < 6; ++dir) fn[dir] = has[dir] ? fv[dir] : fc;
-    T mx = fc, mn = fc;
-#pragma unroll
-    for (int dir = 0; dir < 6; ++dir) { mx = fmax(mx, fn[dir]); mn = fmin(mn, fn[dir]); }
-    // the threshold relative to the local size of f: (K h)^3 S^2, S the largest |f| of the stencil
-    const T S = fmax(fabs(mx), fabs(mn));
-    e2 *= S * S;
-    T phi = T(1);
+    const int patch = b % (npx * npy), run = b / (npx * npy);
+    const int o = run / nvb, l0 = (run - o * nvb) * 64;
+    if (l0 >= g.osize[o]) return;             // uniform over the block
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool act = l0 + lane < g.osize[o];
+    const size_t node = (size_t)g.obase[o] + min(l0 + lane, g.osize[o] - 1);
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const int sx = o & 1, sy = (o >> 1) & 1, sz = (o >> 2) & 1;
+    const int i0 = (patch % npx) * PX, j0 = (patch / npx) * PY;   // in the octant's frame: upwind is one step back
+    const gptr<const T> f = (gptr<const T>)(blockIdx.y ? d.f1 : d.f0);
+    const gptr<T> out = (gptr<T>)(blockIdx.y ? d.ho1 : d.ho0);
+    const gptr<const int> cflag = (gptr<const int>)d.cflag;
+    T ax[3], invh[3], half[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const bool hm = has[2 * a], hp = has[2 * a + 1];
-        const T ga = lsq_component<T>(fn[2 * a], fc, fn[2 * a + 1], hm, hp, (T)g.invh[a]);
-        const T half = T(0.5) * (T)g.h[a];
-        if (hm) {
-            const T d2 = -ga * half;
-            phi = fmin(phi, venkatakrishnan<T>(d2 > T(0) ? mx - fc : mn - fc, d2, e2));
-        }
-        if (hp) {
-            const T d2 = ga * half;
-            phi = fmin(phi, venkatakrishnan<T>(d2 > T(0) ? mx - fc : mn - fc, d2, e2));
-        }
+        ax[a] = T(0.5) * fabs(F32 ? (T)((gptr<const float>)d.nt32)[4 * node + a] : (T)((gptr<const double>)d.nt64)[4 * node + a]);
+        invh[a] = (T)g.invh[a];
+        half[a] = T(0.5) * (T)g.h[a];
     }
-    return phi;
-}
+    const T idt = (T)g.inv_dt, e2 = (T)g.venk_e2;
+    const bool limited = g.limited != 0;
+    const size_t rowb = (size_t)g.nv * sizeof(T);
+    const unsigned loff = (unsigned)node * (unsigned)sizeof(T);
+    // cell of frame column (a, b) of the block at frame height k, clamped into the box
+    auto cell_at = [&](int a, int bb, int k) -> int {
+        const int ii = min(max(i0 + a, 0), nx - 1), jj = min(max(j0 + bb, 0), ny - 1), kk = min(max(k, 0), nz - 1);
+        return (sx ? nx - 1 - ii : ii) + nx * ((sy ? ny - 1 - jj : jj) + ny * (sz ? nz - 1 - kk : kk));
+    };
+    auto value = [&](int a, int bb, int k) -> T {
+        return *(gptr<const T>)((gptr<const char>)f + (size_t)cell_at(a, bb, k) * rowb + loff);
+    };
+    // columns of this wave: its row, the x-upwind one, two y-upwind ones
+    auto col_a = [&](int c) { return c < PX ? c : (c == PX ? -1 : 2 * w + (c - PX - 1)); };
+    auto col_b = [&](int c) { return c <= PX ? w : -1; };
+    // the outer columns this wave brings to the plane
+    constexpr int NOUT = 7;
+    auto out_a = [&](int m) { return m == 0 ? -2 : (m == 1 ? PX : (m < 6 ? 2 * w + (m & 1) : (w == 2 ? PX : -1))); };
+    auto out_b = [&](int m) { return m < 2 ? w : (m < 4 ? -2 : (m < 6 ? PY : (w == 1 ? PY : -1))); };
 
-// The reconstruction term of one axis:
-//   (xi_a / 2) (phi_c g_a,c [downwind face interior] - phi_up g_a,up [upwind face interior])
-// from the values along the axis: fm, fc, fp around the cell, fuu beyond the
-// upwind neighbour, and the limiters of the cell and of the upwind neighbour.
-template <typename T>
-__device__ __forceinline__ T axis_term(int s, T xi, T invh, T fm, T fc, T fp, bool hm, bool hp, T fuu, bool huu,
-                                       T phic, T phup)
-{
-    const bool hup = s ? hp : hm, hdn = s ? hm : hp;
-    const T gc = lsq_component<T>(hm ? fm : fc, fc, hp ? fp : fc, hm, hp, invh);
-    T term = hdn ? phic * gc : T(0);
-    if (hup) {
-        // the upwind cell's neighbours along the axis: this cell, and uu beyond it
-        const T fu = s ? fp : fm;
-        const T vuu = huu ? fuu : fu;
-        const T gu = s ? lsq_component<T>(fc, fu, vuu, true, huu, invh)
-                       : lsq_component<T>(vuu, fu, fc, huu, true, invh);
-        term -= phup * gu;
-    }
-    return T(0.5) * xi * term;
-}
+    // Fluid cells of a plane as one word: bit 5 c + q of column c, q = 0 the cell
+    // itself, 1 and 2 its upwind and downwind neighbour along x, 3 and 4 along y.
+    const int fe = min(lane, 5 * NCOL - 1), fcol = fe / 5, fq = fe - 5 * fcol;
+    const int fa = (fcol < PX ? fcol : (fcol == PX ? -1 : 2 * w + (fcol - PX - 1))) + (fq == 2) - (fq == 1);
+    const int fb = (fcol <= PX ? w : -1) + (fq == 4) - (fq == 3);
+    const bool fin = lane < 5 * NCOL && i0 + fa >= 0 && i0 + fa < nx && j0 + fb >= 0 && j0 + fb < ny;
+    const unsigned long long inxy = __ballot(fin);
+    auto flag_of = [&](int k) -> int { return MASK ? cflag[cell_at(fa, fb, k)] : 1; };
+    auto word_of = [&](int flag, int k) -> unsigned long long {
+        if (k >= nz) return 0ull;
+        return MASK ? __ballot(fin && flag != 0) : inxy;
+    };
+    unsigned long long prv = 0ull, cur = word_of(flag_of(0), 0), nxt = word_of(flag_of(1), 1);
 
-template <typename T, bool DIA>
-__global__ __launch_bounds__(RB) void k_recon_limiter(Geo g, Dev d, int nvb)
-{
-    constexpr int NQ = DIA ? 2 : 1;
-    const ReconBlock rb = recon_block(g, nvb);
-    if (rb.o >= 8 || rb.l >= g.osize[rb.o]) return;
-    const size_t nv = (size_t)g.nv, node = (size_t)g.obase[rb.o] + rb.l;
-    const int nz = g.nz, nxy = g.nx * g.ny;
-    const T e2 = (T)g.venk_e2;
-    const gptr<const int> cflag = (gptr<const int>)d.cflag;
-    gptr<const T> f[NQ];
-    gptr<T> lim[NQ];
+    T fm[NCOL], fc[NCOL], fp[NCOL], fx[NCOL], ov[NOUT], gz[PX];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        f[q] = (gptr<const T>)(q ? d.f1 : d.f0);
-        lim[q] = (gptr<T>)(q ? d.lim1 : d.lim0);
+    for (int c = 0; c < NCOL; ++c) {
+        fc[c] = value(col_a(c), col_b(c), 0);
+        fp[c] = value(col_a(c), col_b(c), 1);
+        fm[c] = fc[c];
     }
-    // z window: the values at k - 1, k, k + 1 and their fluid flags
-    T zm[NQ], zc[NQ], zp[NQ];
-    bool fzm = false, fzc = cflag[rb.col] != 0, fzp = nz > 1 && cflag[rb.col + nxy] != 0;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        zc[q] = f[q][(size_t)rb.col * nv + node];
-        zp[q] = f[q][(size_t)(nz > 1 ? rb.col + nxy : rb.col) * nv + node];
-        zm[q] = zc[q];
-    }
+    for (int m = 0; m < NOUT; ++m) ov[m] = value(out_a(m), out_b(m), 0);
+#pragma unroll
+    for (int c = 0; c < PX; ++c) gz[c] = T(0);
     for (int k = 0; k < nz; ++k) {
-        const int cell = rb.col + k * nxy;
-        const int ahead = k + 2 < nz ? cell + 2 * nxy : cell;   // the next window entry, issued first
-        T nxt[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) nxt[q] = f[q][(size_t)ahead * nv + node];
-        const bool fnx = k + 2 < nz && cflag[ahead] != 0;
-        const AroundXY A = around_xy(g, cflag, cell, rb.i, rb.j, rb.o);
-        if (fzc) {   // uniform over the block
-            const bool has[6] = {A.has[0], A.has[1], A.has[2], A.has[3], k > 0 && fzm, k + 1 < nz && fzp};
+        for (int c = 0; c < NCOL; ++c) sf[col_b(c) + 2][col_a(c) + 2][lane] = fc[c];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                T fv[6];
+        for (int m = 0; m < NOUT; ++m) sf[out_b(m) + 2][out_a(m) + 2][lane] = ov[m];
+        __syncthreads();
+        // ahead
 #pragma unroll
-                for (int dir = 0; dir < 4; ++dir) fv[dir] = f[q][(size_t)A.nb[dir] * nv + node];
-                fv[4] = zm[q];
-                fv[5] = zp[q];
-                const T phi = g.limited ? point_limiter<T>(g, zc[q], fv, has, e2) : T(1);
-                lim[q][(size_t)cell * nv + node] = phi;
+        for (int c = 0; c < NCOL; ++c) fx[c] = value(col_a(c), col_b(c), k + 2);
+#pragma unroll
+        for (int m = 0; m < NOUT; ++m) ov[m] = value(out_a(m), out_b(m), k + 1);
+        const int flag2 = flag_of(k + 2);
+        T xz[PX], gy[PX], gup = T(0);
+        auto gradient = [&](int c, T *G) {
+            const int a = col_a(c), bb = col_b(c);
+            const T v[6] = {sf[bb + 2][a + 1][lane], sf[bb + 2][a + 3][lane], sf[bb + 1][a + 2][lane],
+                            sf[bb + 3][a + 2][lane], fm[c], fp[c]};
+            const unsigned m = (unsigned)(cur >> (5 * c)), zu = (unsigned)(prv >> (5 * c)) & 1u, zd = (unsigned)(nxt >> (5 * c)) & 1u;
+            if ((m & 31u) == 31u && zu && zd) {   // uniform
+                limited_gradient<T>(invh, limited, fc[c], v, e2, G);
+            } else {
+                const bool has[6] = {(m & 2u) != 0, (m & 4u) != 0, (m & 8u) != 0, (m & 16u) != 0, zu != 0, zd != 0};
+                limited_gradient<T>(invh, half, limited, fc[c], v, has, e2, G);
             }
+        };
+        T G[3];
+#pragma unroll
+        for (int c = PX + 1; c < NCOL; ++c) {
+            gradient(c, G);
+            sg[0][col_a(c)][lane] = G[1];
+        }
+        gradient(PX, G);
+        gup = G[0];
+#pragma unroll
+        for (int c = 0; c < PX; ++c) {
+            gradient(c, G);
+            const unsigned m = (unsigned)(cur >> (5 * c));
+            const T tx = (m & 4u ? G[0] : T(0)) - (m & 2u ? gup : T(0));
+            const T tz = ((nxt >> (5 * c)) & 1u ? G[2] : T(0)) - ((prv >> (5 * c)) & 1u ? gz[c] : T(0));
+            xz[c] = fma(ax[0], tx, ax[2] * tz);
+            gy[c] = m & 16u ? G[1] : T(0);
+            gup = G[0];
+            gz[c] = G[2];
+            if (w + 1 < PY) sg[w + 1][c][lane] = G[1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < PX; ++c) {
+            const unsigned m = (unsigned)(cur >> (5 * c));
+            const T ty = gy[c] - (m & 8u ? sg[w][c][lane] : T(0));
+            const T v = idt * fc[c] - fma(ax[1], ty, xz[c]);
+            if (act && (m & 1u))
+                __builtin_nontemporal_store(v, (gptr<T>)((gptr<char>)out + (size_t)cell_at(c, w, k) * rowb + loff));
         }
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) { zm[q] = zc[q]; zc[q] = zp[q]; zp[q] = nxt[q]; }
-        fzm = fzc; fzc = fzp; fzp = fnx;
+        for (int c = 0; c < NCOL; ++c) { fm[c] = fc[c]; fc[c] = fp[c]; fp[c] = fx[c]; }
+        prv = cur;
+        cur = nxt;
+        nxt = word_of(flag2, k + 2);
     }
-}
-
-// inv_dt f^n - (D2 - D1) per point, the sum of axis_term over the three axes
-// (the octant fixes the upwind side for the whole block).
-template <typename T, bool DIA>
-__global__ __launch_bounds__(RB) void k_recon_source(Geo g, Dev d, int nvb)
-{
-    constexpr int NQ = DIA ? 2 : 1;
-    const ReconBlock rb = recon_block(g, nvb);
-    if (rb.o >= 8 || rb.l >= g.osize[rb.o]) return;
-    const size_t nv = (size_t)g.nv, node = (size_t)g.obase[rb.o] + rb.l;
-    const int nz = g.nz, nxy = g.nx * g.ny;
-    constexpr bool F32 = sizeof(T) == 4;
-    const T xi0 = F32 ? (T)d.nt32[4 * node] : (T)d.nt64[4 * node];
-    const T xi1 = F32 ? (T)d.nt32[4 * node + 1] : (T)d.nt64[4 * node + 1];
-    const T xi2 = F32 ? (T)d.nt32[4 * node + 2] : (T)d.nt64[4 * node + 2];
-    const T idt = (T)g.inv_dt;
-    const int sz = (rb.o >> 2) & 1;   // 1: xi_z < 0, the z-upwind side is +
-    const gptr<const int> cflag = (gptr<const int>)d.cflag;
-    gptr<const T> f[NQ], lim[NQ];
-    gptr<T> out[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        f[q] = (gptr<const T>)(q ? d.f1 : d.f0);
-        lim[q] = (gptr<const T>)(q ? d.lim1 : d.lim0);
-        out[q] = (gptr<T>)(q ? d.ho1 : d.ho0);
-    }
-    // z windows: f at k-2 .. k+2, the limiter at k-1 .. k+1, fluid flags at k-2 .. k+2
-    auto row = [&](int k) -> size_t { return (size_t)(rb.col + min(max(k, 0), nz - 1) * nxy) * nv + node; };
-    auto fl = [&](int k) -> bool { return k >= 0 && k < nz && cflag[rb.col + k * nxy] != 0; };
-    T w[NQ][5], lw[NQ][3];
-    unsigned wf = 0;   // bit m: the cell at k - 2 + m is a fluid cell
-#pragma unroll
-    for (int m = 0; m < 5; ++m) wf |= (unsigned)fl(m - 2) << m;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-        for (int m = 0; m < 5; ++m) w[q][m] = f[q][row(m - 2)];
-#pragma unroll
-        for (int m = 0; m < 3; ++m) lw[q][m] = lim[q][row(m - 1)];
-    }
-    for (int k = 0; k < nz; ++k) {
-        const int cell = rb.col + k * nxy;
-        // next window entries, issued first
-        T nf[NQ], nl[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) { nf[q] = f[q][row(k + 3)]; nl[q] = lim[q][row(k + 2)]; }
-        const bool nwf = fl(k + 3);
-        const AroundXY A = around_xy(g, cflag, cell, rb.i, rb.j, rb.o);
-        if (wf & 4u) {   // uniform over the block
-            const bool hzm = (wf & 2u) != 0, hzp = (wf & 8u) != 0;
-            const bool hzuu = sz ? (hzp && (wf & 16u)) : (hzm && (wf & 1u));
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const T fc = w[q][2];
-                T vx[4], vuu[2], phup[2];
-#pragma unroll
-                for (int dir = 0; dir < 4; ++dir) vx[dir] = f[q][(size_t)A.nb[dir] * nv + node];
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    vuu[a] = f[q][(size_t)A.uu[a] * nv + node];
-                    const int s = (rb.o >> a) & 1;
-                    phup[a] = lim[q][(size_t)(s ? A.nb[2 * a + 1] : A.nb[2 * a]) * nv + node];
-                }
-                const T phic = lw[q][1];
-                T corr = axis_term<T>(rb.o & 1, xi0, (T)g.invh[0], vx[0], fc, vx[1], A.has[0], A.has[1], vuu[0],
-                                      A.huu[0], phic, phup[0]);
-                corr += axis_term<T>((rb.o >> 1) & 1, xi1, (T)g.invh[1], vx[2], fc, vx[3], A.has[2], A.has[3],
-                                     vuu[1], A.huu[1], phic, phup[1]);
-                corr += axis_term<T>(sz, xi2, (T)g.invh[2], w[q][1], fc, w[q][3], hzm, hzp,
-                                     sz ? w[q][4] : w[q][0], hzuu, phic, sz ? lw[q][2] : lw[q][0]);
-                out[q][(size_t)cell * nv + node] = idt * fc - corr;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m) w[q][m] = w[q][m + 1];
-            w[q][4] = nf[q];
-            lw[q][0] = lw[q][1];
-            lw[q][1] = lw[q][2];
-            lw[q][2] = nl[q];
-        }
-        wf = (wf >> 1) | ((unsigned)nwf << 4);
-    }
-}
-
-int recon_nvb(const Geo &g)
-{
-    int omax = 0;
-    for (int o = 0; o < 8; ++o) omax = std::max(omax, g.osize[o]);
-    return (omax + RB - 1) / RB;
 }
 
 hipError_t launch_recon(const Geo &g, const Dev &d, bool fp32, hipStream_t s)
 {
-    const int nvb = recon_nvb(g);
-    const long long nblk = (long long)g.nx * g.ny * 8 * nvb;
+    int omax = 0;
+    for (int o = 0; o < 8; ++o) omax = std::max(omax, g.osize[o]);
+    const int nvb = (omax + 63) / 64, npx = (g.nx + PX - 1) / PX, npy = (g.ny + PY - 1) / PY;
+    const long long nblk = (long long)npx * npy * 8 * nvb;
     if (nblk <= 0 || nblk > 0x7fffffffll) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)nblk), block(RB);
-    const bool dia = g.species == 1;
+    const dim3 grid((unsigned)nblk, g.species == 1 ? 2 : 1), block(256);
+    const bool mask = g.nfluid != g.ncell;
     if (fp32) {
-        if (dia) {
-            hipLaunchKernelGGL((k_recon_limiter<float, true>), grid, block, 0, s, g, d, nvb);
-            hipLaunchKernelGGL((k_recon_source<float, true>), grid, block, 0, s, g, d, nvb);
-        } else {
-            hipLaunchKernelGGL((k_recon_limiter<float, false>), grid, block, 0, s, g, d, nvb);
-            hipLaunchKernelGGL((k_recon_source<float, false>), grid, block, 0, s, g, d, nvb);
-        }
+        if (mask) hipLaunchKernelGGL((k_recon<float, true>), grid, block, 0, s, g, d, nvb, npx, npy);
+        else hipLaunchKernelGGL((k_recon<float, false>), grid, block, 0, s, g, d, nvb, npx, npy);
     } else {
-        if (dia) {
-            hipLaunchKernelGGL((k_recon_limiter<double, true>), grid, block, 0, s, g, d, nvb);
-            hipLaunchKernelGGL((k_recon_source<double, true>), grid, block, 0, s, g, d, nvb);
-        } else {
-            hipLaunchKernelGGL((k_recon_limiter<double, false>), grid, block, 0, s, g, d, nvb);
-            hipLaunchKernelGGL((k_recon_source<double, false>), grid, block, 0, s, g, d, nvb);
-        }
+        if (mask) hipLaunchKernelGGL((k_recon<double, true>), grid, block, 0, s, g, d, nvb, npx, npy);
+        else hipLaunchKernelGGL((k_recon<double, false>), grid, block, 0, s, g, d, nvb, npx, npy);
     }
     return hipGetLastError();
 }
