@@ -66,6 +66,7 @@ struct Geo {
     int ubgn;      // pairs of boundary faces
     int ucen;      // 1: centroids given (the macroscopic correction runs)
     double uhmin;  // smallest face distance h of the macroscopic pseudo time step
+    int lnx, lny, lnz, lnrun;   // sizes of the run tables (lnrun 0: none)
     // macroscopic boundary flux of the correction: 0 the Maxwellian's change,
     // 1 the Grad-13 distributions' change
     int wall_flux;
@@ -107,6 +108,10 @@ struct Dev {
     double *cfs64;     // [ncell][6] the same scale by (cell, face direction), for the sweep
     float *cfs32;
     double *lsum;      // node list: [ncell][LSUM] shape sums of the relaxation parameters (else null)
+    // node list on a box, where it falls into runs along x: the x coordinates (by
+    // weight class) and those along y and z, then per run (first x, end x, y, z) and its weight
+    double *lxt, *lyt, *lzt, *lrunw;
+    int4 *lrun;
     double *nt64;      // [nv][4] every node in the internal order: xi_x, xi_y, xi_z, weight
     float *nt32;       // [nv][4] the same in FP32
     double *xi64[3];   // per-axis nodes (tensor grid)

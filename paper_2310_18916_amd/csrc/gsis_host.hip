@@ -6,6 +6,7 @@
 #include "gsis_resid_host.h"
 
 #include <algorithm>
+#include <array>
 #include <map>
 #include <cmath>
 #include <cstdio>
@@ -24,6 +25,8 @@ struct gsis_ctx {
     bool meta_ready = false;
     std::vector<int> cflag, nbr, face_cell, face_dir, face_bc, perm;
     std::vector<double> xi[3], w[3];
+    std::vector<double> lx, ly, lz, lrunw;   // runs of a node list (build_runs)
+    std::vector<int4> lrun;
     std::vector<double> vlist;   // node list [nv][4] in the caller's order (list mode)
     // unstructured spatial mesh (g.umesh): what the sweep needs, built when the
     // mesh is set (see Dev for the meaning of each array)
@@ -286,6 +289,45 @@ void build_tiles(gsis_ctx *c)
 // octant of a node (s_a = 1 when xi_a < 0)
 int list_octant(const double *t) { return (t[0] < 0.0 ? 1 : 0) | (t[1] < 0.0 ? 2 : 0) | (t[2] < 0.0 ? 4 : 0); }
 
+// Runs of a node list: nodes of one (y, z) and weight whose x coordinates are
+// neighbours in the sorted list of that weight's x coordinates (a locally refined
+// Cartesian mesh has a list per cell size).  Kept where the shape sums over runs
+// cost less than over nodes: a run takes about as much as two nodes, a table
+// entry as four (7788 nodes in 556 runs, tables of 42 + 34 + 34: 6.9 -> 1.6 ms on
+// 96 x 64 x 64 cells; 1328 nodes in coarser ones 1.8 -> 1.2).
+void build_runs(gsis_ctx *c)
+{
+    Geo &g = c->g;
+    const double *n = c->vlist.data();
+    std::vector<std::pair<double, double>> x;   // (weight, x)
+    c->ly.clear(); c->lz.clear(); c->lx.clear(); c->lrun.clear(); c->lrunw.clear();
+    for (int k = 0; k < g.nv; ++k) {
+        x.emplace_back(n[4 * k + 3], n[4 * k]);
+        c->ly.push_back(n[4 * k + 1]);
+        c->lz.push_back(n[4 * k + 2]);
+    }
+    auto distinct = [](auto &v) { std::sort(v.begin(), v.end()); v.erase(std::unique(v.begin(), v.end()), v.end()); };
+    distinct(x); distinct(c->ly); distinct(c->lz);
+    for (const auto &p : x) c->lx.push_back(p.second);
+    g.lnx = (int)x.size(); g.lny = (int)c->ly.size(); g.lnz = (int)c->lz.size();
+    g.lnrun = 0;
+    if (std::max(g.lnx, std::max(g.lny, g.lnz)) > 512) return;
+    auto at = [](const auto &v, const auto &e) { return (int)(std::lower_bound(v.begin(), v.end(), e) - v.begin()); };
+    std::vector<std::array<int, 3>> key(g.nv);   // (z, y, x entry): the entry implies the weight
+    for (int k = 0; k < g.nv; ++k)
+        key[k] = {at(c->lz, n[4 * k + 2]), at(c->ly, n[4 * k + 1]), at(x, std::make_pair(n[4 * k + 3], n[4 * k]))};
+    std::sort(key.begin(), key.end());
+    for (int k = 0; k < g.nv; ++k) {
+        const double w = x[key[k][2]].first;
+        const bool more = k > 0 && key[k][0] == key[k - 1][0] && key[k][1] == key[k - 1][1] &&
+                          key[k][2] == key[k - 1][2] + 1 && w == c->lrunw.back();
+        if (more) { c->lrun.back().y++; continue; }
+        c->lrun.push_back(make_int4(key[k][2], key[k][2] + 1, key[k][1], key[k][0]));
+        c->lrunw.push_back(w);
+    }
+    if (2 * c->lrun.size() + 4 * (size_t)(g.lnx + g.lny + g.lnz) <= (size_t)g.nv) g.lnrun = (int)c->lrun.size();
+}
+
 // neighbour table, boundary faces, node permutation, moment vector width
 void build_meta(gsis_ctx *c)
 {
@@ -358,6 +400,7 @@ void build_meta(gsis_ctx *c)
             int kz = ((o & 4) ? 0 : g.k0[2]) + lz;
             c->perm[g.obase[o] + l] = kx + g.n1[0] * (ky + g.n1[1] * kz);
         }
+    if (g.vlist) build_runs(c);
     build_tiles(c);
     c->meta_ready = true;
 }
@@ -412,6 +455,13 @@ size_t layout(gsis_ctx *c, char *base)
     carve(off, d.cfs32, n * 6, base);
     d.lsum = nullptr;
     if (g.vlist) carve(off, d.lsum, n * LSUM, base);
+    if (g.lnrun > 0) {
+        carve(off, d.lxt, g.lnx, base);
+        carve(off, d.lyt, g.lny, base);
+        carve(off, d.lzt, g.lnz, base);
+        carve(off, d.lrun, g.lnrun, base);
+        carve(off, d.lrunw, g.lnrun, base);
+    }
     carve(off, d.nt64, nv * 4, base);
     carve(off, d.nt32, nv * 4, base);
     for (int a = 0; a < 3; ++a) {
@@ -1271,6 +1321,13 @@ gsis_status gsis_bind_workspace(gsis_ctx *ctx, void *device_ptr, size_t bytes)
             HIPCHK(ctx, up(d.xi32[a], x32.data(), g.n1[a] * sizeof(float)));
             HIPCHK(ctx, up(d.w64[a], ctx->w[a].data(), g.n1[a] * sizeof(double)));
         }
+    }
+    if (g.lnrun > 0) {
+        HIPCHK(ctx, up(d.lxt, ctx->lx.data(), g.lnx * sizeof(double)));
+        HIPCHK(ctx, up(d.lyt, ctx->ly.data(), g.lny * sizeof(double)));
+        HIPCHK(ctx, up(d.lzt, ctx->lz.data(), g.lnz * sizeof(double)));
+        HIPCHK(ctx, up(d.lrun, ctx->lrun.data(), g.lnrun * sizeof(int4)));
+        HIPCHK(ctx, up(d.lrunw, ctx->lrunw.data(), g.lnrun * sizeof(double)));
     }
     {
         // every node in the internal order: (xi_x, xi_y, xi_z, weight)

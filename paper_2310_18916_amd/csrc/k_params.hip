@@ -17,6 +17,8 @@
 #include "gsis_common.h"
 #include "gsis_launch.h"
 
+#include <algorithm>
+
 namespace gsis {
 
 __device__ void axis_central(const double *xi, const double *w, int n, double u, double T, double C[6])
@@ -344,6 +346,115 @@ __global__ __launch_bounds__(64) void k_params_list_sums(GSIS_SPAN_ARGS)
     }
 }
 
+// The same sums for a list that falls into runs along x, as locally refined
+// Cartesian meshes do.  The Maxwellian shape factors per axis, so a run's sums
+// over x of E_x c_x^p, p = 0..5, are differences of prefix sums over the x table,
+// made once per cell and shape; a lane takes a run and folds them with its y and z
+// factors into the 22 moments (1, c, c c, c c^2, c c c^2, c c^4) that the Gram
+// entries and Shakhov moments are combinations of.  One wave per cell: a cell costs
+// (x + y + z entries) exponentials instead of one per node, and the runs' folds.
+// Bound by the folds' arithmetic and the LDS reads of the prefix sums.
+template <int NSH>
+__global__ __launch_bounds__(64) void k_params_list_runs(GSIS_SPAN_ARGS)
+{
+    extern __shared__ double lds[];
+    int blk;
+    const Case &C = case_of(span_cases, span_map, blk);
+    const Geo &g = C.g;
+    const Dev &d = C.d;
+    const int cell = blk, lane = threadIdx.x;
+    CellState st;
+    if (!cell_state(g, d, cell, st)) return;   // uniform over the block
+    const int lnx = g.lnx, lny = g.lny, lnz = g.lnz, nrun = g.lnrun;
+    double *P = lds, *Y = P + 6 * (lnx + 1), *Z = Y + 2 * lny;   // P[entry][p]; Y, Z: (E, c)
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    const gptr<const i4> run = (gptr<const i4>)d.lrun;
+    const gptr<const double> runw = (gptr<const double>)d.lrunw;
+    for (int sh = 0; sh < NSH; ++sh) {
+        const double iT = 1.0 / (sh ? st.T : st.Tt);
+        auto line = [&](double c) { return exp_core(fmax(-c * c * iT, -745.0)); };
+        double carry[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        if (lane < 6) P[lane] = 0.0;
+        for (int e0 = 0; e0 < lnx; e0 += 64) {
+            const int e = e0 + lane;
+            const double c = ((gptr<const double>)d.lxt)[min(e, lnx - 1)] - st.u[0];
+            double v = e < lnx ? line(c) : 0.0;
+#pragma unroll
+            for (int p = 0; p < 6; ++p) {
+                double s = v;
+#pragma unroll
+                for (int m = 1; m < 64; m <<= 1) {
+                    const double t = __shfl_up(s, m, 64);
+                    if (lane >= m) s += t;
+                }
+                s += carry[p];
+                if (e < lnx) P[6 * (e + 1) + p] = s;
+                carry[p] = __shfl(s, 63, 64);
+                v *= c;
+            }
+        }
+        for (int e = lane; e < lny; e += 64) {
+            const double c = ((gptr<const double>)d.lyt)[e] - st.u[1];
+            Y[2 * e] = line(c);
+            Y[2 * e + 1] = c;
+        }
+        for (int e = lane; e < lnz; e += 64) {
+            const double c = ((gptr<const double>)d.lzt)[e] - st.u[2];
+            Z[2 * e] = line(c);
+            Z[2 * e + 1] = c;
+        }
+        __syncthreads();
+        double m[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) m[k] = 0.0;
+        for (int r = lane; r < nrun; r += 64) {
+            const i4 R = run[r];
+            const double y = Y[2 * R.z + 1], z = Z[2 * R.w + 1], f = runw[r] * (Y[2 * R.z] * Z[2 * R.w]);
+            double s[6];
+#pragma unroll
+            for (int p = 0; p < 6; ++p) s[p] = f * (P[6 * R.y + p] - P[6 * R.x + p]);
+            const double q = fma(y, y, z * z);
+            // sums of x^p c^2, and of x^p c^4 for p = 0, 1
+            const double a0 = fma(q, s[0], s[2]), a1 = fma(q, s[1], s[3]), a2 = fma(q, s[2], s[4]), a3 = fma(q, s[3], s[5]);
+            const double h0 = fma(q, a0, a2), h1 = fma(q, a1, a3);
+            const double ys = y * s[0], zs = z * s[0], ya = y * a0, za = z * a0;
+            m[0] += s[0];
+            m[1] += s[1]; m[2] += ys; m[3] += zs;
+            m[4] += s[2]; m[5] = fma(y, ys, m[5]); m[6] = fma(z, zs, m[6]);
+            m[7] = fma(y, s[1], m[7]); m[8] = fma(z, s[1], m[8]); m[9] = fma(y, zs, m[9]);
+            m[10] += a1; m[11] += ya; m[12] += za;
+            m[13] += a2; m[14] = fma(y, ya, m[14]); m[15] = fma(z, za, m[15]);
+            m[16] = fma(y, a1, m[16]); m[17] = fma(z, a1, m[17]); m[18] = fma(y, za, m[18]);
+            m[19] += h1; m[20] = fma(y, h0, m[20]); m[21] = fma(z, h0, m[21]);
+        }
+        __syncthreads();   // the tables are free
+        int idx;
+        const double t = wave_reduce_scatter<32>(m, lane, &idx);
+        if ((lane & 1) == 0) lds[idx] = t;
+        __syncthreads();
+        if (lane == 0) {
+            const double *M = lds;
+            const double *qp = sh ? st.qpr : st.qpt;
+            const gptr<double> out = (gptr<double>)d.lsum + (size_t)cell * LSUM + sh * LSUM_SHAPE;
+            const double tr = M[4] + M[5] + M[6];
+            const double G[15] = {M[0], M[1], M[2], M[3], tr, M[4], M[7], M[8], M[10], M[5], M[9], M[11],
+                                  M[6], M[12], M[13] + M[14] + M[15]};
+#pragma unroll
+            for (int k = 0; k < 15; ++k) out[k] = G[k];
+            // E (1 + qp . c (c^2 / T - 5/2)) against 1, c, c^2
+            auto shak = [&](double base, double h0, double h1, double h2, double l0, double l1, double l2) {
+                return base + (qp[0] * (h0 * iT - 2.5 * l0) + qp[1] * (h1 * iT - 2.5 * l1) + qp[2] * (h2 * iT - 2.5 * l2));
+            };
+            out[15] = shak(M[0], M[10], M[11], M[12], M[1], M[2], M[3]);
+            out[16] = shak(M[1], M[13], M[16], M[17], M[4], M[7], M[8]);
+            out[17] = shak(M[2], M[16], M[14], M[18], M[7], M[5], M[9]);
+            out[18] = shak(M[3], M[17], M[18], M[15], M[8], M[9], M[6]);
+            out[19] = shak(tr, M[19], M[20], M[21], M[10], M[11], M[12]);
+        }
+        __syncthreads();
+    }
+}
+
 __global__ __launch_bounds__(64) void k_params_list_finish(GSIS_SPAN_ARGS)
 {
     int blk;
@@ -401,8 +512,13 @@ __global__ __launch_bounds__(256) void k_face_scale(GSIS_SPAN_ARGS)
 hipError_t launch_params(const Target &t, hipStream_t s)
 {
     if (t.vlist) {
-        const dim3 grid(t.host[0].g.ncell);
-        if (t.dia) hipLaunchKernelGGL(k_params_list_sums<2>, grid, dim3(64), 0, s, GSIS_SPAN(t.span(K_CELL1)));
+        const Geo &g = t.host[0].g;
+        const dim3 grid(g.ncell);
+        if (g.lnrun > 0) {
+            const size_t lds = std::max(32, 6 * (g.lnx + 1) + 2 * (g.lny + g.lnz)) * sizeof(double);
+            if (t.dia) hipLaunchKernelGGL(k_params_list_runs<2>, grid, dim3(64), lds, s, GSIS_SPAN(t.span(K_CELL1)));
+            else hipLaunchKernelGGL(k_params_list_runs<1>, grid, dim3(64), lds, s, GSIS_SPAN(t.span(K_CELL1)));
+        } else if (t.dia) hipLaunchKernelGGL(k_params_list_sums<2>, grid, dim3(64), 0, s, GSIS_SPAN(t.span(K_CELL1)));
         else hipLaunchKernelGGL(k_params_list_sums<1>, grid, dim3(64), 0, s, GSIS_SPAN(t.span(K_CELL1)));
         hipLaunchKernelGGL(k_params_list_finish, dim3(t.nblk[K_CELL64]), dim3(64), 0, s, GSIS_SPAN(t.span(K_CELL64)));
         return hipGetLastError();
