@@ -26,7 +26,8 @@ namespace gsis {
 //
 // The order of a cell's sum depends on the octant's size alone, whoever forms
 // it: MCHUNK = 64 consecutive nodes are one chunk, multiplied in 16 products
-// of v_mfma_f64_16x16x4 (product t takes nodes 16 q + t, q = 0..3); four
+// of v_mfma_f64_16x16x4 (product t takes nodes 16 q + t, q = 0..3; even and odd
+// ones are summed apart, which halves the length of the chain); four
 // chunks are a segment, (c0 + c1) + (c2 + c3), a missing one zero; segments
 // are added in order.  The sweep forms the segments of its tiles while the
 // values are in registers (k_sweep), and k_moment_totals adds them up;
@@ -115,9 +116,9 @@ __global__ __launch_bounds__(64) void k_moments(GSIS_SPAN_ARGS)
             else if (n0 + NCH * MCHUNK < n) load(0, n0 + NCH * MCHUNK);
 #pragma unroll
             for (int h = 0; h < NCH; ++h) {
-                d4 acc[G];
+                d4 acc[2][G];
 #pragma unroll
-                for (int k = 0; k < G; ++k) acc[k] = d4{0.0, 0.0, 0.0, 0.0};
+                for (int k = 0; k < G; ++k) acc[0][k] = acc[1][k] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
                 for (int s = 0; s < 16; s += V) {
                     vec a[G];
@@ -131,17 +132,18 @@ __global__ __launch_bounds__(64) void k_moments(GSIS_SPAN_ARGS)
                         const double m = mono(t0.x, t0.y, t1.x, t1.y);
 #pragma unroll
                         for (int k = 0; k < G; ++k)
-                            acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[k][e], m, acc[k], 0, 0, 0);
+                            acc[e & 1][k] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[k][e], m, acc[e & 1][k], 0, 0, 0);
                     }
                 }
                 const int c = (n0 / MCHUNK + h) & 3;   // uniform
                 const bool last = n0 + (h + 1) * MCHUNK >= n;
 #pragma unroll
                 for (int k = 0; k < G; ++k) {
-                    if (c == 0) seg[d][k] = acc[k];
-                    else if (c == 1) seg[d][k] += acc[k];
-                    else if (c == 2) pair[d][k] = acc[k];
-                    else pair[d][k] += acc[k];
+                    const d4 p = acc[0][k] + acc[1][k];
+                    if (c == 0) seg[d][k] = p;
+                    else if (c == 1) seg[d][k] += p;
+                    else if (c == 2) pair[d][k] = p;
+                    else pair[d][k] += p;
                     if (c == 3 || last) {
                         tot[d][k] += seg[d][k] + (c < 2 ? d4{0.0, 0.0, 0.0, 0.0} : pair[d][k]);
                     }

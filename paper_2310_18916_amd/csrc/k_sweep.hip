@@ -325,7 +325,7 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
     constexpr int V = 16 / (int)sizeof(T);
     typedef T vec __attribute__((ext_vector_type(V)));
     vec areg[SUM ? 16 / V : 1];   // 16 nodes of one cell per lane
-    d4 prod = d4{0.0, 0.0, 0.0, 0.0};
+    d4 prod[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};   // even and odd products of a chunk
 #pragma unroll
     for (int k = 0; k < (SUM ? 16 / V : 0); ++k) areg[k] = vec(T(0));
     auto fetch = [&]() {
@@ -337,16 +337,17 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
     };
     auto multiply = [&](int k) {
         const double m = BLDS ? smono[mw][BLDS ? k * 64 + lane : 0] : bmono[SUM && !BLDS ? k : 0];
-        prod = __builtin_amdgcn_mfma_f64_16x16x4f64((double)areg[SUM ? k / V : 0][k % V], m,
-                                                    k == 0 ? d4{0.0, 0.0, 0.0, 0.0} : prod, 0, 0, 0);
+        prod[k & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)areg[SUM ? k / V : 0][k % V], m,
+                                                           k < 2 ? d4{0.0, 0.0, 0.0, 0.0} : prod[k & 1], 0, 0, 0);
     };
     // lane l of a product holds sum (l & 15) of cells 4 r + (l >> 4), r = 0..3
     auto hand = [&](int par, int slot, int d) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = 4 * r + (lane >> 4), col = lane & 15;
-            if (d == 0) sprod[par][slot][mw][SUM ? row * 16 + col : 0] = prod[r];
-            else if (col < 4) sprod1[SUM && DIA ? par : 0][slot][mw][SUM && DIA ? row * 4 + col : 0] = prod[r];
+            const double p = prod[0][r] + prod[1][r];
+            if (d == 0) sprod[par][slot][mw][SUM ? row * 16 + col : 0] = p;
+            else if (col < 4) sprod1[SUM && DIA ? par : 0][slot][mw][SUM && DIA ? row * 4 + col : 0] = p;
         }
     };
     // the block's sums of the 16 cells of a group, base the cell at its slab's
