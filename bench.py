@@ -70,6 +70,14 @@ SWEEP_SOURCES = ("paper_2310_18916_amd/csrc/k_sweep.hip", "paper_2310_18916_amd/
                  "paper_2310_18916_amd/csrc/gsis_sweep_math.h")
 
 
+def moment_read_gbs(nbytes, ms):
+    """Rate at which the moment phase read the VDF; None where it did not: the sweep
+    of a large state forms the sums and the phase adds up its segments, in less time
+    than reading at the HBM peak would take."""
+    gbs = nbytes / (ms * 1e-3) / 1e9
+    return gbs if gbs <= HBM_PEAK_GBS else None
+
+
 def sweep_traffic(dtype, tile, workload_name):
     """HBM bytes per sweep pass from the committed rocprofv3 counter summary, or
     None when that summary was taken on other kernel sources or has no entry
@@ -192,16 +200,16 @@ def second_order(case, k, steps, warmup, macro, out, converge_too=True):
         esz = 8 if dt == "fp64" else 4
         rec_ms, rec_n = prof["recon"]
         sw_ms, sw_n = prof["sweep"]
-        recon_gbs = pts * nvdf * esz * 5 / (rec_ms / rec_n * 1e-3) / 1e9
+        recon_gbs = pts * nvdf * esz * 2 / (rec_ms / rec_n * 1e-3) / 1e9   # read f^n, write the term
         res[dt] = {"value": pts * steps / r["seconds"], "ms_per_step": r["seconds"] / steps * 1e3,
                    "sweep_tile": r["tile"], "phases_ms_per_step": {kk: v[0] / steps for kk, v in prof.items()},
                    "recon_gbs": recon_gbs,
                    "sweep_gbs": pts * nvdf * esz * 2 / (sw_ms / sw_n * 1e-3) / 1e9,
-                   # the dominant phase of a second-order pass: limiter + source, per pass
-                   "roofline": {"bound": "hbm", "kernel": "k_recon_limiter + k_recon_source",
+                   # the dominant phase of a second-order pass, per pass
+                   "roofline": {"bound": "hbm", "kernel": "k_recon",
                                 "achieved": recon_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                 "frac": recon_gbs / HBM_PEAK_GBS, "traffic": None,
-                                "algorithmic_bytes": pts * nvdf * esz * 5}}
+                                "algorithmic_bytes": pts * nvdf * esz * 2}}
         del r
     if converge_too and case.gsis:
         c1st, m1st = converge(case, "fp64", out["sweep_tile"], full=False)
@@ -428,7 +436,7 @@ def refined_mesh(steps, warmup):
         res[dtype] = {"value": pts * steps / r["seconds"], "ms_per_pass": r["seconds"] / steps * 1e3,
                       "phases_ms_per_pass": {k: v[0] / steps for k, v in prof.items() if v[1]},
                       "sweep_gbs": pts * esz / (sweep_ms / n * 1e-3) / 1e9,
-                      "moments_gbs": pts * esz / (mom_ms / n * 1e-3) / 1e9, "sweep_tile": r["tile"]}
+                      "moments_gbs": moment_read_gbs(pts * esz, mom_ms / n), "sweep_tile": r["tile"]}
         del r
         torch.cuda.empty_cache()
     return res
@@ -507,7 +515,7 @@ def main():
     sweep_bytes = pts * nvdf * esz * (2 if case.inv_dt != 0 else 1)   # write f^{n+1/2} (+ read f^n if 1/dt != 0)
     mom_bytes = pts * nvdf * esz                                       # read f^{n+1/2}
     sweep_gbs = sweep_bytes / (sweep_ms / sweep_n * 1e-3) / 1e9
-    mom_gbs = mom_bytes / (mom_ms / mom_n * 1e-3) / 1e9
+    mom_gbs = moment_read_gbs(mom_bytes, mom_ms / mom_n)
     dominant = "sweep" if sweep_ms >= mom_ms else "moments"
     ach = sweep_gbs if dominant == "sweep" else mom_gbs
     traffic = sweep_traffic(dtype, r["tile"], a.workload) if dominant == "sweep" else None
@@ -539,7 +547,7 @@ def main():
                      "algorithmic_bytes": sweep_bytes if dominant == "sweep" else mom_bytes},
         "phases_ms_per_step": {k: v[0] / steps for k, v in prof.items()},
         "kinetic_only_updates_per_s": pts * steps / ((prof["prep"][0] + sweep_ms + mom_ms) * 1e-3),
-        "kinetic_pass_gbs": (sweep_bytes + mom_bytes) / ((sweep_ms + mom_ms) / sweep_n * 1e-3) / 1e9,
+        "kinetic_pass_gbs": (sweep_bytes + (mom_bytes if mom_gbs else 0)) / ((sweep_ms + mom_ms) / sweep_n * 1e-3) / 1e9,
         "sweep_gbs": sweep_gbs,
         "moments_gbs": mom_gbs,
         "final_eps": eps_head,

@@ -301,17 +301,17 @@ void build_runs(gsis_ctx *c)
     const double *n = c->vlist.data();
     std::vector<std::pair<double, double>> x;   // (weight, x)
     c->ly.clear(); c->lz.clear(); c->lx.clear(); c->lrun.clear(); c->lrunw.clear();
-    for (int k = 0; k < g.nv; ++k) {
-        x.emplace_back(n[4 * k + 3], n[4 * k]);
-        c->ly.push_back(n[4 * k + 1]);
-        c->lz.push_back(n[4 * k + 2]);
-    }
-    auto distinct = [](auto &v) { std::sort(v.begin(), v.end()); v.erase(std::unique(v.begin(), v.end()), v.end()); };
-    distinct(x); distinct(c->ly); distinct(c->lz);
+    g.lnrun = 0;
+    // sorted distinct values, given up beyond 512 (a list without a lattice)
+    auto add = [](auto &v, const auto &e) -> bool {
+        const auto it = std::lower_bound(v.begin(), v.end(), e);
+        if (it == v.end() || *it != e) v.insert(it, e);
+        return v.size() <= 512;
+    };
+    for (int k = 0; k < g.nv; ++k)
+        if (!add(x, std::make_pair(n[4 * k + 3], n[4 * k])) || !add(c->ly, n[4 * k + 1]) || !add(c->lz, n[4 * k + 2])) return;
     for (const auto &p : x) c->lx.push_back(p.second);
     g.lnx = (int)x.size(); g.lny = (int)c->ly.size(); g.lnz = (int)c->lz.size();
-    g.lnrun = 0;
-    if (std::max(g.lnx, std::max(g.lny, g.lnz)) > 512) return;
     auto at = [](const auto &v, const auto &e) { return (int)(std::lower_bound(v.begin(), v.end(), e) - v.begin()); };
     std::vector<std::array<int, 3>> key(g.nv);   // (z, y, x entry): the entry implies the weight
     for (int k = 0; k < g.nv; ++k)
@@ -328,7 +328,7 @@ void build_runs(gsis_ctx *c)
     if (2 * c->lrun.size() + 4 * (size_t)(g.lnx + g.lny + g.lnz) <= (size_t)g.nv) g.lnrun = (int)c->lrun.size();
 }
 
-// neighbour table, boundary faces, node permutation, moment vector width
+// neighbour table, boundary faces, node permutation
 void build_meta(gsis_ctx *c)
 {
     Geo &g = c->g;
