@@ -37,15 +37,16 @@ namespace gsis {
 // k_moments: lane l of a product supplies f(cell l & 15, node 16 (l >> 4) + t)
 // and monomial l & 15 of that node.  A block is one wave for 16 G cells of one
 // octant; its loads take whole stretches of 1 / G KB of a row and pass through
-// LDS, the next chunk's in flight while one is multiplied.  Bound by reading
-// the VDF once in FP64: 12.6 ms for 75.5 GB (64 x 48 x 48 cells, 40^3 nodes), 6.0
-// TB/s; in FP32 by the products' LDS reads, 10.9 ms for 51.5 GB.  (Sums along
-// the rows of the tensor grid with a reduction over lanes read 6.8 and 5.8 TB/s,
-// but in an order that the sweep can't form; with the segments in the sweep
-// this kernel runs for small states, where both take 0.03 to 0.05 ms, and once
-// when a state is set.)
+// LDS, the next chunk's in flight while one is multiplied.  One VDF is held to two
+// waves per SIMD (286 registers otherwise: 15.1 against 11.4 ms in FP32); two VDFs
+// spill 400 bytes there (9.8 against 6.0 ms).  Bound by reading the VDF in FP64:
+// 11.7 ms for 75.5 GB (64 x 48 x 48 cells, 40^3 nodes), 6.4 TB/s; in FP32 by the
+// products' LDS reads, 11.4 ms for 51.5 GB.  (Sums along the rows of the tensor
+// grid with a reduction over lanes read 6.8 and 5.8 TB/s, but in an order that the
+// sweep can't form; with the segments in the sweep this kernel runs for small
+// states, where both take 0.03 to 0.05 ms, and once when a state is set.)
 template <typename T, bool DIA>
-__global__ __launch_bounds__(64) void k_moments(GSIS_SPAN_ARGS)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIA ? 1 : 2))) void k_moments(GSIS_SPAN_ARGS)
 {
     typedef double d4 __attribute__((ext_vector_type(4)));
     typedef double d2 __attribute__((ext_vector_type(2)));

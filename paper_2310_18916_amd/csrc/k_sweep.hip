@@ -637,8 +637,9 @@ static const Shape *find_shape(bool fp32, int tx, int ty)
 template <typename T, int TX, int TY, int WX, int WY, bool SUM>
 static void sweep_launch(const Target &t, int p, hipStream_t s, unsigned nblk, bool mask, int eoff)
 {
-    constexpr bool kDia = TX * TY <= 32;   // two register planes only for the small slabs
-    constexpr bool kMono = !SUM || TX * TY == 16;
+    // two register planes only for the small slabs
+    constexpr bool kDia = TX * TY <= 32 && !(SUM && TX == 8 && sizeof(T) == 4);
+    constexpr bool kMono = !(SUM && TX == 8 && sizeof(T) == 8);
     const dim3 grid(nblk);
     const Span sp{t.cases, t.pmap ? t.pmap[p] : nullptr};
 #define GSIS_SWEEP(D, R, M) \
@@ -696,13 +697,14 @@ int sweep_shapes(bool fp32, int *out, int max)
     return n;
 }
 
-// Four waves over the nodes of a 4 x 4 tile make a segment; so do those of the
-// 8 x 4 tile where its larger slab is the faster one (FP64, two VDFs: 19.7 + 0.5
-// ms against 20.1 + 0.5 on 64 x 48 x 48 cells x 24^3 nodes; FP32: 24.0 against
-// 22.0 on 96 x 64 x 64 x 32^3).
+// Four waves over the nodes of a 4 x 4 tile make a segment, and of an 8 x 4 tile in
+// FP64 with two VDFs (19.7 + 0.5 ms against 20.1 + 0.5 for 4 x 4 on 64 x 48 x 48 cells
+// x 24^3 nodes) and in FP32 with one (24.0 + 1.5 against 16.4 + 10.9 with the sums
+// apart, on 96 x 64 x 64 x 32^3).  FP64 with one gains nothing from it (38.7 + 1.0
+// against 27.5 + 12.6 on 64 x 48 x 48 x 40^3).
 bool sweep_forms_sums(const Target &t)
 {
-    return t.mseg && t.bs == 256 && t.ty == 4 && (t.tx == 4 || (t.dia && !t.fp32));
+    return t.mseg && t.bs == 256 && t.ty == 4 && (t.tx == 4 || t.dia != t.fp32);
 }
 
 hipError_t launch_sweep(const Target &t, hipStream_t s)
@@ -714,7 +716,8 @@ hipError_t launch_sweep(const Target &t, hipStream_t s)
     for (int p = 0; p < t.nplane; ++p) {
         if (t.npblk[p] == 0) continue;
         if (sweep_forms_sums(t)) {
-            if (t.fp32) sweep_plane<float, 4, 4, 1, 1, true>(t, p, s);
+            if (t.fp32 && tx == 8) sweep_plane<float, 8, 4, 1, 1, true>(t, p, s);
+            else if (t.fp32) sweep_plane<float, 4, 4, 1, 1, true>(t, p, s);
             else if (tx == 4) sweep_plane<double, 4, 4, 1, 1, true>(t, p, s);
             else sweep_plane<double, 8, 4, 1, 1, true>(t, p, s);
         } else if (t.fp32) {

@@ -48,6 +48,7 @@ CASES = {
     "whole": (lambda: box((4, 4, 4), (88, 96, 96)), "fp64"),
     "over": (lambda: box((5, 4, 3), (90, 89, 91)), "fp64"),
     "over_fp32": (lambda: box((5, 9, 3), (90, 89, 91)), "fp32"),
+    "over_fp32_8x4": (lambda: box((11, 5, 9), (60, 61, 59)), "fp32"),
     "thin": (lambda: box((1, 1, 29), (118, 97, 102)), "fp64"),
     "few_nodes": (lambda: box((83, 81, 82), (4, 4, 4)), "fp64"),
     "term": (lambda: box((5, 4, 3), (90, 89, 91), inv_dt=3.0), "fp64"),
@@ -77,7 +78,7 @@ def test_segments(name):
     print(name, case.nx, case.ny, case.nz, case.nv, dtype, flush=True)
     esz = 8 if dtype == "fp64" else 4
     assert case.ncell * case.nvel * esz * (2 if case.species == I.DIATOMIC else 1) > 256e6
-    s = run(case, dtype, None)
+    s = run(case, dtype, (8, 4, 8, 256) if name.endswith("8x4") else None)
     assert s.get_tile()[3] == 256
     a = s.moments()
     live = np.ones(case.ncell, bool) if case.solid is None else np.asarray(case.solid).reshape(-1) == 0
