@@ -110,7 +110,7 @@ bool forms_sums(const gsis_ctx *const *cs, size_t nc)
         double seg = 0;
         for (int o = 0; o < 8; ++o) seg += (g.osize[o] + MSEG - 1) / MSEG;
         bytes += vdf_bytes(cs[k]);
-        all += vdf_bytes(cs[k]) * (g.order == 2 ? 2 : 1) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
+        all += vdf_bytes(cs[k]) * (g.order == 2 ? 3 : 1) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
     }
     return !g0.umesh && all <= 240e9 && bytes > 256e6;
 }
@@ -420,16 +420,24 @@ size_t layout(gsis_ctx *c, char *base)
     d.rs0 = f0;
     d.rs1 = f1;
     d.ho0 = d.ho1 = nullptr;
+    char *l0 = nullptr, *l1 = nullptr;   // order 2: one more buffer per VDF
     if (g.order == 2) {
         char *h0 = nullptr, *h1 = nullptr;
         carve(off, h0, (n + 1) * nv * esz, base);
-        if (g.species == 1) carve(off, h1, (n + 1) * nv * esz, base);
+        carve(off, l0, n * nv * esz, base);
+        if (g.species == 1) {
+            carve(off, h1, (n + 1) * nv * esz, base);
+            carve(off, l1, n * nv * esz, base);
+        }
         d.ho0 = h0; d.ho1 = h1;
         d.rs0 = h0; d.rs1 = h1;
     }
     carve(off, d.mom8, n * 8 * NRS, base);
     d.mseg = d.mseg1 = nullptr;
-    if (c->segments) {
+    if (c->segments && g.order == 2 && (size_t)g.oseg[8] * 16 * sizeof(double) <= nv * esz) {
+        d.mseg = (double *)l0;   // the second-order term needs no buffer but ho0, ho1
+        d.mseg1 = (double *)l1;
+    } else if (c->segments) {
         carve(off, d.mseg, n * g.oseg[8] * 16, base);
         if (g.species == 1) carve(off, d.mseg1, n * g.oseg[8] * 4, base);
     }
