@@ -287,6 +287,11 @@ gsis_status gsis_set_tile(gsis_ctx *ctx, int tx, int ty, int tz, int block);
 /* Current sweep configuration (tx, ty, tz, block) into tile[4]. */
 gsis_status gsis_get_tile(const gsis_ctx *ctx, int *tile);
 
+/* *forms = 1 where the sweep of a kinetic pass also forms the moment sums under
+ * the current configuration, 0 where they are summed from the stored VDF (the
+ * result is the same to the bit).  ESTATE before gsis_bind_workspace. */
+gsis_status gsis_forms_sums(const gsis_ctx *ctx, int *forms);
+
 /* Autotuner: performs the next kinetic pass, running its sweep reps >= 1 times
  * under every compiled (tx, ty) tile shape, tile depths tz in {tx/2, tx, 2 tx}
  * and blocks of 128 and 256 threads, timed with HIP events; selects the

@@ -1791,6 +1791,14 @@ gsis_status gsis_get_tile(const gsis_ctx *ctx, int *tile)
     return GSIS_OK;
 }
 
+gsis_status gsis_forms_sums(const gsis_ctx *ctx, int *forms)
+{
+    if (!ctx || !forms) return GSIS_EINVAL;
+    if (!ctx->bound) return GSIS_ESTATE;
+    *forms = !ctx->g.umesh && sweep_forms_sums(target_of(ctx));
+    return GSIS_OK;
+}
+
 gsis_status gsis_tile_shapes(int *out, int max, int *count)
 {
     if (!out || !count || max < 0) return GSIS_EINVAL;

@@ -152,6 +152,12 @@ class Solver(Context):
         self._check(self.L.gsis_get_tile(self.h, t), "gsis_get_tile")
         return tuple(t)
 
+    def forms_sums(self) -> bool:
+        """Whether the sweep of a pass also forms the moment sums."""
+        n = C.c_int()
+        self._check(self.L.gsis_forms_sums(self.h, C.byref(n)), "gsis_forms_sums")
+        return bool(n.value)
+
     def autotune(self, reps: int = 2):
         """Time the next pass's sweep under every compiled configuration and keep the
         fastest; returns [((tx, ty, tz, block), ms), ...]."""
