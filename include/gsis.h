@@ -199,7 +199,15 @@ gsis_status gsis_set_boundary(gsis_ctx *ctx, int face, int kind, const double u[
  * ESTATE once bound. */
 gsis_status gsis_set_wall_flux(gsis_ctx *ctx, int model);
 
-/* Bytes of device workspace the context needs (after the mask is set). */
+/* lean != 0 leaves out of the workspace what only saves time: of a VDF above
+ * 256 MB the segments of the moment sums (6 to 20% of it), with order 2 one array
+ * of the VDF's size per VDF.  Results are the same to the bit.  Default 0; must
+ * precede gsis_workspace_size and gsis_bind_workspace (in a batch its own calls);
+ * ESTATE once bound. */
+gsis_status gsis_set_lean(gsis_ctx *ctx, int lean);
+
+/* Bytes of device workspace the context needs (after the mask, and a caller's own
+ * sweep tile, are set: a tile that forms no moment sums needs no segments). */
 gsis_status gsis_workspace_size(const gsis_ctx *ctx, size_t *bytes);
 
 /* Bind caller-owned device memory (>= gsis_workspace_size bytes, 256-byte

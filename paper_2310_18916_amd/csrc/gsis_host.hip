@@ -35,7 +35,9 @@ struct gsis_ctx {
     std::vector<int> ucf_face, uf_cell, ucf_first, ubf_face;
     std::vector<int> ubg, ubgd, ubr, ubro;   // ubg, ubr: 2 ints per pair and run
     int tx = 0, ty = 0, tz = 0, bs = 0;
-    bool segments = false;   // the workspace holds the segments of the moment sums
+    bool segments = false;   // the sweep's tile forms the moment sums, and the workspace holds their segments
+    bool lean = false;       // gsis_set_lean: no segments, no spare array
+    bool in_batch = false;   // the batch decides on the segments
     bool tile_auto = true;   // the built-in choice (until gsis_set_tile or the autotuner names one)
     std::vector<int> tiles, plane_off, plane_cnt, npblk;
     std::vector<int> tent, nclean;   // split sweep entries (cases with solid cells)
@@ -100,7 +102,7 @@ double vdf_bytes(const gsis_ctx *c)
 // x 40^3; FP32 0.20 and 0.17, 0.48 and 0.50, 2.3 and 2.65; with
 // a finite time step, FP64, 0.90 and 1.06 on 24^3 x 20^3.  The segments take 6% of
 // an FP64 VDF, 12% of an FP32 one; not where that would leave no room on a 288 GB
-// card.
+// card.  The second order keeps them in an array that it has.
 bool forms_sums(const gsis_ctx *const *cs, size_t nc)
 {
     const Geo &g0 = cs[0]->g;
@@ -110,9 +112,18 @@ bool forms_sums(const gsis_ctx *const *cs, size_t nc)
         double seg = 0;
         for (int o = 0; o < 8; ++o) seg += (g.osize[o] + MSEG - 1) / MSEG;
         bytes += vdf_bytes(cs[k]);
-        all += vdf_bytes(cs[k]) * (g.order == 2 ? 3 : 1) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
+        all += vdf_bytes(cs[k]) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
     }
-    return !g0.umesh && all <= 240e9 && bytes > 256e6;
+    return !g0.umesh && (g0.order == 2 || all <= 240e9) && bytes > 256e6;
+}
+
+// Room for the segments: where the sweep's tile fills them.  A caller's own tile
+// that doesn't form sums needs none.  The second order has it anyway.  Decided
+// once, before a caller is told the size.
+void choose_segments(gsis_ctx *c)
+{
+    c->segments = forms_sums(&c, 1) &&
+                  (c->g.order == 2 || tile_forms_sums(c->fp32, c->g.species == GSIS_DIATOMIC, c->tx, c->ty, c->bs));
 }
 
 // The built-in sweep tile of one case, or of the average case of a batch.
@@ -350,8 +361,8 @@ void build_meta(gsis_ctx *c)
     }
     g.oseg[0] = 0;
     for (int o = 0; o < 8; ++o) g.oseg[o + 1] = g.oseg[o] + (g.osize[o] + MSEG - 1) / MSEG;
-    c->segments = forms_sums(&c, 1);   // the velocity set is final now
-    if (c->tile_auto) default_tile(c);
+    if (c->tile_auto) default_tile(c);   // the velocity set is final now
+    if (!c->in_batch) choose_segments(c);
     if (c->mask.empty()) c->mask.assign(n, 0);
     c->cflag.assign(n, 0);
     c->nbr.assign((size_t)n * 6, 0);
@@ -405,6 +416,8 @@ void build_meta(gsis_ctx *c)
     c->meta_ready = true;
 }
 
+bool holds_segments(const gsis_ctx *c) { return c->segments && !c->lean; }
+
 // Layout of the workspace; with base == nullptr only the size is computed.
 size_t layout(gsis_ctx *c, char *base)
 {
@@ -420,24 +433,24 @@ size_t layout(gsis_ctx *c, char *base)
     d.rs0 = f0;
     d.rs1 = f1;
     d.ho0 = d.ho1 = nullptr;
-    char *l0 = nullptr, *l1 = nullptr;   // order 2: one more buffer per VDF
+    char *l0 = nullptr, *l1 = nullptr;   // order 2: a spare array per VDF
     if (g.order == 2) {
         char *h0 = nullptr, *h1 = nullptr;
         carve(off, h0, (n + 1) * nv * esz, base);
-        carve(off, l0, n * nv * esz, base);
+        if (!c->lean) carve(off, l0, n * nv * esz, base);
         if (g.species == 1) {
             carve(off, h1, (n + 1) * nv * esz, base);
-            carve(off, l1, n * nv * esz, base);
+            if (!c->lean) carve(off, l1, n * nv * esz, base);
         }
         d.ho0 = h0; d.ho1 = h1;
         d.rs0 = h0; d.rs1 = h1;
     }
     carve(off, d.mom8, n * 8 * NRS, base);
     d.mseg = d.mseg1 = nullptr;
-    if (c->segments && g.order == 2 && (size_t)g.oseg[8] * 16 * sizeof(double) <= nv * esz) {
+    if (holds_segments(c) && g.order == 2 && (size_t)g.oseg[8] * 16 * sizeof(double) <= nv * esz) {
         d.mseg = (double *)l0;   // the second-order term needs no buffer but ho0, ho1
         d.mseg1 = (double *)l1;
-    } else if (c->segments) {
+    } else if (holds_segments(c)) {
         carve(off, d.mseg, n * g.oseg[8] * 16, base);
         if (g.species == 1) carve(off, d.mseg1, n * g.oseg[8] * 4, base);
     }
@@ -543,6 +556,16 @@ size_t layout(gsis_ctx *c, char *base)
     return align256(off);
 }
 
+// Bytes of the workspace, as a bind would carve it.
+size_t space(gsis_ctx *c)
+{
+    const Dev d = c->d;
+    Case *const dcase = c->dcase;
+    const size_t n = layout(c, nullptr);
+    c->d = d;
+    c->dcase = dcase;
+    return n;
+}
 
 // The launch target of this context alone.
 Target target_of(const gsis_ctx *c)
@@ -559,7 +582,7 @@ Target target_of(const gsis_ctx *c)
     t.mask = c->g.nfluid != c->g.ncell;
     t.rfn = c->g.inv_dt != 0.0 || c->g.order == 2;
     t.vlist = c->g.vlist != 0;
-    t.mseg = c->segments;
+    t.mseg = holds_segments(c);
     t.g13 = c->g.wall_flux == GSIS_WALLFLUX_G13;
     if (!c->nclean.empty()) {
         t.nclean = c->nclean.data();
@@ -1279,9 +1302,15 @@ gsis_status gsis_workspace_size(const gsis_ctx *cctx, size_t *bytes)
     gsis_ctx *ctx = const_cast<gsis_ctx *>(cctx);
     if (!ctx || !bytes) return GSIS_EINVAL;
     if (!ctx->meta_ready) build_meta(ctx);
-    Dev save = ctx->d;
-    *bytes = layout(ctx, nullptr);
-    ctx->d = save;
+    *bytes = space(ctx);
+    return GSIS_OK;
+}
+
+gsis_status gsis_set_lean(gsis_ctx *ctx, int lean)
+{
+    if (!ctx) return GSIS_EINVAL;
+    if (ctx->bound) return fail(ctx, GSIS_ESTATE, "set_lean must precede bind_workspace");
+    ctx->lean = lean != 0;
     return GSIS_OK;
 }
 
@@ -1879,6 +1908,7 @@ struct gsis_batch {
     std::vector<gsis_ctx *> cs;
     hipStream_t stream = nullptr;
     bool bound = false, inited = false;
+    bool sized = false;            // a caller was told the workspace size
     bool fp32 = false, dia = false;
     int tx = 4, ty = 4, tz = 4, bs = 128;
     char *ws = nullptr;
@@ -1957,11 +1987,7 @@ size_t batch_layout(gsis_batch *b, char *base)
     for (size_t c = 0; c < nc; ++c) {
         off = align256(off);
         b->case_off[c] = off;
-        Dev save = b->cs[c]->d;
-        Case *dsave = b->cs[c]->dcase;
-        off += layout(b->cs[c], nullptr);
-        b->cs[c]->d = save;
-        b->cs[c]->dcase = dsave;
+        off += space(b->cs[c]);
     }
     return align256(off);
 }
@@ -2032,7 +2058,8 @@ hipError_t batch_build_maps(gsis_batch *b)
     for (const gsis_ctx *c : b->cs) t.mask = t.mask || c->g.nfluid != c->g.ncell;
     for (const gsis_ctx *c : b->cs) t.g13 = t.g13 || c->g.wall_flux == GSIS_WALLFLUX_G13;
     t.rfn = false;
-    t.mseg = b->cs[0]->segments;
+    t.mseg = true;
+    for (const gsis_ctx *c : b->cs) t.mseg = t.mseg && holds_segments(c);
     t.tx = b->tx;
     t.ty = b->ty;
     t.bs = b->bs;
@@ -2055,6 +2082,10 @@ gsis_status batch_apply_tile(gsis_batch *b, int tx, int ty, int tz, int bs)
     const gsis_ctx *c0 = b->cs[0];
     b->tx = c0->tx; b->ty = c0->ty; b->tz = c0->tz; b->bs = c0->bs;
     b->drop_graph();
+    if (!b->bound && !b->sized) {
+        const bool sums = forms_sums(b->cs.data(), b->cs.size()) && tile_forms_sums(b->fp32, b->dia, b->tx, b->ty, b->bs);
+        for (gsis_ctx *c : b->cs) c->segments = sums;
+    }
     if (b->bound) {
         BHIPCHK(b, batch_upload_cases(b));
         BHIPCHK(b, batch_build_maps(b));
@@ -2110,15 +2141,15 @@ gsis_status gsis_batch_create(gsis_batch **out, gsis_ctx *const *cases, int ncas
     b->cs.assign(cases, cases + ncases);
     b->fp32 = cases[0]->fp32;
     b->dia = cases[0]->g.species == GSIS_DIATOMIC;
+    for (gsis_ctx *c : b->cs) c->in_batch = true;
     gsis_status st = batch_apply_tile(b, 0, 0, 0, 0);
     if (st) {
+        for (gsis_ctx *c : b->cs) c->in_batch = false;
         delete b;
         return st;
     }
     for (gsis_ctx *c : b->cs)
         if (!c->meta_ready) build_meta(c);
-    const bool sums = forms_sums(b->cs.data(), b->cs.size());
-    for (gsis_ctx *c : b->cs) c->segments = sums;
     b->map_cap = batch_map_cap(b);
     *out = b;
     return GSIS_OK;
@@ -2139,6 +2170,7 @@ gsis_status gsis_batch_workspace_size(gsis_batch *b, size_t *bytes)
     double *h = b->hist;
     int *hc = b->hist_ctr;
     *bytes = batch_layout(b, nullptr);
+    b->sized = true;
     b->dcases = dc; b->dmap = dm; b->hist = h; b->hist_ctr = hc;
     return GSIS_OK;
 }
@@ -2156,9 +2188,7 @@ gsis_status gsis_batch_bind_workspace(gsis_batch *b, void *device_ptr, size_t by
     batch_layout(b, base);
     for (size_t c = 0; c < b->cs.size(); ++c) {
         gsis_ctx *x = b->cs[c];
-        size_t sz = 0;
-        gsis_workspace_size(x, &sz);
-        gsis_status st = gsis_bind_workspace(x, base + b->case_off[c], sz);
+        gsis_status st = gsis_bind_workspace(x, base + b->case_off[c], space(x));
         if (st) return bfail(b, st, "case " + std::to_string(c) + ": " + x->err);
         x->stream = b->stream;
     }

@@ -57,7 +57,9 @@ bool sweep_shape_supported(bool fp32, bool dia, int tx, int ty);
 int sweep_shape_waves(bool fp32, int tx, int ty);
 int sweep_shapes(bool fp32, int *out, int max);
 hipError_t launch_sweep(const Target &t, hipStream_t s);
-// whether launch_sweep also forms the segments of the moment sums (all cases hold the buffer)
+// whether launch_sweep also forms the segments of the moment sums: a tile that
+// does, and all cases hold the buffer
+bool tile_forms_sums(bool fp32, bool dia, int tx, int ty, int bs);
 bool sweep_forms_sums(const Target &t);
 // unstructured mesh: boundary-face density scales, then the sweep level by level
 // (lev_off[L] .. lev_off[L + 1] are the entries of level L)

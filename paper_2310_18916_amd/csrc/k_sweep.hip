@@ -702,10 +702,12 @@ int sweep_shapes(bool fp32, int *out, int max)
 // x 24^3 nodes) and in FP32 with one (24.0 + 1.5 against 16.4 + 10.9 with the sums
 // apart, on 96 x 64 x 64 x 32^3).  FP64 with one gains nothing from it (38.7 + 1.0
 // against 27.5 + 12.6 on 64 x 48 x 48 x 40^3).
-bool sweep_forms_sums(const Target &t)
+bool tile_forms_sums(bool fp32, bool dia, int tx, int ty, int bs)
 {
-    return t.mseg && t.bs == 256 && t.ty == 4 && (t.tx == 4 || t.dia != t.fp32);
+    return bs == 256 && ty == 4 && (tx == 4 || dia != fp32);
 }
+
+bool sweep_forms_sums(const Target &t) { return t.mseg && tile_forms_sums(t.fp32, t.dia, t.tx, t.ty, t.bs); }
 
 hipError_t launch_sweep(const Target &t, hipStream_t s)
 {

@@ -55,6 +55,17 @@ def tile_shapes():
     return [(buf[3 * k], buf[3 * k + 1], buf[3 * k + 2]) for k in range(n.value)]
 
 
+def workspace(torch, size, ctxs):
+    """size() bytes of device memory; the contexts' lean workspace where the card has
+    no room for more."""
+    try:
+        return torch.empty(size(), dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        for c in ctxs:
+            c.set_lean()
+    return torch.empty(size(), dtype=torch.uint8, device="cuda")
+
+
 class Context:
     """A gsis_ctx without device memory: creation, mask, boundaries, workspace size.
     Touches no GPU (usable on a CPU-only host)."""
@@ -114,6 +125,9 @@ class Context:
         self._check(self.L.gsis_workspace_size(self.h, C.byref(n)), "gsis_workspace_size")
         return n.value
 
+    def set_lean(self, lean: bool = True):
+        self._check(self.L.gsis_set_lean(self.h, int(lean)), "gsis_set_lean")
+
     def close(self):
         if getattr(self, "h", None):
             self.L.gsis_destroy(self.h)
@@ -137,9 +151,9 @@ class Solver(Context):
         self.torch = torch
         if tile is not None:
             self.set_tile(*tile)
-        nbytes = self.workspace_size()
-        self.ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-        self._check(self.L.gsis_bind_workspace(self.h, C.c_void_p(self.ws.data_ptr()), nbytes), "gsis_bind_workspace")
+        self.ws = workspace(torch, self.workspace_size, [self])
+        self._check(self.L.gsis_bind_workspace(self.h, C.c_void_p(self.ws.data_ptr()), self.ws.numel()),
+                    "gsis_bind_workspace")
         self._check(self.L.gsis_set_stream(self.h, C.c_void_p(torch.cuda.current_stream().cuda_stream)),
                     "gsis_set_stream")
         self.nmom = _lib.NMOM[case.species]
@@ -325,11 +339,9 @@ class Batch:
         self._check(self.L.gsis_batch_set_stream(self.h, C.c_void_p(self.stream.cuda_stream)), "gsis_batch_set_stream")
         if tile is not None:
             self.set_tile(*tile)
-        n = C.c_size_t()
-        self._check(self.L.gsis_batch_workspace_size(self.h, C.byref(n)), "gsis_batch_workspace_size")
-        self.ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+        self.ws = workspace(torch, self.workspace_size, self.ctxs)
         torch.cuda.current_stream().synchronize()
-        self._check(self.L.gsis_batch_bind_workspace(self.h, C.c_void_p(self.ws.data_ptr()), n.value),
+        self._check(self.L.gsis_batch_bind_workspace(self.h, C.c_void_p(self.ws.data_ptr()), self.ws.numel()),
                     "gsis_batch_bind_workspace")
         self.members = [BatchMember(c, self) for c in self.ctxs]
 
@@ -337,6 +349,11 @@ class Batch:
         if st:
             msg = self.L.gsis_batch_last_error(self.h)
             raise GsisError(st, where, msg.decode() if msg else "")
+
+    def workspace_size(self) -> int:
+        n = C.c_size_t()
+        self._check(self.L.gsis_batch_workspace_size(self.h, C.byref(n)), "gsis_batch_workspace_size")
+        return n.value
 
     def __len__(self):
         return len(self.members)

@@ -1,0 +1,127 @@
+"""What the device workspace holds beyond the VDF, and that less of it gives the
+same bits.
+
+Bounds: beside its arrays of the VDF's size a context keeps about 350 words of 8
+bytes per cell (136 of them octant sums) and 40 per node, here at most 512 and 64,
+and, where the sweep forms the moment sums, their segments.  Bitwise otherwise: the
+sums have one order, whoever forms them.
+"""
+import ctypes as C
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2310_18916_amd import gsis as G
+from paper_2310_18916_amd import inputs as I
+
+GAS = {"species": I.DIATOMIC, "dr": I.N2_DR, "Zr": I.N2_ZR, "A": I.N2_A}
+KINDS = [("fp64", {}), ("fp32", {}), ("fp64", GAS), ("fp32", GAS)]
+
+
+def box(n, m, **kw):
+    c = dataclasses.replace(I.cavity(4, 4, 0.1, lid=0.2), **kw)
+    c.nx, c.ny, c.nz, c.nv = *n, m
+    return c
+
+
+def room(case, dtype, arrays):
+    vdf = case.nvel * (8 if dtype == "fp64" else 4) * (2 if case.species == I.DIATOMIC else 1)
+    return arrays * vdf * (case.ncell + 1) + 4096 * case.ncell + 512 * case.nvel
+
+
+@pytest.mark.parametrize("dtype, kw", KINDS)
+def test_own_tile_without_sums(dtype, kw):
+    case = box((24, 24, 24), (32, 32, 32), **kw)
+    ctx = G.Context(case, dtype)
+    assert ctx.L.gsis_set_tile(ctx.h, 4, 4, 4, 128) == 0
+    size = ctx.workspace_size()
+    assert size <= room(case, dtype, 1)
+    # a size that was told is not outgrown
+    assert ctx.L.gsis_set_tile(ctx.h, 4, 4, 4, 256) == 0
+    assert ctx.workspace_size() == size
+
+
+@pytest.mark.parametrize("dtype, kw", KINDS)
+@pytest.mark.parametrize("n", [24, 72])
+def test_lean(n, dtype, kw):
+    case = box((n, n, n), (32, 32, 32), **kw)
+    for order in (1, 2):
+        ctx = G.Context(dataclasses.replace(case, order=order), dtype)
+        full = ctx.workspace_size()
+        ctx.set_lean()
+        assert ctx.workspace_size() <= room(case, dtype, order)
+        ctx.set_lean(False)
+        assert ctx.workspace_size() == full
+
+
+def test_batch_own_tile():
+    cases = [box((24, 24, 24), (24, 24, 24)), box((9, 5, 4), (16, 16, 16))]
+    for tile, lean in (((4, 4, 4, 128), False), (None, True)):
+        ctxs = [G.Context(c, "fp32") for c in cases]
+        L = ctxs[0].L
+        h = C.c_void_p()
+        arr = (C.c_void_p * 2)(*[c.h.value for c in ctxs])
+        assert L.gsis_batch_create(C.byref(h), arr, 2) == 0
+        if tile:
+            assert L.gsis_batch_set_tile(h, *tile) == 0
+        for c in ctxs:
+            c.set_lean(lean)
+        n = C.c_size_t()
+        assert L.gsis_batch_workspace_size(h, C.byref(n)) == 0
+        maps = sum(-(-c.nx // 4) * -(-c.ny // 4) * c.nz * c.nvel // 8 for c in cases) + 2 ** 22
+        assert n.value <= sum(room(c, "fp32", 1) for c in cases) + maps
+        if tile:
+            assert L.gsis_batch_set_tile(h, 4, 4, 4, 256) == 0
+            m = C.c_size_t()
+            assert L.gsis_batch_workspace_size(h, C.byref(m)) == 0 and m.value == n.value
+        L.gsis_batch_destroy(h)
+
+
+def solve(case, dtype, lean):
+    ctx = G.Context(case, dtype)
+    if lean:
+        ctx.set_lean()
+    import torch
+    ws = torch.empty(ctx.workspace_size(), dtype=torch.uint8, device="cuda")
+    assert ctx.L.gsis_bind_workspace(ctx.h, C.c_void_p(ws.data_ptr()), ws.numel()) == 0
+    r, u, T, Tr = case.init
+    assert ctx.L.gsis_init_maxwellian(ctx.h, r, (C.c_double * 3)(*u), T, Tr) == 0
+    assert ctx.L.gsis_kinetic_step(ctx.h, 2) == 0
+    forms = C.c_int()
+    assert ctx.L.gsis_forms_sums(ctx.h, C.byref(forms)) == 0
+    out = np.empty((case.ncell, 18 if case.species == I.DIATOMIC else 14))
+    assert ctx.L.gsis_moments(ctx.h, out.ctypes.data_as(C.c_void_p), 0) == 0
+    torch.cuda.synchronize()
+    return out, bool(forms.value)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("dtype, kw", KINDS)
+def test_lean_bitwise(dtype, kw, order):
+    case = box((9, 8, 7), (44, 45, 46), order=order, **kw)
+    a, forms = solve(case, dtype, False)
+    b, lean = solve(case, dtype, True)
+    assert not lean and (forms or dtype == "fp32" and not kw)
+    assert np.array_equal(a, b)
+
+
+@pytest.mark.gpu
+def test_out_of_memory_takes_less(monkeypatch):
+    import torch
+    real, asked = torch.empty, []
+
+    def empty(*a, **kw):
+        if kw.get("dtype") is torch.uint8:
+            asked.append(a[0])
+            if len(asked) == 1:
+                raise torch.cuda.OutOfMemoryError("no room")
+        return real(*a, **kw)
+
+    case = box((9, 8, 7), (44, 45, 46))
+    monkeypatch.setattr(torch, "empty", empty)
+    s = G.Solver(case, "fp64")
+    s.init_maxwellian()
+    s.kinetic_step()
+    assert len(asked) == 2 and asked[1] < asked[0] and not s.forms_sums()
