@@ -188,9 +188,14 @@ Tile pick_tile(const gsis_ctx *const *cs, size_t nc)
     for (size_t k = 0; k < nc; ++k) {
         const Geo &g = cs[k]->g;
         while ((g.nz + t.tz - 1) / t.tz > 1023 && t.tz < 1024) t.tz *= 2;
-        if ((g.nx + t.tx - 1) / t.tx > 1023 || (g.ny + t.ty - 1) / t.ty > 1023) {
+        // 8 x 8 cells (FP32 with two VDFs: 16 x 8) reach the 4096 cells an axis may have
+        if ((g.ny + t.ty - 1) / t.ty > 1023) {
+            t.tx = cs[0]->fp32 && dia ? 16 : 8;
+            t.ty = 8;
+            t.bs = 256;
+        } else if ((g.nx + t.tx - 1) / t.tx > 1023) {
             t.tx = 8;
-            t.ty = cs[0]->fp32 && !dia ? 8 : 4;
+            t.ty = std::max(t.ty, cs[0]->fp32 && !dia ? 8 : 4);
             t.bs = 256;
         }
     }
