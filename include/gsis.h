@@ -302,14 +302,15 @@ gsis_status gsis_forms_sums(const gsis_ctx *ctx, int *forms);
 
 /* Autotuner: performs the next kinetic pass, running its sweep reps >= 1 times
  * under every compiled (tx, ty) tile shape, tile depths tz in {tx/2, tx, 2 tx}
- * and blocks of 128 and 256 threads, timed with HIP events; selects the
- * configuration with the fastest sweep and moment sums (which some
- * configurations form in the sweep) for the context.  Valid because every configuration
+ * and blocks of 128 and 256 threads, and the moment sums after it (which some
+ * configurations form in the sweep), timed with HIP events; selects the fastest
+ * configuration for the context.  Valid because every configuration
  * gives a bitwise-identical sweep; requires source iteration (inv_dt = 0)
  * and order 1, where the sweep does not read f^n (an order-2 context takes
  * the tile found for its first-order twin through gsis_set_tile).  Writes up to max entries of
- * (tx, ty, tz, block) to cfg_out[4*k] and their mean sweep time in ms to
- * ms_out[k], and the number of entries to *count (any output may be NULL).
+ * (tx, ty, tz, block) to cfg_out[4*k] and their mean time of sweep and moment
+ * sums in ms to ms_out[k] (the configuration kept is the first with the least),
+ * and the number of entries to *count (any output may be NULL).
  * Synchronises. */
 gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out, int max, int *count);
 
@@ -377,8 +378,8 @@ gsis_status gsis_batch_set_stream(gsis_batch *b, void *hip_stream);
 /* One tile shape for every case (see gsis_set_tile); all zeros = default. */
 gsis_status gsis_batch_set_tile(gsis_batch *b, int tx, int ty, int tz, int block);
 gsis_status gsis_batch_get_tile(const gsis_batch *b, int *tile);
-/* Time the batched sweep of the next pass under every compiled tile
- * configuration (reps timed launches after a warm-up) and keep the fastest;
+/* Time the batched sweep and moment sums of the next pass under every compiled
+ * tile configuration (reps timed launches after a warm-up) and keep the fastest;
  * counts as one kinetic pass of every case.  Same output as gsis_autotune.
  * Synchronises. */
 gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *ms_out, int max, int *count);

@@ -600,6 +600,19 @@ Target target_of(const gsis_ctx *c)
     return t;
 }
 
+// Mean time in ms of the moment sums after a sweep, after a warm-up launch.
+hipError_t time_moments(const Target &t, int reps, hipEvent_t e0, hipEvent_t e1, hipStream_t s, float *ms)
+{
+    hipError_t e = launch_moments(t, s, true);
+    if (e == hipSuccess) e = hipEventRecord(e0, s);
+    for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch_moments(t, s, true);
+    if (e == hipSuccess) e = hipEventRecord(e1, s);
+    if (e == hipSuccess) e = hipEventSynchronize(e1);
+    if (e == hipSuccess) e = hipEventElapsedTime(ms, e0, e1);
+    *ms /= (float)reps;
+    return e;
+}
+
 // Tile lists, plane offsets and the case record to the device (stream-ordered
 // with earlier work: the host waits for the stream first).
 hipError_t upload_tiles(gsis_ctx *c)
@@ -1733,7 +1746,7 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
     bool dia = g.species == GSIS_DIATOMIC;
     int shapes[32];
     int nsh = sweep_shapes(ctx->fp32, shapes, 16);
-    struct Cand { int tx, ty, tz, bs; double ms, rank = 0.0; };
+    struct Cand { int tx, ty, tz, bs; double ms; };
     std::vector<Cand> cands;
     float moms[2] = {-1.0f, -1.0f};
     for (int k = 0; k < nsh; ++k) {
@@ -1766,18 +1779,11 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-        // ranked with the moment sums, timed once formed in the sweep and once not
+        // with the moment sums, which depend on the tile only by who forms them
         float &mom = moms[sweep_forms_sums(tc)];
-        if (mom < 0.0f) {
-            if (e == hipSuccess) e = hipEventRecord(e0, ctx->stream);
-            if (e == hipSuccess) e = launch_moments(tc, ctx->stream, true);
-            if (e == hipSuccess) e = hipEventRecord(e1, ctx->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            if (e == hipSuccess) e = hipEventElapsedTime(&mom, e0, e1);
-        }
+        if (e == hipSuccess && mom < 0.0f) e = time_moments(tc, reps, e0, e1, ctx->stream, &mom);
         if (e != hipSuccess) { st = fail(ctx, GSIS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e)); break; }
-        c.ms = ms / reps;
-        c.rank = c.ms + mom;
+        c.ms = ms / reps + mom;
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
@@ -1789,7 +1795,7 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
     }
     size_t best = 0;
     for (size_t k = 1; k < cands.size(); ++k)
-        if (cands[k].rank < cands[best].rank) best = k;
+        if (cands[k].ms < cands[best].ms) best = k;
     ctx->tile_auto = false;
     ctx->tx = cands[best].tx; ctx->ty = cands[best].ty; ctx->tz = cands[best].tz; ctx->bs = cands[best].bs;
     build_tiles(ctx);
@@ -2250,7 +2256,7 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
     const gsis_ctx *c0 = b->cs[0];
     int shapes[32];
     int nsh = sweep_shapes(b->fp32, shapes, 16);
-    struct Cand { int tx, ty, tz, bs; double ms, rank = 0.0; };
+    struct Cand { int tx, ty, tz, bs; double ms; };
     std::vector<Cand> cands;
     float moms[2] = {-1.0f, -1.0f};
     for (int k = 0; k < nsh; ++k) {
@@ -2279,18 +2285,11 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-        // ranked with the moment sums, timed once formed in the sweep and once not
+        // with the moment sums, which depend on the tile only by who forms them
         float &mom = moms[sweep_forms_sums(b->t)];
-        if (mom < 0.0f) {
-            if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
-            if (e == hipSuccess) e = launch_moments(b->t, b->stream, true);
-            if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            if (e == hipSuccess) e = hipEventElapsedTime(&mom, e0, e1);
-        }
+        if (e == hipSuccess && mom < 0.0f) e = time_moments(b->t, reps, e0, e1, b->stream, &mom);
         if (e != hipSuccess) { st = bfail(b, GSIS_EDEVICE, std::string("autotune: ") + hipGetErrorString(e)); break; }
-        c.ms = ms / reps;
-        c.rank = c.ms + mom;
+        c.ms = ms / reps + mom;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -2300,7 +2299,7 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
     }
     size_t best = 0;
     for (size_t k = 1; k < cands.size(); ++k)
-        if (cands[k].rank < cands[best].rank) best = k;
+        if (cands[k].ms < cands[best].ms) best = k;
     st = batch_apply_tile(b, cands[best].tx, cands[best].ty, cands[best].tz, cands[best].bs);
     if (st) return st;
     // every case now holds this pass's sweep result (identical under every configuration)

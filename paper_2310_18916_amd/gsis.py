@@ -173,8 +173,8 @@ class Solver(Context):
         return bool(n.value)
 
     def autotune(self, reps: int = 2):
-        """Time the next pass's sweep under every compiled configuration and keep the
-        fastest; returns [((tx, ty, tz, block), ms), ...]."""
+        """Time the next pass's sweep and moment sums under every compiled configuration
+        and keep the fastest; returns [((tx, ty, tz, block), ms), ...]."""
         cfg = (C.c_int * 512)()
         ms = (C.c_double * 128)()
         n = C.c_int()
