@@ -325,7 +325,7 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
     constexpr int V = 16 / (int)sizeof(T);
     typedef T vec __attribute__((ext_vector_type(V)));
     vec areg[SUM ? 16 / V : 1];   // 16 nodes of one cell per lane
-    d4 prod[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};   // even and odd products of a chunk
+    d4 prod[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};   // sum of the chunk's chains of four so far, and this one
 #pragma unroll
     for (int k = 0; k < (SUM ? 16 / V : 0); ++k) areg[k] = vec(T(0));
     auto fetch = [&]() {
@@ -337,8 +337,10 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
     };
     auto multiply = [&](int k) {
         const double m = BLDS ? smono[mw][BLDS ? k * 64 + lane : 0] : bmono[SUM && !BLDS ? k : 0];
-        prod[k & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)areg[SUM ? k / V : 0][k % V], m,
-                                                           k < 2 ? d4{0.0, 0.0, 0.0, 0.0} : prod[k & 1], 0, 0, 0);
+        if (k == 4) prod[0] = prod[1];
+        else if (k % 4 == 0 && k > 0) prod[0] += prod[1];
+        prod[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)areg[SUM ? k / V : 0][k % V], m,
+                                                       k % 4 == 0 ? d4{0.0, 0.0, 0.0, 0.0} : prod[1], 0, 0, 0);
     };
     // lane l of a product holds sum (l & 15) of cells 4 r + (l >> 4), r = 0..3
     auto hand = [&](int par, int slot, int d) {
