@@ -744,7 +744,7 @@ __device__ __forceinline__ void stepped_W(PV rec, int it, double Dm, double iDm,
     if (it > 0) {
 #pragma unroll
         for (int k = 0; k < 5; ++k) Wn[k] += rec[NW + k] * iDm;
-        if (DIA) Wn[5] += rec[NW + 5] * recip(Dm + rec[DIA ? WSRC : 0]);
+        if (DIA) Wn[5] += quot(rec[NW + 5], Dm + rec[DIA ? WSRC : 0]);
     }
 }
 
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(256) void k_mac_bface(GSIS_SPAN_ARGS, int it)
     constexpr int WS = DIA ? WS_DIA : WS_MONO;
     stepped_W<DIA>(src + (size_t)cell * WS, it, Dm, iDm, Wn);
     short_prims<DIA>(g, Wn, P);
-    const double mu = pow_line(P[4], g.omega) * g.idelta;
+    const double mu = quot(pow_line(P[4], g.omega), g.delta, g.idelta);
     if (G13 && !EULER && g.wall_flux == 1) {
         // NSF_c from the new states of the cell and its neighbours (one per lane) plus the cell's HoT_c
         int who = cell;
@@ -976,7 +976,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const double el = sp[QE][hL], er = sp[QE][hR];
             double sA = 0.0, s1 = 0.0, s2 = 0.0, qn = 0.0, qr = 0.0, mu = 0.0;
             if (!EULER) {
-                mu = pow_line(0.5 * (tl + tr), g.omega) * g.idelta;
+                mu = quot(pow_line(0.5 * (tl + tr), g.omega), g.delta, g.idelta);
                 // twice the mean over the face's two cells of the derivatives along the axis of stride S
                 // of the velocity components qa (normal) and qb (that axis)
                 auto tangential = [&](int S, int qa, int qb, double invh, double &da, double &db) {
@@ -1019,7 +1019,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 const double gl = sp[QER][hL], gr = sp[QER][hR];
                 sf[NW - 1][t] = (0.5 * (gl * ul + gr * ur) - hs * (gr - gl) + qr) * ih;
             }
-            sf[NW][t] = (EULER ? smax : fma(g.Cd * mu * ih, recip(0.5 * (rl + rr)), smax)) * ih;
+            sf[NW][t] = (EULER ? smax : smax + quot(g.Cd * mu * ih, 0.5 * (rl + rr))) * ih;
         } else if ((fL && fq > 0) || (fR && fq < MT)) {
             // the boundary face of a cell of this tile (at most one of the two is fluid)
             const int e = atomicAdd(&scount, 1);
@@ -1097,9 +1097,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             } else {
                 const int b = fe.x >> 20;
                 const double rho = sp[QR][h], T = sp[QT][h];
-                const double mu = EULER ? 0.0 : pow_line(T, g.omega) * g.idelta;
+                const double mu = EULER ? 0.0 : quot(pow_line(T, g.omega), g.delta, g.idelta);
                 const double piT = PI * T;
-                const double K = rho * recip(piT * sqrt(piT)) * ((dir & 1) ? 1.0 : -1.0);
+                const double K = quot(rho, piT * sqrt(piT)) * ((dir & 1) ? 1.0 : -1.0);
                 const double e1 = DIA ? 0.5 * g.dr * sp[QTR][h] : 0.0;
                 const double *S0 = ssum + e * 3 * NS, *S1 = S0 + NS, *S2 = S1 + NS;
                 const int bb1 = ba == 2 ? 0 : ba + 1;
@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                                           ba == 0 ? sq[5] : (ba == 1 ? sq[4] : sq[3])};
                     const double ql[3] = {rot(6, ba), rot(6, bb1), rot(6, bb2)};
                     const double rl[3] = {rot(9, ba), rot(9, bb1), rot(9, bb2)};
-                    const double cs = recip(rho * T * T), c5 = 0.4 * recip(T);
+                    const double cs = recip(rho * T * T), c5 = quot(2.0, 5.0 * T);
                     // the seven bracketed sums (1, c_n, c_1, c_2, c_n^2, c_1^2, c_2^2), shared out over the quad
                     double *B = sb + e * 8;
                     for (int k = t & 3; k < 7; k += 4) {
@@ -1148,7 +1148,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                     const double uu = ul0 * ul0 + ul1 * ul1 + ul2 * ul2;
                     const double e0 = B[4] + B[5] + B[6] + 2.0 * (ul0 * B[1] + ul1 * B[2] + ul2 * B[3]) + uu * B[0];
                     const double sr = rl[0] * S0[1] * S1[0] * S2[0] + rl[1] * S0[0] * S1[1] * S2[0] + rl[2] * S0[0] * S1[0] * S2[1];
-                    Fe[5] = DIA ? K * (e1 * B[0] + 2.0 * recip(rho * T) * sr) : 0.0;
+                    Fe[5] = DIA ? K * (e1 * B[0] + quot(2.0, rho * T) * sr) : 0.0;
                     Fe[4] = K * e0 + Fe[5];
                 } else {
                     const double s12 = S1[0] * S2[0];
@@ -1162,10 +1162,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 Fe[1] = ba == 0 ? oA : (ba == 1 ? o2 : o1);
                 Fe[2] = ba == 1 ? oA : (ba == 2 ? o2 : o1);
                 Fe[3] = ba == 2 ? oA : (ba == 0 ? o2 : o1);
-                const double sc = bc.kind[b] == 1 ? bc.rho[b] : Fe[0] * recip(-in[0]);
+                const double sc = bc.kind[b] == 1 ? bc.rho[b] : quot(Fe[0], -in[0]);
 #pragma unroll
                 for (int k = 0; k < NW; ++k) Fe[k] += sc * in[k];
-                gam = fabs(sp[QU + ba][h]) + sp[QC][h] + (EULER ? 0.0 : g.Cd * mu * ih * recip(rho));
+                gam = fabs(sp[QU + ba][h]) + sp[QC][h] + (EULER ? 0.0 : quot(g.Cd * mu * ih, rho));
             }
             if (QF == 1 || (t & 3) == 0) {
 #pragma unroll
@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (live) {
         const double u0 = sp[QU][h], u1 = sp[QU + 1][h], u2 = sp[QU + 2][h], T = sp[QT][h];
         const double sumG = ((sf[NW][xl] + sf[NW][xh]) + (sf[NW][yl] + sf[NW][yh])) + (sf[NW][zl] + sf[NW][zh]);
-        const double vis = EULER ? 0.0 : g.Cd * (pow_line(T, g.omega) * g.idelta) * recip(sp[QR][h] * g.hmin);
+        const double vis = EULER ? 0.0 : quot(g.Cd * quot(pow_line(T, g.omega), g.delta, g.idelta), sp[QR][h] * g.hmin);
         const double idt = (sqrt(u0 * u0 + u1 * u1 + u2 * u2) + sp[QC][h] + vis) / (g.macro_cfl * g.hmin);
         D = idt + 0.5 * sumG;
         if (!(D > 0.0 && isfinite(D))) {
