@@ -367,6 +367,15 @@ __device__ __forceinline__ double pow_line(double x, double y)
     return exp_line(y * lx);
 }
 
+// t + e += b, e the sum of the additions' roundings (exact by Knuth's two-sum)
+template <typename D> __device__ __forceinline__ void add_compensated(D &t, D &e, D b)
+{
+#pragma clang fp contract(off) reassociate(off)
+    const D s = t + b, bb = s - t;
+    e += (t - (s - bb)) + (b - bb);
+    t = s;
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);

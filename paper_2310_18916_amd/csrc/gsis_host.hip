@@ -318,7 +318,8 @@ void build_runs(gsis_ctx *c)
     std::vector<std::pair<double, double>> x;   // (weight, x)
     c->ly.clear(); c->lz.clear(); c->lx.clear(); c->lrun.clear(); c->lrunw.clear();
     g.lnrun = 0;
-    // sorted distinct values, given up beyond 512 (a list without a lattice)
+    // sorted distinct values, given up beyond 512 (a list without a lattice; the
+    // tables of as many take 57 KB LDS)
     auto add = [](auto &v, const auto &e) -> bool {
         const auto it = std::lower_bound(v.begin(), v.end(), e);
         if (it == v.end() || *it != e) v.insert(it, e);

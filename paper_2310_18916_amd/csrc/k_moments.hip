@@ -21,15 +21,6 @@
 
 namespace gsis {
 
-// t + e += b, e the sum of the additions' roundings (exact by Knuth's two-sum)
-template <typename D> __device__ __forceinline__ void add_compensated(D &t, D &e, D b)
-{
-#pragma clang fp contract(off) reassociate(off)
-    const D s = t + b, bb = s - t;
-    e += (t - (s - bb)) + (b - bb);
-    t = s;
-}
-
 // Octant sums of a box case, tensor grid or node list, as a matrix product:
 // [cells x nodes] times [nodes x 13 monomials] on the FP64 matrix cores.
 //
