@@ -1205,7 +1205,32 @@ gsis_status gsis_set_spatial_mesh(gsis_ctx *ctx, int ncell, const double *volume
     }
     // boundary faces by outward direction (+n_k: 2 k, -n_k: 2 k + 1) in pairs,
     // and the runs of nodes that leave through each direction
+    // (with those of the entering classes that hold a node which leaves through one
+    // of the direction's faces all the same: normals of one orientation differ by up
+    // to 1e-9, and products that cancel round)
     std::vector<int> bg, bgd, br, bro(1, 0);
+    std::vector<double> off_ori(2 * nori, 0.0);   // largest distance of a boundary normal from its orientation
+    for (int f : bface) {
+        const int q = 2 * fk[f] + fflip[f];
+        double s = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double e = face_geom[(size_t)f * 4 + 1 + a] - (q & 1 ? -ori[4 * fk[f] + a] : ori[4 * fk[f] + a]);
+            s += e * e;
+        }
+        off_ori[q] = std::max(off_ori[q], std::sqrt(s));
+    }
+    auto grazes = [&](int q, int c) {
+        const double *n = &ori[4 * (q >> 1)];
+        for (int p = cpos[c]; p < cpos[c + 1]; ++p) {
+            const double *t = &ctx->vlist[(size_t)perm[p] * 4];
+            const double x[3] = {t[0] * n[0], t[1] * n[1], t[2] * n[2]}, d = x[0] + x[1] + x[2];
+            const double all = std::fabs(x[0]) + std::fabs(x[1]) + std::fabs(x[2]);
+            const double speed = std::sqrt(t[0] * t[0] + t[1] * t[1] + t[2] * t[2]);
+            const double cancel = all == std::fabs(d) ? 0.0 : 4e-16 * all;
+            if ((q & 1 ? -d : d) + 2.0 * off_ori[q] * speed + cancel > 0.0) return true;
+        }
+        return false;
+    };
     for (int q = 0; q < 2 * nori; ++q) {
         bool open = false;
         for (size_t b = 0; b < bface.size(); ++b) {
@@ -1219,7 +1244,7 @@ gsis_status gsis_set_spatial_mesh(gsis_ctx *ctx, int ncell, const double *volume
             open = !open;
         }
         for (int c = 0; c < ncls; ++c) {
-            if (((masks[c] >> (q >> 1)) & 1u) == (unsigned)(q & 1)) continue;   // the class enters
+            if (((masks[c] >> (q >> 1)) & 1u) == (unsigned)(q & 1) && !grazes(q, c)) continue;   // the class enters
             if ((int)br.size() > 2 * bro[q] && br.back() == cpos[c]) br.back() = cpos[c + 1];
             else br.insert(br.end(), {cpos[c], cpos[c + 1]});
         }
