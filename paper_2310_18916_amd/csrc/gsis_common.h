@@ -112,6 +112,7 @@ struct Dev {
     // weight class) and those along y and z, then per run (first x, end x, y, z) and its weight
     double *lxt, *lyt, *lzt, *lrunw;
     int4 *lrun;
+    double *mono;      // box: [chunk][16][64] monomials of every chunk of an octant (k_monomials)
     double *nt64;      // [nv][4] every node in the internal order: xi_x, xi_y, xi_z, weight
     float *nt32;       // [nv][4] the same in FP32
     double *xi64[3];   // per-axis nodes (tensor grid)
@@ -429,7 +430,23 @@ __device__ __forceinline__ double maxwell64(double rho, const double *u, double 
 // Octant sums as a matrix product over the nodes (k_moments, k_sweep): chunks of
 // MCHUNK nodes, segments of MSEG.
 constexpr int MCHUNK = 64, MSEG = 4 * MCHUNK;
-constexpr int MOM_GROUPS = 2;   // groups of 16 cells a block of k_moments takes
+constexpr int MOM_WAVES = 4;   // waves of a block of k_moments, 16 cells each
+
+// Chunks of the octants before octant o
+__host__ __device__ inline int mom_chunk(const Geo &g, int o)
+{
+    int n = 0;
+    for (int k = 0; k < o; ++k) n += (g.osize[k] + MCHUNK - 1) / MCHUNK;
+    return n;
+}
+
+// Node of its chunk that lanes 16 q to 16 q + 15 supply to product t: the values of
+// a 16-byte load are consecutive nodes, and the four loads of a cell 64 bytes.
+template <typename T> __host__ __device__ constexpr int mom_node(int q, int t)
+{
+    constexpr int V = 16 / (int)sizeof(T);
+    return 4 * V * (t / V) + V * q + t % V;
+}
 
 // Monomial i of a node times its weight: 1, x, y, z, xx, yy, zz, xy, xz, yz,
 // x|xi|^2, y|xi|^2, z|xi|^2, and zero from 13 on.  As (w a) b with a of 1, x, y,

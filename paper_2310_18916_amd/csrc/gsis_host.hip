@@ -482,6 +482,8 @@ size_t layout(gsis_ctx *c, char *base)
         carve(off, d.lrunw, g.lnrun, base);
     }
     carve(off, d.nt64, nv * 4, base);
+    d.mono = nullptr;
+    if (!g.umesh) carve(off, d.mono, (size_t)mom_chunk(g, 8) * 16 * 64, base);
     carve(off, d.nt32, nv * 4, base);
     for (int a = 0; a < 3; ++a) {
         carve(off, d.xi64[a], (size_t)g.n1[a], base);
@@ -1457,6 +1459,7 @@ gsis_status gsis_bind_workspace(gsis_ctx *ctx, void *device_ptr, size_t bytes)
     HIPCHK(ctx, hipMemset(d.errflag, 0, 4 * sizeof(int)));
     HIPCHK(ctx, hipMemset(d.dmax, 0, (size_t)DSETS * DSLOT * DSTRIDE * sizeof(unsigned long long)));
     HIPCHK(ctx, launch_setup_tables(g, ctx->bc, d, nullptr));
+    if (!g.umesh) HIPCHK(ctx, launch_monomials(g, d, ctx->fp32, nullptr));
     HIPCHK(ctx, hipDeviceSynchronize());
     ctx->bound = true;
     return GSIS_OK;

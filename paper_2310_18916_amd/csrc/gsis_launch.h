@@ -44,6 +44,8 @@ hipError_t launch_apply_correction(const Geo &g, const Dev &d, bool fp32, hipStr
 // order 2: limiter, then inv_dt f^n - (D2 - D1) into d.ho0/ho1, from the stored f^n
 hipError_t launch_recon(const Geo &g, const Dev &d, bool fp32, hipStream_t s);
 
+// the table of the moment sums, from d.nt64
+hipError_t launch_monomials(const Geo &g, const Dev &d, bool fp32, hipStream_t s);
 // swept: the VDF is the result of the last launch_sweep of this target
 hipError_t launch_moments(const Target &t, hipStream_t s, bool swept);
 hipError_t launch_derive(const Target &t, hipStream_t s);

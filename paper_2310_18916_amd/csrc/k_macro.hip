@@ -1927,7 +1927,7 @@ int kind_blocks(const Geo &g, Kind k)
     case K_FACE8: return face_blocks(g);
     case K_GRAD: return grad_blocks(g);
     case K_MTILE: return mtile_blocks(g);
-    case K_MOM: return (g.ncell + 16 * MOM_GROUPS - 1) / (16 * MOM_GROUPS) * 8;
+    case K_MOM: return (g.ncell + 16 * MOM_WAVES - 1) / (16 * MOM_WAVES) * (g.species == 1 ? 16 : 8);
     case K_MSUM: return (g.ncell + 15) / 16 * 8;
     case K_CASE: return 1;
     default: return 0;

@@ -26,7 +26,7 @@ namespace gsis {
 //
 // The order of a cell's sum depends on the octant's size alone, whoever forms
 // it: MCHUNK = 64 consecutive nodes are one chunk, multiplied in 16 products
-// of v_mfma_f64_16x16x4 (product t takes nodes 16 q + t, q = 0..3) in chains of
+// of v_mfma_f64_16x16x4 (product t takes nodes mom_node(q, t), q = 0..3) in chains of
 // four, ((p0 + p1) + p2) + p3; four chunks are a segment, (c0 + c1) + (c2 + c3), a
 // missing one zero; segments are added in order, with the rounding of each
 // addition carried along, and so are the octants (k_derive).  Root-mean-square
@@ -39,144 +39,162 @@ namespace gsis {
 // k_moments does all of it from the stored VDF, for a state that was set and
 // for tiles that don't form segments, with the same result to the bit.
 //
-// k_moments: lane l of a product supplies f(cell l & 15, node 16 (l >> 4) + t)
-// and monomial l & 15 of that node.  A block is one wave for 16 G cells of one
-// octant; its loads take whole stretches of 1 / G KB of a row and pass through
-// LDS, the next chunk's in flight while one is multiplied.  One VDF is held to two
-// waves per SIMD (286 registers otherwise: 15.1 against 11.4 ms in FP32); two VDFs
-// spill 400 bytes there (9.8 against 6.0 ms).  Bound by reading the VDF in FP64:
-// 11.7 ms for 75.5 GB (64 x 48 x 48 cells, 40^3 nodes), 6.4 TB/s; in FP32 by the
-// products' LDS reads, 11.4 ms for 51.5 GB.  (Sums along the rows of the tensor
-// grid with a reduction over lanes read 6.8 and 5.8 TB/s, but in an order that the
-// sweep can't form; with the segments in the sweep this kernel runs for small
-// states, where both take 0.03 to 0.05 ms, and once when a state is set.)
-template <typename T, bool DIA>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIA ? 1 : 2))) void k_moments(GSIS_SPAN_ARGS)
+// k_moments: a wave takes 16 cells of one octant and one VDF; lane l of product t
+// supplies f(cell l & 15, node mom_node(l >> 4, t)).  Loads take 512 bytes of a row at
+// a time, the next stretch's in flight while this one, brought to the lanes through
+// the wave's own LDS tile, is multiplied.  The monomials come from a table
+// (k_monomials, 128 bytes a node, in the XCD's L2 as blocks of one octant go to one
+// XCD), a chunk at a time through LDS for the four waves of a block: formed in the
+// kernel they took a third of its instructions.
+// Bound in FP64 by reading the VDF, 11.4 ms for 75.5 GB (64 x 48 x 48 cells, 40^3 nodes,
+// 6.6 TB/s); in FP32 by instructions, the products' 1024 cycles a chunk and the
+// conversions, 9.3 ms for 51.5 GB (96 x 64 x 64, 32^3) and 18.3 for 100.7 (40^3); two
+// VDFs 5.3 for 32.6 GB and 3.4 for 16.3.  The kernel that formed its monomials, a wave
+// per block, took 12.0, 11.3, 22.0, 6.1 and 5.7; sums along the rows of the tensor grid
+// with a reduction over lanes, in an order that the sweep can't form, 11.3, 8.7, 15.9,
+// 5.8 and 3.5.  It runs for states under 256 MB and with few nodes an octant, for a
+// caller's tile that forms no sums (tile_forms_sums), for a lean workspace, and once
+// when a state is set.
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_moments(GSIS_SPAN_ARGS)
 {
     typedef double d4 __attribute__((ext_vector_type(4)));
     typedef double d2 __attribute__((ext_vector_type(2)));
-    constexpr int G = MOM_GROUPS;
-    constexpr int V = 16 / (int)sizeof(T);   // values of one 16-byte load
-    constexpr int LR = 64 / G;               // lanes along a row
-    constexpr int NCH = LR * V / MCHUNK;     // chunks of a stretch
-    constexpr int PITCH = 1024 + 16;         // 16 rows at one offset take all LDS banks
-    constexpr int ND = DIA ? 2 : 1;
+    constexpr int V = 16 / (int)sizeof(T);   // values of a load
+    constexpr int ROW = 512, NROW = ROW / (int)sizeof(T), NCH = NROW / MCHUNK;   // bytes, nodes, chunks of a stretch
+    constexpr int PITCH = ROW + 16;          // 16 rows at one offset take all LDS banks
     // a row starts at any element
     typedef T vec __attribute__((ext_vector_type(V)));
     typedef T uvec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
-    __shared__ __attribute__((aligned(16))) char sv[16 * PITCH];
-    __shared__ d2 sn[NCH * MCHUNK * 2];
+    __shared__ __attribute__((aligned(16))) char stile[MOM_WAVES][16 * PITCH];
+    __shared__ d2 smono2[2][16 * 32];
     int blk;
     const Case &C = case_of(span_cases, span_map, blk);
     const Geo &g = C.g;
-    const int o = blk & 7, c0 = (blk >> 3) * 16 * G;
-    const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;
+    const bool dia = g.species == 1;
+    const int o = blk & 7, d = dia ? (blk >> 3) & 1 : 0, r = blk >> (dia ? 4 : 3);
+    const int t = threadIdx.x, lane = t & 63, i = lane & 15, q = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int c0 = (r * MOM_WAVES + w) * 16;   // the wave's cells
     const int n = g.osize[o], ob = g.obase[o], ncell = g.ncell;
-    const size_t nv = (size_t)g.nv;
-    const gptr<const d2> nt = (gptr<const d2>)C.d.nt64 + 2 * (size_t)ob;
-    // load k reads G cells' rows
-    const int lr = lane / LR, lv = (lane % LR) * V;
-    auto rowp = [&](int d, int k) {
-        const int c = min(c0 + G * k + lr, ncell - 1);
-        return (d ? (gptr<const T>)C.d.f1 : (gptr<const T>)C.d.f0) + (size_t)c * nv + ob;
-    };
-    const Monomial mono(i);
-    d4 tot[ND][G], err[ND][G], seg[ND][G], pair[ND][G];
+    const int nch = (n + MCHUNK - 1) / MCHUNK;
+    const bool live = c0 < ncell;   // uniform over the wave
+    const gptr<const d2> tab = (gptr<const d2>)C.d.mono + (size_t)mom_chunk(g, o) * (16 * 32) + 2 * t;
+    // load k reads two cells' rows
+    const int lr = lane >> 5, lv = (lane & 31) * V;
+    const gptr<const T> f = d ? (gptr<const T>)C.d.f1 : (gptr<const T>)C.d.f0;
+    auto row = [&](int k) { return f + (size_t)min(c0 + 2 * k + lr, ncell - 1) * (size_t)g.nv + ob; };
+    vec pv[8];
+    auto load = [&](int n0) {
+        if (n0 + NROW <= n) {
 #pragma unroll
-    for (int d = 0; d < ND; ++d)
+            for (int k = 0; k < 8; ++k) pv[k] = __builtin_nontemporal_load((gptr<const uvec>)(row(k) + n0 + lv));
+        } else {   // nodes past the end read the last one (and weigh 0)
 #pragma unroll
-        for (int k = 0; k < G; ++k) tot[d][k] = err[d][k] = seg[d][k] = pair[d][k] = d4{0.0, 0.0, 0.0, 0.0};
-    vec pv[16];
-    d2 pn[NCH * 2];
-    auto load = [&](int d, int n0) {
-        if (n0 + NCH * MCHUNK <= n) {
+            for (int k = 0; k < 8; ++k)
 #pragma unroll
-            for (int k = 0; k < 16; ++k) pv[k] = __builtin_nontemporal_load((gptr<const uvec>)(rowp(d, k) + n0 + lv));
-        } else {
-#pragma unroll
-            for (int k = 0; k < 16; ++k)
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    const int l = n0 + lv + e;
-                    const T f = rowp(d, k)[min(l, n - 1)];
-                    pv[k][e] = l < n ? f : T(0);
-                }
-        }
-        if (d == 0) {
-#pragma unroll
-            for (int k = 0; k < NCH * 2; ++k) pn[k] = nt[min(2 * n0 + 64 * k + lane, 2 * n - 1)];
+                for (int e = 0; e < V; ++e) pv[k][e] = row(k)[min(n0 + lv + e, n - 1)];
         }
     };
-    if (n > 0) load(0, 0);
-    for (int n0 = 0; n0 < n; n0 += NCH * MCHUNK)
+    // monomials of a chunk, a part per thread, read before the values that are in flight longer
+    struct Mono { d2 a, b; };
+    auto read = [&](int h) {
+        const gptr<const d2> p = tab + (size_t)min(h, nch - 1) * (16 * 32);
+        return Mono{p[0], p[1]};
+    };
+    auto place = [&](int h, const Mono &m) {
+        smono2[h & 1][2 * t] = m.a;
+        smono2[h & 1][2 * t + 1] = m.b;
+    };
+    d4 tot, err, seg, pair;
+    const d4 zero = {0.0, 0.0, 0.0, 0.0};
+    tot = err = seg = pair = zero;
+    Mono m1;
+    if (n > 0) {
+        place(0, read(0));
+        m1 = read(1);
+        if (live) load(0);
+        __syncthreads();
+    }
+    for (int h0 = 0; h0 < nch; h0 += NCH) {
+        if (live) {
 #pragma unroll
-        for (int d = 0; d < ND; ++d) {
+            for (int k = 0; k < 8; ++k) *(vec *)(stile[w] + (2 * k + lr) * PITCH + (lane & 31) * 16) = pv[k];
+            // LDS accesses of one wave complete in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
 #pragma unroll
-            for (int k = 0; k < 16; ++k) *(vec *)(sv + k * PITCH + lane * 16) = pv[k];
-            if (d == 0) {
+        for (int c = 0; c < NCH; ++c) {
+            const int h = h0 + c;
+            if (h >= nch) break;
+            place(h + 1, m1);
+            m1 = read(h + 2);
+            const double *const smono = (const double *)smono2[h & 1];
+            if (c == 0 && live && h0 + NCH < nch) load((h0 + NCH) * MCHUNK);
+            if (live) {
+                d4 sum, p;
 #pragma unroll
-                for (int k = 0; k < NCH * 2; ++k) sn[64 * k + lane] = pn[k];
-            }
-            __syncthreads();
-            if (d + 1 < ND) load(d + 1, n0);
-            else if (n0 + NCH * MCHUNK < n) load(0, n0 + NCH * MCHUNK);
+                for (int s = 0; s < 16; s += V) {
+                    const vec a = *(const vec *)(stile[w] + i * PITCH + (c * MCHUNK + mom_node<T>(q, s)) * sizeof(T));
 #pragma unroll
-            for (int h = 0; h < NCH; ++h) {
-                d4 acc[G];
-#pragma unroll 2
-                for (int s4 = 0; s4 < 16; s4 += 4) {
-                    d4 p[G];
-#pragma unroll
-                    for (int k = 0; k < G; ++k) p[k] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int s = s4; s < s4 + 4; s += V) {
-                        vec a[G];
-#pragma unroll
-                        for (int k = 0; k < G; ++k)
-                            a[k] = *(const vec *)(sv + i * PITCH + k * (1024 / G) + (h * MCHUNK + 16 * q + s) * sizeof(T));
-#pragma unroll
-                        for (int e = 0; e < V; ++e) {
-                            const int l = h * MCHUNK + 16 * q + s + e;
-                            const d2 t0 = sn[2 * l], t1 = sn[2 * l + 1];
-                            const double m = mono(t0.x, t0.y, t1.x, t1.y);
-#pragma unroll
-                            for (int k = 0; k < G; ++k) p[k] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[k][e], m, p[k], 0, 0, 0);
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < G; ++k) acc[k] = s4 == 0 ? p[k] : acc[k] + p[k];
-                }
-                const int c = (n0 / MCHUNK + h) & 3;   // uniform
-                const bool last = n0 + (h + 1) * MCHUNK >= n;
-#pragma unroll
-                for (int k = 0; k < G; ++k) {
-                    const d4 p = acc[k];
-                    if (c == 0) seg[d][k] = p;
-                    else if (c == 1) seg[d][k] += p;
-                    else if (c == 2) pair[d][k] = p;
-                    else pair[d][k] += p;
-                    if (c == 3 || last) {
-                        add_compensated(tot[d][k], err[d][k], seg[d][k] + (c < 2 ? d4{0.0, 0.0, 0.0, 0.0} : pair[d][k]));
+                    for (int e = 0; e < V; ++e) {
+                        p = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[e], smono[(s + e) * 64 + lane],
+                                                                 (s + e) % 4 == 0 ? zero : p, 0, 0, 0);
+                        if (s + e == 3) sum = p;
+                        else if ((s + e) % 4 == 3) sum += p;
                     }
                 }
-                if (last) break;
+                const int m = h & 3;   // uniform
+                if (m == 0) seg = sum;
+                else if (m == 1) seg += sum;
+                else if (m == 2) pair = sum;
+                else pair += sum;
+                if (m == 3 || h + 1 == nch) add_compensated(tot, err, seg + (m < 2 ? zero : pair));
             }
             __syncthreads();
         }
-    // lane l holds sum (l & 15) of rows 4 r + (l >> 4), r = 0..3
+    }
+    if (!live) return;
+    // lane l holds sum (l & 15) of rows 4 j + (l >> 4), j = 0..3
     const gptr<double> mom8 = (gptr<double>)C.d.mom8;
     const gptr<const int> cflag = (gptr<const int>)C.d.cflag;
 #pragma unroll
-    for (int k = 0; k < G; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int cell = c0 + G * (4 * r + q) + k;
-            if (cell >= ncell) continue;
-            const bool live = cflag[cell] != 0;
-            const gptr<double> out = mom8 + ((size_t)cell * 8 + o) * NRS;
-            if (i < 13) out[i] = live ? tot[0][k][r] + err[0][k][r] : 0.0;
-            if (i < 4) out[13 + i] = DIA && live ? tot[ND - 1][k][r] + err[ND - 1][k][r] : 0.0;
-        }
+    for (int j = 0; j < 4; ++j) {
+        const int cell = c0 + 4 * j + q;
+        if (cell >= ncell) continue;
+        const double v = cflag[cell] != 0 ? tot[j] + err[j] : 0.0;
+        const gptr<double> out = mom8 + ((size_t)cell * 8 + o) * NRS;
+        if (d == 0 && i < 13) out[i] = v;
+        if (d == 1 && i < 4) out[13 + i] = v;
+        if (!dia && i < 4) out[13 + i] = 0.0;
+    }
+}
+
+// The monomials of every chunk of an octant as k_moments multiplies them: for product
+// p and lane l monomial l & 15 of node mom_node(l >> 4, p), zero past the octant's end
+// (a block per chunk).
+template <typename T>
+__global__ __launch_bounds__(256) void k_monomials(Geo g, Dev d)
+{
+    const int chunk = (int)blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int o = 0;
+    while (o < 7 && chunk >= mom_chunk(g, o + 1)) ++o;
+    const Monomial mono(lane & 15);
+    for (int p = w; p < 16; p += 4) {
+        const int l = (chunk - mom_chunk(g, o)) * MCHUNK + mom_node<T>(lane >> 4, p);
+        const double *t = d.nt64 + 4 * ((size_t)g.obase[o] + min(l, g.osize[o] - 1));
+        d.mono[((size_t)chunk * 16 + p) * 64 + lane] = mono(t[0], t[1], t[2], l < g.osize[o] ? t[3] : 0.0);
+    }
+}
+
+hipError_t launch_monomials(const Geo &g, const Dev &d, bool fp32, hipStream_t s)
+{
+    const dim3 grid(mom_chunk(g, 8));
+    if (fp32) hipLaunchKernelGGL(k_monomials<float>, grid, dim3(256), 0, s, g, d);
+    else hipLaunchKernelGGL(k_monomials<double>, grid, dim3(256), 0, s, g, d);
+    return hipGetLastError();
 }
 
 // The octant sums from the segments that the sweep stored: 16 cells of one
@@ -532,7 +550,7 @@ static void moments(const Target &t, hipStream_t s)
                            GSIS_SPAN(t.span(K_CELL1)));
         return;
     }
-    hipLaunchKernelGGL((k_moments<T, DIA>), dim3(t.nblk[K_MOM]), dim3(64), 0, s, GSIS_SPAN(t.span(K_MOM)));
+    hipLaunchKernelGGL(k_moments<T>, dim3(t.nblk[K_MOM]), dim3(64 * MOM_WAVES), 0, s, GSIS_SPAN(t.span(K_MOM)));
 }
 
 hipError_t launch_moments(const Target &t, hipStream_t s, bool swept)

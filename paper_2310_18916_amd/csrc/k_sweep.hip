@@ -295,12 +295,13 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
     if constexpr (SUM) {
         typedef double d2 __attribute__((ext_vector_type(2)));
         const Monomial mono(lane & 15);
-        const int lb = vb * bs + mw * 64 + 16 * (lane >> 4);
+        const int lb = vb * bs + mw * 64;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
-            const gptr<const d2> tp = (gptr<const d2>)C.d.nt64 + 2 * ((size_t)g.obase[o] + min(lb + k, g.osize[o] - 1));
+            const int ln = lb + mom_node<T>(lane >> 4, k);
+            const gptr<const d2> tp = (gptr<const d2>)C.d.nt64 + 2 * ((size_t)g.obase[o] + min(ln, g.osize[o] - 1));
             const d2 t0 = tp[0], t1 = tp[1];
-            const double m = mono(t0.x, t0.y, t1.x, lb + k < g.osize[o] ? t1.y : 0.0);
+            const double m = mono(t0.x, t0.y, t1.x, ln < g.osize[o] ? t1.y : 0.0);
             if (BLDS) smono[mw][k * 64 + lane] = m;
             else {
                 bmono[BLDS ? 0 : k] = m;
@@ -332,7 +333,7 @@ void k_sweep(GSIS_SPAN_ARGS, int plane, int eoff)
         wave_fence();
 #pragma unroll
         for (int k = 0; k < (SUM ? 16 / V : 0); ++k)
-            areg[k] = *(const vec *)(&stile[mw][SUM ? (lane & 15) * TP + (16 * (lane >> 4) + k * V) * sizeof(T) : 0]);
+            areg[k] = *(const vec *)(&stile[mw][SUM ? (lane & 15) * TP + mom_node<T>(lane >> 4, k * V) * sizeof(T) : 0]);
         wave_fence();
     };
     auto multiply = [&](int k) {
