@@ -200,7 +200,7 @@ gsis_status gsis_set_boundary(gsis_ctx *ctx, int face, int kind, const double u[
 gsis_status gsis_set_wall_flux(gsis_ctx *ctx, int model);
 
 /* lean != 0 leaves out of the workspace what only saves time: of a VDF above
- * 256 MB the segments of the moment sums (6 to 20% of it), with order 2 one array
+ * 256 MB the segments of the moment sums (6 to 25% of it), with order 2 one array
  * of the VDF's size per VDF.  Results are the same to the bit.  Default 0; must
  * precede gsis_workspace_size and gsis_bind_workspace (in a batch its own calls);
  * ESTATE once bound. */

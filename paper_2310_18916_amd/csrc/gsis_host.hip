@@ -96,25 +96,36 @@ double vdf_bytes(const gsis_ctx *c)
 
 // Whether the sweep forms the moment sums of these cases (on boxes): where
 // reading the VDF again costs more than the products in the sweep, that is once
-// it no longer fits the 256 MB of memory-side cache.  Sweep + moments, formed and
-// not: 0.24 and 0.21 ms on 16^3 cells x 16^3 nodes FP64 (134 MB), 0.69 and 0.75 on
-// 24^3 x 20^3 (0.9 GB), 4.2 and 4.6 on 32^3 x 32^3, 34.7 and 37.6 on 64 x 48 x 48
-// x 40^3; FP32 0.20 and 0.17, 0.48 and 0.50, 2.3 and 2.65; with
-// a finite time step, FP64, 0.90 and 1.06 on 24^3 x 20^3.  The segments take 6% of
-// an FP64 VDF, 12% of an FP32 one; not where that would leave no room on a 288 GB
-// card.  The second order keeps them in an array that it has.
+// it no longer fits the 256 MB of memory-side cache.  Sweep + moments in ms, formed
+// and not: 0.47 and 0.47 on 20^3 cells x 20^3 nodes FP64 (0.5 GB), 0.68 and 0.73 on
+// 24^3 x 20^3, 4.2 and 4.6 on 32^3 x 32^3, 33.6 and 37.3 on 64 x 48 x 48 x 40^3; FP32
+// 0.48 and 0.49, 2.3 and 2.5, and 23.7 and 25.4 on 64 x 64 x 96 x 32^3; with a finite
+// time step, FP64, 0.91 and 1.44 on 24^3 x 20^3; two VDFs 20.2 and 21.4 on 48 x 48 x 64
+// x 24^3, FP32 10.0 and 9.9.
+//
+// A segment is 128 bytes a cell (160 with two VDFs), however few of its 256 nodes the
+// octant has: not where it holds fewer than 128 on average (100 with two VDFs or, FP64,
+// a per-point term).  3.0 and 2.5 ms on 62^3 x 10^3 (125 nodes an octant), 4.1 and 3.0
+// on 78^3 x 8^3, 32 and 18 on 150^3 x 4^3, FP64; FP32 3.2 and 3.2, 4.4 and 3.8, 21 and
+// 13; 2.6 and 2.9 on 57^3 x 11^3.  Two VDFs 3.8 and 4.0 on 49^3 x 10^3 and 6.1 and 5.3 on
+// 62^3 x 8^3.  So the segments take 6% of an FP64 VDF and 12% of an FP32 one where the
+// octants are large, at most 13 and 25%.  Not where they would leave no room on a
+// 288 GB card.  The second order keeps them in an array that it has.
 bool forms_sums(const gsis_ctx *const *cs, size_t nc)
 {
     const Geo &g0 = cs[0]->g;
-    double bytes = 0, all = 0;
+    double bytes = 0, all = 0, points = 0, records = 0;
     for (size_t k = 0; k < nc; ++k) {
         const Geo &g = cs[k]->g;
         double seg = 0;
         for (int o = 0; o < 8; ++o) seg += (g.osize[o] + MSEG - 1) / MSEG;
+        points += (double)g.nv * g.ncell;
+        records += seg * g.ncell;
         bytes += vdf_bytes(cs[k]);
         all += vdf_bytes(cs[k]) + seg * g.ncell * (g.species == GSIS_DIATOMIC ? 160 : 128);
     }
-    return !g0.umesh && (g0.order == 2 || all <= 240e9) && bytes > 256e6;
+    return !g0.umesh && (g0.order == 2 || all <= 240e9) && bytes > 256e6 &&
+           points >= (g0.species == GSIS_DIATOMIC || (!cs[0]->fp32 && (g0.inv_dt != 0.0 || g0.order == 2)) ? 100 : 128) * records;
 }
 
 // Room for the segments: where the sweep's tile fills them.  A caller's own tile
@@ -129,7 +140,7 @@ void choose_segments(gsis_ctx *c)
 // The built-in sweep tile of one case, or of the average case of a batch.
 //
 // A launch runs one tile plane, so what decides is the waves a plane has, W =
-// tiles x nodes / 64 / planes (1024 SIMDs want several each).  Larger tiles
+// tiles / planes x waves for the nodes of the octants (1024 SIMDs want several each).  Larger tiles
 // read fewer inflow values again; smaller ones make more and wider planes and
 // shorter chains.  Each line stands where two neighbours measured equal (ms per
 // pass, sweep and moments, boxes of 8 to 96 cells by 12 to 40 nodes a side):
@@ -165,7 +176,9 @@ Tile tile_by_size(const gsis_ctx *const *cs, size_t nc)
         for (size_t k = 0; k < nc; ++k) {
             const Geo &g = cs[k]->g;
             const int a = up(g.nx, tx), b = up(g.ny, ty), c = up(g.nz, tz);
-            w += (double)a * b * c / (a + b + c - 2) * g.nv / 64.0;
+            double waves = 0;
+            for (int o = 0; o < 8; ++o) waves += (g.osize[o] + 63) / 64;
+            w += (double)a * b * c / (a + b + c - 2) * waves;
         }
         return w / (double)nc;
     };

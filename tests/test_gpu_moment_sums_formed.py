@@ -38,6 +38,11 @@ def test_formed(name):
     assert not s.forms_sums()
 
 
+def test_not_formed():
+    make, dtype = CASES["few_nodes"]
+    assert not Solver(make(), dtype).forms_sums()
+
+
 def test_formed_batch():
     cases = [box((5, 9, 3), (60, 60, 60)), box((4, 4, 4), (80, 81, 82)), box((13, 3, 6), (31, 30, 33))]
     b = Batch(cases, "fp64")

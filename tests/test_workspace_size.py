@@ -55,6 +55,16 @@ def test_lean(n, dtype, kw):
         assert ctx.workspace_size() == full
 
 
+@pytest.mark.parametrize("dtype, kw", KINDS)
+@pytest.mark.parametrize("m", [4, 6, 8])
+def test_few_nodes(m, dtype, kw):
+    """A segment holds 256 nodes; octants of 8 to 64 would leave it all but empty."""
+    ctx = G.Context(box((160, 120, 100), (m, m, m), **kw), dtype)
+    full = ctx.workspace_size()
+    ctx.set_lean()
+    assert ctx.workspace_size() == full
+
+
 def test_batch_own_tile():
     cases = [box((24, 24, 24), (24, 24, 24)), box((9, 5, 4), (16, 16, 16))]
     for tile, lean in (((4, 4, 4, 128), False), (None, True)):
