@@ -70,12 +70,25 @@ SWEEP_SOURCES = ("paper_2310_18916_amd/csrc/k_sweep.hip", "paper_2310_18916_amd/
                  "paper_2310_18916_amd/csrc/gsis_sweep_math.h")
 
 
-def moment_read_gbs(nbytes, ms):
-    """Rate at which the moment phase read the VDF; None where it did not: the sweep
-    of a large state forms the sums and the phase adds up its segments, in less time
-    than reading at the HBM peak would take."""
-    gbs = nbytes / (ms * 1e-3) / 1e9
-    return gbs if gbs <= HBM_PEAK_GBS else None
+def moment_bytes(case, dtype, formed):
+    """Bytes the moment phase reads: the VDF, or, where the sweep formed the sums, its
+    segments (records of 16 sums, 4 more for a second VDF, of every cell per 256 nodes
+    of an octant)."""
+    import numpy as np
+    nvdf = 2 if case.species == 1 else 1
+    if not formed:
+        return case.nfluid * case.nvel * nvdf * (8 if dtype == "fp64" else 4)
+    if case.velocity_list is not None:
+        octants = np.bincount(((np.asarray(case.velocity_list)[:, :3] < 0) @ [1, 2, 4]).astype(int), minlength=8)
+    else:
+        neg = []
+        for a in range(3):
+            x = None if case.nodes is None else case.nodes[a]
+            if x is None:
+                x = case.vmin[a] + np.arange(case.nv[a]) * ((case.vmax[a] - case.vmin[a]) / (case.nv[a] - 1))
+            neg.append(int((np.asarray(x) < 0).sum()))
+        octants = [np.prod([neg[a] if (o >> a) & 1 else case.nv[a] - neg[a] for a in range(3)]) for o in range(8)]
+    return case.ncell * sum(-(-int(k) // 256) for k in octants) * 8 * (16 + (4 if nvdf == 2 else 0))
 
 
 def sweep_traffic(dtype, tile, workload_name):
@@ -138,7 +151,7 @@ def run_gpu(case, dtype, steps, warmup, macro_iters, tile):
     s.profile(False)
     prof = s.profile_read(reset=True)
     return {"seconds": t1 - t0, "prof": prof, "eps": [float(x) for x in eps], "solver": s, "tune": tune,
-            "tile": s.get_tile(), "moments": s.moments()}
+            "tile": s.get_tile(), "forms_sums": s.forms_sums(), "moments": s.moments()}
 
 
 def converge(case, dtype, tile, tol=1e-6, max_iters=200, pre=None, full=True):
@@ -436,7 +449,8 @@ def refined_mesh(steps, warmup):
         res[dtype] = {"value": pts * steps / r["seconds"], "ms_per_pass": r["seconds"] / steps * 1e3,
                       "phases_ms_per_pass": {k: v[0] / steps for k, v in prof.items() if v[1]},
                       "sweep_gbs": pts * esz / (sweep_ms / n * 1e-3) / 1e9,
-                      "moments_gbs": moment_read_gbs(pts * esz, mom_ms / n), "sweep_tile": r["tile"]}
+                      "moments_gbs": moment_bytes(case, dtype, r["forms_sums"]) / (mom_ms / n * 1e-3) / 1e9,
+                      "moments_read": "segments" if r["forms_sums"] else "vdf", "sweep_tile": r["tile"]}
         del r
         torch.cuda.empty_cache()
     return res
@@ -513,9 +527,10 @@ def main():
     mom_ms, mom_n = prof["moments"]
     nvdf = 2 if case.species == 1 else 1                                # the diatomic gas carries f0 and f1
     sweep_bytes = pts * nvdf * esz * (2 if case.inv_dt != 0 else 1)   # write f^{n+1/2} (+ read f^n if 1/dt != 0)
-    mom_bytes = pts * nvdf * esz                                       # read f^{n+1/2}
+    formed = r["forms_sums"]
+    mom_bytes = moment_bytes(case, dtype, formed)                      # read f^{n+1/2}, or the sweep's segments
     sweep_gbs = sweep_bytes / (sweep_ms / sweep_n * 1e-3) / 1e9
-    mom_gbs = moment_read_gbs(mom_bytes, mom_ms / mom_n)
+    mom_gbs = mom_bytes / (mom_ms / mom_n * 1e-3) / 1e9
     dominant = "sweep" if sweep_ms >= mom_ms else "moments"
     ach = sweep_gbs if dominant == "sweep" else mom_gbs
     traffic = sweep_traffic(dtype, r["tile"], a.workload) if dominant == "sweep" else None
@@ -547,9 +562,11 @@ def main():
                      "algorithmic_bytes": sweep_bytes if dominant == "sweep" else mom_bytes},
         "phases_ms_per_step": {k: v[0] / steps for k, v in prof.items()},
         "kinetic_only_updates_per_s": pts * steps / ((prof["prep"][0] + sweep_ms + mom_ms) * 1e-3),
-        "kinetic_pass_gbs": (sweep_bytes + (mom_bytes if mom_gbs else 0)) / ((sweep_ms + mom_ms) / sweep_n * 1e-3) / 1e9,
+        # the sweep writes the segments that the moments read
+        "kinetic_pass_gbs": (sweep_bytes + mom_bytes * (2 if formed else 1)) / ((sweep_ms + mom_ms) / sweep_n * 1e-3) / 1e9,
         "sweep_gbs": sweep_gbs,
         "moments_gbs": mom_gbs,
+        "moments_read": "segments" if formed else "vdf",
         "final_eps": eps_head,
         "sweep_tile": tile_head,
         "autotune_top": tune_top,
