@@ -193,7 +193,13 @@ Tile tile_by_size(const gsis_ctx *const *cs, size_t nc)
     return {4, 4, W(4, 4, 4) < (fp32 ? 1000 : 500) ? 2 : 4, 256};
 }
 
-// ... and within the 1023 tiles per axis that a packed tile index holds.
+// Whether the tiles of a box number at most 1023 per axis, as a packed tile index holds.
+bool tile_fits(const Geo &g, int tx, int ty, int tz)
+{
+    return (g.nx + tx - 1) / tx <= 1023 && (g.ny + ty - 1) / ty <= 1023 && (g.nz + tz - 1) / tz <= 1023;
+}
+
+// The built-in tile within that limit.
 Tile pick_tile(const gsis_ctx *const *cs, size_t nc)
 {
     Tile t = tile_by_size(cs, nc);
@@ -1766,8 +1772,7 @@ gsis_status gsis_set_tile(gsis_ctx *ctx, int tx, int ty, int tz, int block)
         const int nw = sweep_shape_waves(ctx->fp32, tx, ty);
         if (nw > 1 && block != 64 * nw) return fail(ctx, GSIS_EINVAL, "block must be 64 x the waves of this tile's wave grid");
         if (nw == 1 && block != 64 && block != 128 && block != 256) return fail(ctx, GSIS_EINVAL, "block must be 64, 128 or 256");
-        int ntx = (ctx->g.nx + tx - 1) / tx, nty = (ctx->g.ny + ty - 1) / ty, ntz = (ctx->g.nz + tz - 1) / tz;
-        if (ntx > 1023 || nty > 1023 || ntz > 1023) return fail(ctx, GSIS_EINVAL, "too many tiles per axis");
+        if (!tile_fits(ctx->g, tx, ty, tz)) return fail(ctx, GSIS_EINVAL, "too many tiles per axis");
         ctx->tx = tx; ctx->ty = ty; ctx->tz = tz; ctx->bs = block;
         ctx->tile_auto = false;
     }
@@ -1795,9 +1800,11 @@ gsis_status gsis_autotune(gsis_ctx *ctx, int reps, int *cfg_out, double *ms_out,
         int tx = shapes[2 * k], ty = shapes[2 * k + 1];
         if (!sweep_shape_supported(ctx->fp32, dia, tx, ty)) continue;
         const int nw = sweep_shape_waves(ctx->fp32, tx, ty);
-        for (int tz : {tx / 2, tx, 2 * tx, 4 * tx})
+        for (int tz : {tx / 2, tx, 2 * tx, 4 * tx}) {
+            if (!tile_fits(g, tx, ty, tz)) continue;
             for (int bs : {64, 128, 256})
-                if (nw == 1 || bs == 64 * nw) cands.push_back({tx, ty, std::max(tz, 1), bs, 0.0});
+                if (nw == 1 || bs == 64 * nw) cands.push_back({tx, ty, tz, bs, 0.0});
+        }
     }
     int save[4] = {ctx->tx, ctx->ty, ctx->tz, ctx->bs};
     {
@@ -2305,9 +2312,13 @@ gsis_status gsis_batch_autotune(gsis_batch *b, int reps, int *cfg_out, double *m
         int tx = shapes[2 * k], ty = shapes[2 * k + 1];
         if (!sweep_shape_supported(b->fp32, b->dia, tx, ty)) continue;
         const int nw = sweep_shape_waves(b->fp32, tx, ty);
-        for (int tz : {tx / 2, tx, 2 * tx, 4 * tx})
+        for (int tz : {tx / 2, tx, 2 * tx, 4 * tx}) {
+            bool fits = true;
+            for (const gsis_ctx *c : b->cs) fits = fits && tile_fits(c->g, tx, ty, tz);
+            if (!fits) continue;
             for (int bs : {64, 128, 256})
-                if (nw == 1 || bs == 64 * nw) cands.push_back({tx, ty, std::max(tz, 1), bs, 0.0});
+                if (nw == 1 || bs == 64 * nw) cands.push_back({tx, ty, tz, bs, 0.0});
+        }
     }
     (void)c0;
     const int save[4] = {b->tx, b->ty, b->tz, b->bs};
