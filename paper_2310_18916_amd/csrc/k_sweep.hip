@@ -51,9 +51,9 @@ namespace gsis {
 // of one tile are one segment.  The products (16 matrix instructions of 64 cycles
 // per 16 cells, against about 450 cycles per cell for everything else) are made
 // one group of 16 cells late, between the next group's updates.  Sweep + moments
-// before and after: 26.5 + 11.1 and 34.3 + 1.0 ms on 64 x 48 x 48 cells x 40^3
-// nodes in FP64, 16.4 + 8.6 and 22.2 + 1.5 on 96 x 64 x 64 x 32^3 in FP32, 9.5 +
-// 2.6 and 9.9 + 0.2 with the second-order term on 40^3 x 32^3.  What the sweep
+// with the sums apart and formed: 26.2 + 11.4 and 34.0 + 1.0 ms on 64 x 48 x 48 cells x
+// 40^3 nodes in FP64, 15.6 + 9.4 and 22.3 + 1.5 on 96 x 64 x 64 x 32^3 in FP32, 12.7 +
+// 2.9 and 10.0 + 0.2 with the second-order term on 40^3 x 32^3.  What the sweep
 // loses: 2.4 ms to the products (without them 31.3, the FP64 figure), 0.7 to the
 // segments' stores, 3 to two waves per SIMD instead of three.  There an inflow
 // value of the next slab is read into the register that this slab's has left
@@ -641,8 +641,8 @@ template <typename T, int TX, int TY, int WX, int WY, bool SUM>
 static void sweep_launch(const Target &t, int p, hipStream_t s, unsigned nblk, bool mask, int eoff)
 {
     // two register planes only for the small slabs
-    constexpr bool kDia = TX * TY <= 32 && !(SUM && TX == 8 && sizeof(T) == 4);
-    constexpr bool kMono = !(SUM && TX == 8 && sizeof(T) == 8);
+    constexpr bool kDia = TX * TY <= 32;
+    constexpr bool kMono = !(SUM && TX == 8);
     const dim3 grid(nblk);
     const Span sp{t.cases, t.pmap ? t.pmap[p] : nullptr};
 #define GSIS_SWEEP(D, R, M) \
@@ -701,13 +701,14 @@ int sweep_shapes(bool fp32, int *out, int max)
 }
 
 // Four waves over the nodes of a 4 x 4 tile make a segment, and of an 8 x 4 tile in
-// FP64 with two VDFs (19.7 + 0.5 ms against 20.1 + 0.5 for 4 x 4 on 64 x 48 x 48 cells
-// x 24^3 nodes) and in FP32 with one (24.0 + 1.5 against 16.4 + 10.9 with the sums
-// apart, on 96 x 64 x 64 x 32^3).  FP64 with one gains nothing from it (38.7 + 1.0
-// against 27.5 + 12.6 on 64 x 48 x 48 x 40^3).
+// FP64 with two VDFs (20.1 + 0.4 ms against 20.4 + 0.4 for 4 x 4 on 64 x 48 x 48 cells
+// x 24^3 nodes, and 16.6 + 5.0 with the sums apart).  With one VDF an 8 x 4 slab's
+// registers leave no room for the products: 38.7 + 1.0 against 33.5 + 11.4 with the
+// sums apart in FP64 (64 x 48 x 48 x 40^3), 25.7 + 1.5 against 15.5 + 9.4 in FP32 (96 x
+// 64 x 64 x 32^3, spilling).
 bool tile_forms_sums(bool fp32, bool dia, int tx, int ty, int bs)
 {
-    return bs == 256 && ty == 4 && (tx == 4 || dia != fp32);
+    return bs == 256 && ty == 4 && (tx == 4 || (dia && !fp32));
 }
 
 bool sweep_forms_sums(const Target &t) { return t.mseg && tile_forms_sums(t.fp32, t.dia, t.tx, t.ty, t.bs); }
@@ -721,8 +722,7 @@ hipError_t launch_sweep(const Target &t, hipStream_t s)
     for (int p = 0; p < t.nplane; ++p) {
         if (t.npblk[p] == 0) continue;
         if (sweep_forms_sums(t)) {
-            if (t.fp32 && tx == 8) sweep_plane<float, 8, 4, 1, 1, true>(t, p, s);
-            else if (t.fp32) sweep_plane<float, 4, 4, 1, 1, true>(t, p, s);
+            if (t.fp32) sweep_plane<float, 4, 4, 1, 1, true>(t, p, s);
             else if (tx == 4) sweep_plane<double, 4, 4, 1, 1, true>(t, p, s);
             else sweep_plane<double, 8, 4, 1, 1, true>(t, p, s);
         } else if (t.fp32) {

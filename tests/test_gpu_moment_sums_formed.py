@@ -1,5 +1,6 @@
 """Which kernel makes the moment sums: the sweep really forms them in the cases of
-test_gpu_moment_segments.py and doesn't in their 128-thread twins, and the
+test_gpu_moment_segments.py and doesn't in their 128-thread twins nor in an FP32 tile
+8 cells wide, and the
 compiled variants that those leave out (second order with two VDFs and in FP32, a
 per-point term with solid cells and in FP32) give the same bits both ways.
 
@@ -23,15 +24,14 @@ if not torch.cuda.is_available():
 from paper_2310_18916_amd.gsis import Batch, Solver  # noqa: E402
 from test_gpu_moment_segments import CASES, GAS, box, solid  # noqa: E402
 
-TILE = {"over_fp32_8x4": (8, 4, 8, 256)}      # the tile asked for there
-WIDTH = {"over_fp32_8x4": 8, "two_vdfs_wide": 8, "two_vdfs_solid": 4, "solid": 4}
+WIDTH = {"two_vdfs_wide": 8, "two_vdfs_solid": 4, "solid": 4}
 
 
-@pytest.mark.parametrize("name", [n for n in CASES if n != "few_nodes"])
+@pytest.mark.parametrize("name", [n for n in CASES if n not in ("few_nodes", "over_fp32_8x4")])
 def test_formed(name):
     make, dtype = CASES[name]
     case = make()
-    s = Solver(case, dtype, tile=TILE.get(name))
+    s = Solver(case, dtype)
     assert s.forms_sums()
     assert s.get_tile()[0] == WIDTH.get(name, s.get_tile()[0])
     s.set_tile(4, 4, 4, 128)
@@ -39,8 +39,9 @@ def test_formed(name):
 
 
 def test_not_formed():
-    make, dtype = CASES["few_nodes"]
-    assert not Solver(make(), dtype).forms_sums()
+    for name, tile in (("few_nodes", None), ("over_fp32_8x4", (8, 4, 8, 256))):
+        make, dtype = CASES[name]
+        assert not Solver(make(), dtype, tile=tile).forms_sums()
 
 
 def test_formed_batch():
