@@ -696,10 +696,11 @@ __global__ __launch_bounds__(128) void k_mac_const(GSIS_SPAN_ARGS)
 // both sides) and an advance launch per iteration: cavity of 48^3 cells 18.9
 // (32.6), nitrogen block of 64 x 48 x 48 cells 29.2 (45.7), cavity of 12 x 11
 // x 13 cells with the Grad-13 wall flux 11.8 (20.7).  What bounds it now: an
-// iteration moves about 30 MB between the XCDs' caches and the memory side
-// (half of the time on 48^3 cells), then the latency of the three dependent
-// phases, twice over for the tiles that do not fit the chip at once (five
-// blocks of 30 KB LDS per CU); the boundary faces' 1-D sums add 3.6 us.
+// iteration fetches 16.6 MB and writes 9.0 MB between the XCDs' caches and the
+// memory side on 48^3 cells (FETCH_SIZE, WRITE_SIZE; about 5 us of the 18.9 at
+// the rate of a large copy), then the latency of the three dependent phases,
+// twice over for the tiles that do not fit the chip at once (five blocks of
+// 30 KB LDS per CU); the boundary faces' 1-D sums add 3.6 us.
 constexpr int MT = 4, MH = MT + 2, MHN = MH * MH * MH;
 constexpr int MFN = 3 * (MT + 1) * MT * MT;   // faces of a tile
 constexpr int MBC = 48;                       // boundary faces finished together
